@@ -106,6 +106,17 @@ def work_model(locregs, sz):
         # x down pass + the three kinetic parts -> compressed output pattern
         add("back_x", sz * (q + kx + ky + kz + nout),
             2 * 2 * 4 * o1 * o2 * _count_down(n0, e) + 3 * 8 * o0 * o1 * o2)
+        # the plane kernels: compressed phi -> (x, y)-fine planes; the z column
+        # pass; the z kinetic part; x and y kinetic parts, y and x down passes
+        # and the compression
+        fx, fy = 2 * 2 * 4 * n1 * n2 * _count_up(n0), 2 * 2 * 2 * r0 * n2 * _count_up(n1)
+        add("up_plane", sz * (nin + g1), fx + fy)
+        add("col_tile", sz * (g1 + g + g2),
+            2 * 2 * r0 * r1 * _count_up(n2) + 3 * g + 2 * 2 * r0 * r1 * _count_down(n2, e))
+        add("kin_slab", sz * (nin + kz), 2 * 58 * kz)
+        add("back_plane", sz * (nin + g2 + kz + nout),
+            2 * 2 * 2 * r0 * o2 * _count_down(n1, e) + 2 * 2 * 4 * o1 * o2 * _count_down(n0, e)
+            + 2 * 58 * (kx + ky) + 3 * 8 * o0 * o1 * o2)
     return out
 
 
@@ -124,7 +135,7 @@ def path_bytes(locregs, sz):
 
 def source_hash():
     h = hashlib.sha256()
-    for f in ("wvl_kernels.hip", "wvl_fused.hip", "wvl_static.hip", "wvl_host.cpp",
+    for f in ("wvl_kernels.hip", "wvl_fused.hip", "wvl_planes.hip", "wvl_static.hip", "wvl_host.cpp",
               "wvl_internal.h", "wvl_filters.h"):
         with open(os.path.join(ROOT, "paper_1401_7441_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())

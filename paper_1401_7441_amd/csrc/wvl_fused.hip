@@ -344,7 +344,7 @@ __global__ __launch_bounds__(256) void k_up_z(const SfDev* __restrict__ sfs,
                                               const SfWork* __restrict__ wk,
                                               const T* __restrict__ ws,
                                               const int64_t* __restrict__ fine_off,
-                                              T* __restrict__ fine) {
+                                              T* __restrict__ fine, int padded) {
   const SfWork& w = wk[blockIdx.y];
   const SfDev& sf = sfs[w.id];
   const int N0 = sf.n[0], N1 = sf.n[1], N2 = sf.n[2];
@@ -352,8 +352,10 @@ __global__ __launch_bounds__(256) void k_up_z(const SfDev* __restrict__ sfs,
   const int64_t plane = (int64_t)R1 * R0;
   const int64_t col = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (col >= plane) return;
-  const T* in0 = ws + w.g1 + col;                 // a3 = 0
-  const T* in1 = in0 + (int64_t)N2 * plane;       // a3 = 1
+  // (padded: the plane kernels' G1 rows)
+  const int64_t ld = padded ? pad16(R0) : R0, gplane = R1 * ld;
+  const T* in0 = ws + w.g1 + (col / R0) * ld + col % R0;   // a3 = 0
+  const T* in1 = in0 + (int64_t)N2 * gplane;                // a3 = 1
   T* out = fine + fine_off[w.id] + col;
   constexpr int PF = pf_up_y<T>();   // the same stream shape as k_up_y
   T xs[16], xd[16], f0[PF], f1[PF];
@@ -361,8 +363,8 @@ __global__ __launch_bounds__(256) void k_up_z(const SfDev* __restrict__ sfs,
   for (int k = 0; k < 16; ++k) xs[k] = xd[k] = T(0);
 #pragma unroll
   for (int d = 0; d < PF; ++d) {
-    f0[d] = ld_clamp(in0, d, N2, plane);
-    f1[d] = ld_clamp(in1, d, N2, plane);
+    f0[d] = ld_clamp(in0, d, N2, gplane);
+    f1[d] = ld_clamp(in1, d, N2, gplane);
   }
   const int qend = N2 + 14;
   for (int q0 = 0; q0 <= qend; q0 += 16, out += 32 * plane) {
@@ -370,8 +372,8 @@ __global__ __launch_bounds__(256) void k_up_z(const SfDev* __restrict__ sfs,
     for (int u = 0; u < 16; ++u) {
       const int q = q0 + u, sp = u % PF;
       const T v0 = f0[sp], v1 = f1[sp];
-      f0[sp] = ld_clamp(in0, q + PF, N2, plane);
-      f1[sp] = ld_clamp(in1, q + PF, N2, plane);
+      f0[sp] = ld_clamp(in0, q + PF, N2, gplane);
+      f1[sp] = ld_clamp(in1, q + PF, N2, gplane);
       if (q <= qend) {
         xs[u] = q < N2 ? v0 : T(0);
         xd[u] = q < N2 ? v1 : T(0);
@@ -402,7 +404,8 @@ __global__ __launch_bounds__(256) void k_pot_column(const SfDev* __restrict__ sf
                                                     T* __restrict__ ws, const T* __restrict__ pot,
                                                     int nf1, int nf2,
                                                     double* __restrict__ epart,
-                                                    const double* __restrict__ conf, double hh) {
+                                                    const double* __restrict__ conf, double hh,
+                                                    int padded) {
   const SfWork& w = wk[blockIdx.y];
   const SfDev& sf = sfs[w.id];
   // confining potential a |r - R|^4 (a = 0: none); fine point p of an axis
@@ -416,10 +419,12 @@ __global__ __launch_bounds__(256) void k_pot_column(const SfDev* __restrict__ sf
   double eacc = 0.0;
   if (col < ncol) {
     const int px = (int)(col % R0), py = (int)(col / R0);
-    const T* in0 = ws + w.g1 + col;
-    const T* in1 = in0 + (int64_t)N2 * ncol;
-    T* out0 = ws + w.g2 + col;
-    T* out1 = out0 + (int64_t)O2 * ncol;
+    // G1 and G2 rows R0 apart (padded, the plane kernels': pad16(R0))
+    const int64_t ld = padded ? pad16(R0) : R0, pst = R1 * ld;
+    const T* in0 = ws + w.g1 + py * ld + px;
+    const T* in1 = in0 + (int64_t)N2 * pst;
+    T* out0 = ws + w.g2 + py * ld + px;
+    T* out1 = out0 + (int64_t)O2 * pst;
     const int64_t vstride = (int64_t)nf1 * nf2;
     // no potential array: V = 0 (the confinement alone)
     const T* vp = pot ? pot + ((int64_t)(2 * sf.lo[2]) * nf2 + (2 * sf.lo[1] + py)) * nf1 +
@@ -435,8 +440,8 @@ __global__ __launch_bounds__(256) void k_pot_column(const SfDev* __restrict__ sf
     for (int k = 0; k < 16; ++k) xs[k] = xd[k] = a0[k] = a1[k] = T(0);
 #pragma unroll
     for (int d = 0; d < PF; ++d) {
-      f0[d] = ld_clamp(in0, d, N2, ncol);
-      f1[d] = ld_clamp(in1, d, N2, ncol);
+      f0[d] = ld_clamp(in0, d, N2, pst);
+      f1[d] = ld_clamp(in1, d, N2, pst);
       fve[d] = vp ? ld_clamp(vp, 2 * d, R2, vstride) : T(0);
       fvo[d] = vp ? ld_clamp(vp, 2 * d + 1, R2, vstride) : T(0);
     }
@@ -455,8 +460,8 @@ __global__ __launch_bounds__(256) void k_pot_column(const SfDev* __restrict__ sf
           v1 = f1[sp];
           pve = fve[sp];
           pvo = fvo[sp];
-          f0[sp] = ld_clamp(in0, q + PF, N2, ncol);
-          f1[sp] = ld_clamp(in1, q + PF, N2, ncol);
+          f0[sp] = ld_clamp(in0, q + PF, N2, pst);
+          f1[sp] = ld_clamp(in1, q + PF, N2, pst);
           if (vp) {
             fve[sp] = ld_clamp(vp, 2 * (q + PF), R2, vstride);
             fvo[sp] = ld_clamp(vp, 2 * (q + PF) + 1, R2, vstride);
@@ -465,8 +470,8 @@ __global__ __launch_bounds__(256) void k_pot_column(const SfDev* __restrict__ sf
         if (q <= qend) {
         if constexpr (PF == 0) {
           const int p = 2 * q;
-          v0 = q < N2 ? in0[(int64_t)q * ncol] : T(0);
-          v1 = q < N2 ? in1[(int64_t)q * ncol] : T(0);
+          v0 = q < N2 ? in0[(int64_t)q * pst] : T(0);
+          v1 = q < N2 ? in1[(int64_t)q * pst] : T(0);
           pve = (vp && p < R2) ? vp[(int64_t)p * vstride] : T(0);
           pvo = (vp && p + 1 < R2) ? vp[(int64_t)(p + 1) * vstride] : T(0);
         }
@@ -504,8 +509,8 @@ __global__ __launch_bounds__(256) void k_pot_column(const SfDev* __restrict__ sf
         const int sl = (u + 1) & 15;
         const int pp = q - 15 + e;
         if (pp >= 0 && pp < O2) {
-          out0[(int64_t)pp * ncol] = a0[sl];
-          out1[(int64_t)pp * ncol] = a1[sl];
+          out0[(int64_t)pp * pst] = a0[sl];
+          out1[(int64_t)pp * pst] = a1[sl];
         }
         a0[sl] = T(0);
         a1[sl] = T(0);
@@ -1213,29 +1218,31 @@ int launch_up(int f64, void* stream, int axis, const SfWork* wk, const SfDev* sf
 }
 
 int launch_up_z(int f64, void* stream, const SfWork* wk, const SfDev* sf, int nsf, int gridx,
-                const void* ws, const int64_t* fine_off, void* fine) {
+                const void* ws, const int64_t* fine_off, void* fine, int padded) {
   if (nsf == 0) return 0;
   const dim3 g((unsigned)gridx, (unsigned)nsf);
   if (f64)
     hipLaunchKernelGGL(k_up_z<double>, g, dim3(256), 0, (hipStream_t)stream, sf, wk,
-                       (const double*)ws, fine_off, (double*)fine);
+                       (const double*)ws, fine_off, (double*)fine, padded);
   else
     hipLaunchKernelGGL(k_up_z<float>, g, dim3(256), 0, (hipStream_t)stream, sf, wk,
-                       (const float*)ws, fine_off, (float*)fine);
+                       (const float*)ws, fine_off, (float*)fine, padded);
   return (int)hipGetLastError();
 }
 
 int launch_pot_column(int f64, void* stream, const SfDev* sf, const SfWork* wk, int sf0, int nsf,
                       int gridx, void* ws, const void* pot, int nf1, int nf2, double* epart,
-                      const double* conf, double hh) {
+                      const double* conf, double hh, int padded) {
   if (nsf == 0 || gridx == 0) return 0;
   const dim3 g((unsigned)gridx, (unsigned)nsf);
   if (f64)
     hipLaunchKernelGGL(k_pot_column<double>, g, dim3(256), 0, (hipStream_t)stream, sf, wk, sf0,
-                       (double*)ws, (const double*)pot, nf1, nf2, epart, conf, hh);
+                       (double*)ws, (const double*)pot, nf1, nf2, epart, conf, hh,
+                       padded);
   else
     hipLaunchKernelGGL(k_pot_column<float>, g, dim3(256), 0, (hipStream_t)stream, sf, wk, sf0,
-                       (float*)ws, (const float*)pot, nf1, nf2, epart, conf, hh);
+                       (float*)ws, (const float*)pot, nf1, nf2, epart, conf, hh,
+                       padded);
   return (int)hipGetLastError();
 }
 

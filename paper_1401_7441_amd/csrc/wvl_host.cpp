@@ -23,12 +23,14 @@ using namespace wvl;
 enum KernelKind {
   KK_GATHER, KK_SCATTER, KK_UNPACK, KK_UP_X, KK_UP_Y, KK_POT_COLUMN, KK_KIN_XCOL, KK_KIN_YCOL, KK_KIN_ZCOL,
   KK_BACK_Y, KK_BACK_X, KK_FINALIZE, KK_PATTERN, KK_SPARSE_S, KK_SPARSE_H,
-  KK_UPDATE, KK_UP_Z, KK_DENS_TILE, KK_FOE_MM, KK_FOE, KK_GRADIENT, KK_COUNT
+  KK_UPDATE, KK_UP_Z, KK_DENS_TILE, KK_FOE_MM, KK_FOE, KK_GRADIENT,
+  KK_UP_PLANE, KK_COL_TILE, KK_KIN_SLAB, KK_BACK_PLANE, KK_COUNT
 };
 static const char* kKernelNames[KK_COUNT] = {
     "uncompress", "compress", "unpack", "up_x", "up_y", "pot_column", "kin_xcol", "kin_ycol", "kin_zcol",
     "back_y", "back_x", "finalize", "pattern", "sparse_s", "sparse_h", "update",
-    "up_z", "dens_tile", "foe_mm", "foe", "gradient"};
+    "up_z", "dens_tile", "foe_mm", "foe", "gradient",
+    "up_plane", "col_tile", "kin_slab", "back_plane"};
 
 // LDS a block of the fused plane kernels may use (gfx950: 160 KiB per block),
 // less what their fixed-order reductions declare statically
@@ -714,15 +716,34 @@ void wvl_plan_destroy(wvl_plan* plan) {
 // bin counts the autotuner tries (the plan's workspace covers all of them)
 static const int kTuneBins[] = {1, 2, 3, 4, 6, 8};
 
-static int64_t sf_elems(const SfDev& S) {
+// workspace elements of one function's arrays; slim: the plane kernels' only
+static int64_t sf_elems(const SfDev& S, bool slim) {
   const int64_t n0 = S.n[0], n1 = S.n[1], n2 = S.n[2], e = S.ext;
-  const int64_t r0 = 2 * n0 + 29, r1 = 2 * n1 + 29;
+  const int64_t r0 = 2 * n0 + 29, r1 = 2 * n1 + 29, p0 = pad16((int)r0);
   const int64_t o0 = n0 + 2 * e, o1 = n1 + 2 * e, o2 = n2 + 2 * e;
-  return 2 * align64(8 * n0 * n1 * n2) + align64(2 * n2 * r0 * r1) + align64(2 * o2 * r0 * r1) +
-         align64(4 * o2 * r0 * qrow_stride((int)o1)) + align64(8 * n2 * o0 * n1) +
-         align64(8 * n2 * qrow_stride((int)o1) * n0) +
-         align64(8 * o2 * n0 * n1) + align64(4 * n2 * n1 * r0);
+  const int64_t pl = align64(2 * n2 * p0 * r1) + align64(2 * o2 * p0 * r1) + align64(8 * o2 * n0 * n1);
+  if (slim) return pl;
+  return pl + 2 * align64(8 * n0 * n1 * n2) + align64(4 * o2 * r0 * qrow_stride((int)o1)) +
+         align64(8 * n2 * o0 * n1) + align64(8 * n2 * qrow_stride((int)o1) * n0) +
+         align64(4 * n2 * n1 * r0);
 }
+
+// types in which a function takes the plane kernels (bit 0 FP32, bit 1 FP64)
+static int plane_bits(const SfDev& S) {
+  return (plane_fits(S.n[0], S.n[1], S.n[2], S.ext, 4) ? 1 : 0) |
+         (plane_fits(S.n[0], S.n[1], S.n[2], S.ext, 8) ? 2 : 0);
+}
+
+// blocks of k_back_plane per CU, FP32 and FP64
+static int back_blocks(const SfDev& S) {
+  const int64_t cu = 160 * 1024, fix = 1792;   // static LDS
+  const int64_t a = cu / (4 * plane_lds_back(S.n[0], S.n[1], S.ext) + fix);
+  const int64_t b = cu / (8 * plane_lds_back(S.n[0], S.n[1], S.ext) + fix);
+  return (int)(64 * std::min<int64_t>(4, a) + std::min<int64_t>(4, b));
+}
+// fewest functions of a launch split off for its LDS size (their blocks fill
+// the chip several times: 100 or more per function)
+constexpr int kLdsSplit = 64;
 
 // Builds the layout for `nbins` bins; false (with a message) when a box
 // does not fit the kernels' LDS stages.
@@ -745,8 +766,20 @@ static bool make_layout(const wvl_plan* P, int nbins, bool zmfma, Layout* L, std
       ch.sf0 = k;
       int64_t elems = 0;
       int j = k;
+      // the matrix-core z part belongs to the column kernels; a chunk's
+      // functions take the same kernels
+      const int bits = zmfma ? 0 : plane_bits(P->h_sf[P->order[k]]);
+      const bool slim = bits == 3;
+      ch.plane[0] = bits & 1;
+      ch.plane[1] = bits & 2;
       for (; j < b1; ++j) {
-        const int64_t need = sf_elems(P->h_sf[P->order[j]]);
+        if (!zmfma && plane_bits(P->h_sf[P->order[j]]) != bits) break;
+        // one launch has one LDS size: smaller boxes, of which more blocks fit
+        // a CU, get a launch of their own where there are enough of either
+        if (j - k >= kLdsSplit && b1 - j >= kLdsSplit && bits &&
+            back_blocks(P->h_sf[P->order[j]]) != back_blocks(P->h_sf[P->order[k]]))
+          break;
+        const int64_t need = sf_elems(P->h_sf[P->order[j]], slim);
         // partial slots are at most a few per 256 output points
         const int64_t bytes = align_bytes((elems + need) * 8) + (int64_t)(j - k + 1) * 4096 * 8;
         if (j > k && P->max_ws > 0 && (size_t)bytes > P->max_ws) break;
@@ -763,16 +796,39 @@ static bool make_layout(const wvl_plan* P, int nbins, bool zmfma, Layout* L, std
         const int64_t r0 = 2 * n0 + 29, r1 = 2 * n1 + 29;
         const int64_t o0 = n0 + 2 * e, o1 = n1 + 2 * e, o2 = n2 + 2 * e;
         SfWork& W = L->wk[q];
+        const int64_t p0 = pad16((int)r0);
         W.id = id;
-        W.c8 = off;  off += align64(8 * n0 * n1 * n2);
-        W.c8x = off; off += align64(8 * n0 * n1 * n2);
-        W.g1 = off;  off += align64(2 * n2 * r0 * r1);
-        W.g2 = off;  off += align64(2 * o2 * r0 * r1);
-        W.q = off;   off += align64(4 * o2 * r0 * qrow_stride((int)o1));
-        W.ox = off;  off += align64(8 * n2 * o0 * n1);
-        W.oy = off;  off += align64(8 * n2 * qrow_stride((int)o1) * n0);
+        W.g1 = off;  off += align64(2 * n2 * p0 * r1);
+        W.g2 = off;  off += align64(2 * o2 * p0 * r1);
         W.oz = off;  off += align64(8 * o2 * n0 * n1);
-        W.gx = off;  off += align64(4 * n2 * n1 * r0);
+        if (!slim) {
+          W.c8 = off;  off += align64(8 * n0 * n1 * n2);
+          W.c8x = off; off += align64(8 * n0 * n1 * n2);
+          W.q = off;   off += align64(4 * o2 * r0 * qrow_stride((int)o1));
+          W.ox = off;  off += align64(8 * n2 * o0 * n1);
+          W.oy = off;  off += align64(8 * n2 * qrow_stride((int)o1) * n0);
+          W.gx = off;  off += align64(4 * n2 * n1 * r0);
+        }
+        // plane kernels: partials counted on the function's own box
+        const int ns = plane_strips((int)o1);
+        W.nepart_pl[0] = (r0 * r1 + 255) / 256;
+        W.nepart_pl[1] = (r1 * (p0 / 16) + 3) / 4;
+        W.nkpart_pl = 2 * n2 * ns + 2 * n1;
+        ch.grid_up = (int32_t)std::max<int64_t>(ch.grid_up, 2 * n2);
+        ch.grid_ct = (int32_t)std::max<int64_t>(ch.grid_ct, W.nepart_pl[1]);
+        ch.grid_ks = (int32_t)std::max<int64_t>(ch.grid_ks, 2 * n1);
+        ch.grid_bp = (int32_t)std::max<int64_t>(ch.grid_bp, 8 * ((o2 + 7) / 8) * 2 * ns);
+        ch.nblk_kin = (int32_t)std::max<int64_t>(ch.nblk_kin, W.nkpart_pl);
+        for (int d = 0; d < 2; ++d) {
+          const int sz = d ? 8 : 4;
+          if (!ch.plane[d]) continue;
+          // FP64: both a2 at once while two blocks fit a CU; one value per
+          // chunk (it does not change results)
+          if (q == k) ch.up_both[d] = 1;
+          if (sz * plane_lds_up(n0, n1, true, sz) > 80 * 1024) ch.up_both[d] = 0;
+          ch.lds_ks[d] = std::max<int64_t>(ch.lds_ks[d], sz * plane_lds_kin(n0, n2));
+          ch.lds_bp[d] = std::max<int64_t>(ch.lds_bp[d], sz * plane_lds_back(n0, n1, e));
+        }
         ch.maxbox_in = std::max(ch.maxbox_in, 8 * n0 * n1 * n2);
         ch.grid_u[0] = (int32_t)std::max<int64_t>(ch.grid_u[0], n2);   // planes; scaled below
         ch.grid_ux = (int32_t)std::max<int64_t>(ch.grid_ux, (4 * n2 * n1 + 63) / 64);
@@ -789,7 +845,7 @@ static bool make_layout(const wvl_plan* P, int nbins, bool zmfma, Layout* L, std
       // k_unpack: as many components per block as the LDS stage fits
       const int64_t nz = ch.grid_u[0];
       for (int d = 0; d < 2; ++d) {
-        if (ch.lds_u[d] > kLdsBudget) {
+        if (ch.lds_u[d] > kLdsBudget && !ch.plane[d]) {
           *err = "a box's x-y plane (" + std::to_string(ch.lds_u[d]) +
                  " bytes) does not fit the unpack stage's LDS";
           return false;
@@ -800,8 +856,15 @@ static bool make_layout(const wvl_plan* P, int nbins, bool zmfma, Layout* L, std
         ch.grid_u[d] = (int32_t)((8 / g) * nz);
         ch.lds_u[d] *= g;
       }
-      ch.nblk_pot = ch.grid_b;
-      ch.nblk_kin = ch.grid_kx + ch.grid_ky + ch.grid_kz;
+      for (int d = 0; d < 2; ++d)
+        for (int q = k; ch.plane[d] && q < j; ++q) {
+          const SfDev& S = P->h_sf[P->order[q]];
+          ch.lds_up[d] = std::max<int64_t>(ch.lds_up[d], (d ? 8 : 4) * plane_lds_up(S.n[0], S.n[1],
+                                                                                  ch.up_both[d],
+                                                                                  d ? 8 : 4));
+        }
+      ch.nblk_pot = std::max(ch.grid_b, ch.grid_ct);
+      ch.nblk_kin = std::max(ch.nblk_kin, ch.grid_kx + ch.grid_ky + ch.grid_kz);
       int64_t poff = L->disjoint ? pbase : 0;
       for (int q = k; q < j; ++q) {
         const SfDev& S = P->h_sf[P->order[q]];
@@ -945,11 +1008,14 @@ wvl_status wvl_plan_create(wvl_ctx* ctx, int32_t nsf, const wvl_locreg* lr, cons
     bbox(segs, L.seg_c, L.nseg_c, S.bb_in);
     bbox(segs, L.oseg_c, L.noseg_c, S.bb_out);
   }
-  // processing order: largest boxes first, ties by index
+  // processing order: the functions of the column kernels first, then the
+  // largest boxes, ties by index
   P->order.resize(nsf);
   for (int k = 0; k < nsf; ++k) P->order[k] = k;
   std::stable_sort(P->order.begin(), P->order.end(), [&](int a, int b) {
     const SfDev &A = P->h_sf[a], &B = P->h_sf[b];
+    const int pa = plane_bits(A), pb = plane_bits(B);
+    if (pa != pb) return pa < pb;
     return (int64_t)A.n[0] * A.n[1] * A.n[2] > (int64_t)B.n[0] * B.n[1] * B.n[2];
   });
   P->max_ws = max_workspace_bytes;
@@ -1084,6 +1150,34 @@ static wvl_status apply_chunk(wvl_plan* P, size_t c, int f64, uint32_t terms, co
   const ChunkDev& ch = P->lay.chunks[c];
   const SfWork* wk = P->d_wk + ch.sf0;
   double* parts = (double*)((char*)workspace + align_bytes(P->lay.elems_span * sz));
+  if (ch.plane[d]) {
+    if (pot_on) {
+      WVL_LAUNCH(ctx, KK_UP_PLANE,
+                 launch_up_plane(f64, st, P->d_sf, P->d_seg, P->d_rt, P->d_rr, psi_c, wk, ch.nsf,
+                                 ch.grid_up, ch.up_both[d], (size_t)ch.lds_up[d], workspace));
+      if (f64)
+        WVL_LAUNCH(ctx, KK_COL_TILE,
+                   launch_col_tile(st, P->d_sf, wk, ch.nsf, ch.grid_ct, workspace, pot, nf1, nf2,
+                                   parts, conf, 0.5 * ctx->grid.h));
+      else
+        WVL_LAUNCH(ctx, KK_POT_COLUMN,
+                   launch_pot_column(f64, st, P->d_sf, wk, ch.sf0, ch.nsf, ch.grid_b, workspace,
+                                     pot, nf1, nf2, parts, conf, 0.5 * ctx->grid.h, 1));
+    }
+    if (kin_on)
+      WVL_LAUNCH(ctx, KK_KIN_SLAB,
+                 launch_kin_slab(f64, st, P->d_sf, P->d_seg, P->d_rt, P->d_rr, psi_c, wk, ch.nsf,
+                                 ch.grid_ks, (size_t)ch.lds_ks[d], workspace, fac, parts));
+    WVL_LAUNCH(ctx, KK_BACK_PLANE,
+               launch_back_plane(f64, st, P->d_sf, P->d_seg, P->d_rt, P->d_rr, psi_c, wk, ch.nsf,
+                                 ch.grid_bp, (size_t)ch.lds_bp[d], workspace, hpsi_c, pot_on,
+                                 kin_on, accumulate, fac, parts));
+    if ((pot_on && e_pot) || (kin_on && e_kin))
+      WVL_LAUNCH(ctx, KK_FINALIZE, launch_plane_energies(f64, st, wk, ch.nsf, parts,
+                                                         kin_on ? e_kin : nullptr,
+                                                         pot_on ? e_pot : nullptr));
+    return WVL_OK;
+  }
   WVL_LAUNCH(ctx, KK_UNPACK,
              launch_unpack(f64, st, P->d_sf, P->d_seg, P->d_rt, P->d_rr, psi_c, wk, ch.nsf,
                            ch.grid_u[d], ch.group_u[d], (size_t)ch.lds_u[d], workspace));
@@ -1092,7 +1186,7 @@ static wvl_status apply_chunk(wvl_plan* P, size_t c, int f64, uint32_t terms, co
     WVL_LAUNCH(ctx, KK_UP_Y, launch_up(f64, st, 1, wk, P->d_sf, ch.nsf, ch.grid_uy, workspace));
     WVL_LAUNCH(ctx, KK_POT_COLUMN,
                launch_pot_column(f64, st, P->d_sf, wk, ch.sf0, ch.nsf, ch.grid_b, workspace, pot,
-                                 nf1, nf2, parts, conf, 0.5 * ctx->grid.h));
+                                 nf1, nf2, parts, conf, 0.5 * ctx->grid.h, 0));
     if (e_pot)
       WVL_LAUNCH(ctx, KK_FINALIZE,
                  launch_finalize(st, wk, ch.sf0, ch.nsf, parts, 0, ch.grid_b, e_pot));
@@ -1388,13 +1482,25 @@ wvl_status wvl_synthesize(wvl_plan* P, wvl_dtype dt, const void* psi_c, void* fi
     const ChunkDev& ch = P->lay.chunks[c];
     const SfWork* wk = P->d_wk + ch.sf0;
     hipStream_t st = ctx->stream;
+    if (ch.plane[f64]) {
+      WVL_LAUNCH(ctx, KK_UP_PLANE,
+                 launch_up_plane(f64, st, P->d_sf, P->d_seg, P->d_rt, P->d_rr, psi_c, wk, ch.nsf,
+                                 ch.grid_up, ch.up_both[f64], (size_t)ch.lds_up[f64], workspace));
+      if (f64)
+        WVL_LAUNCH(ctx, KK_UP_Z, launch_syn_tile(st, P->d_sf, wk, ch.nsf, ch.grid_ct, workspace,
+                                                 P->d_foff, fine));
+      else
+        WVL_LAUNCH(ctx, KK_UP_Z, launch_up_z(f64, st, wk, P->d_sf, ch.nsf, ch.grid_b, workspace,
+                                             P->d_foff, fine, 1));
+      continue;
+    }
     WVL_LAUNCH(ctx, KK_UNPACK,
                launch_unpack(f64, st, P->d_sf, P->d_seg, P->d_rt, P->d_rr, psi_c, wk, ch.nsf,
                              ch.grid_u[f64], ch.group_u[f64], (size_t)ch.lds_u[f64], workspace));
     WVL_LAUNCH(ctx, KK_UP_X, launch_up(f64, st, 0, wk, P->d_sf, ch.nsf, ch.grid_ux, workspace));
     WVL_LAUNCH(ctx, KK_UP_Y, launch_up(f64, st, 1, wk, P->d_sf, ch.nsf, ch.grid_uy, workspace));
     WVL_LAUNCH(ctx, KK_UP_Z, launch_up_z(f64, st, wk, P->d_sf, ch.nsf, ch.grid_b, workspace,
-                                         P->d_foff, fine));
+                                         P->d_foff, fine, 0));
   }
   return WVL_OK;
 }
@@ -1916,6 +2022,7 @@ static wvl_status capture_step(wvl_plan* P, wvl_dtype dt, uint32_t terms, const 
   // constant filter tables) must not happen inside the capture
   int pe = preload_kernels();
   if (pe == 0) pe = preload_fused_kernels();
+  if (pe == 0) pe = preload_plane_kernels();
   if (pe != 0)
     return hip_fail(ctx, "graph capture", "kernel preload (hipFuncGetAttributes)",
                     (hipError_t)pe);

@@ -56,17 +56,21 @@ constexpr int kBackOutRows = 16;
 //   c8x  dense input box, y fastest      [8][N2][N0][N1]
 //   g1   after the x, y up passes        [2][N2][R1][R0]
 //   g2   after the z column pass         [2][O2][R1][R0]
+//        (plane kernels: rows pad16(R0) apart)
 //   q    after the y down pass           [4][O2][R0][O1]   (channel a2 + 2 a3)
 //   ox   x part of the kinetic term      [8][N2][O0][N1]
 //   oy   y part of the kinetic term      [8][N2][N0][O1]
-//   oz   z part of the kinetic term      [8][O2][N0][N1]
+//   oz   z part of the kinetic term      [8][O2][N0][N1] (plane kernels:
+//        [8][O2][N1][N0])
 //   gx   after the x up pass             [4][N2][N1][R0]   (channel a2 + 2 a3)
+// A function of the plane kernels (in both types) has g1, g2 and oz only.
 struct SfWork {
   int64_t id;         // the function's index in the plan (SfDev array, outputs)
   int64_t c8, c8x, g1, g2, q, ox, oy, oz, gx;
   int64_t epart;      // offset (in doubles) of its e_pot partials
   int64_t kpart;      // offset (in doubles) of its e_kin partials
   int64_t nkpart;     // number of e_kin partials: its own k_kin_col blocks
+  int64_t nepart_pl[2], nkpart_pl;   // partials of the plane kernels (e_pot per type, e_kin)
 };
 
 // e_kin partial slots of one function: the blocks of k_kin_col along x, then
@@ -83,6 +87,41 @@ __host__ __device__ inline int kin_blocks(int axis, int n0, int n1, int n2, bool
          : zmfma ? (n0 * n1 + 15) / 16 : (4 * n0 * n1 + 255) / 256;
 }
 
+// Plane kernels (wvl_planes.hip).  LDS strides: see k_up_plane.
+__host__ __device__ constexpr int pad16(int n) { return (n + 15) & ~15; }
+__host__ __device__ constexpr int plane_ldx(int n0) { return ((n0 + 3) & ~7) + 4; }   // 4 (mod 8)
+__host__ __device__ constexpr int plane_ych(int n0, int n1) {                          // 16 (mod 32)
+  return ((n1 * (pad16(2 * n0 + 29) + 4) + 15) & ~31) + 16;
+}
+constexpr int kPlaneStrip = 24;      // output rows y' per k_back_plane block
+constexpr int kPlaneThreads = 256;   // k_kin_slab, k_back_plane
+__host__ __device__ constexpr int plane_strips(int o1) { return (o1 + kPlaneStrip - 1) / kPlaneStrip; }
+// dynamic LDS in elements of the compute type
+constexpr int64_t plane_lds_up(int64_t n0, int64_t n1, bool both, int sz) {
+  return sz == 4 ? 4 + 2 * n1 * (2 * n0 + 1) + n1 * (4 * n0 + 59)
+                 : (both ? 4 : 2) * n1 * plane_ldx((int)n0) + 2 * (int64_t)plane_ych((int)n0, (int)n1);
+}
+__host__ __device__ constexpr int plane_kin_elems(int n0, int rows) {   // 4-aligned
+  return (4 + rows * (4 * n0 + 1) + 3) & ~3;
+}
+constexpr int64_t plane_lds_kin(int64_t n0, int64_t n2) { return plane_kin_elems((int)n0, (int)n2); }
+constexpr int64_t plane_lds_back(int64_t n0, int64_t n1, int64_t e) {
+  const int64_t q = 2 * kPlaneStrip * (pad16((int)(2 * n0 + 29)) + 4),
+                x = plane_kin_elems((int)n0, (int)n1);
+  return (q > x ? q : x) + 4 * kPlaneStrip * ((n0 + 2 * e) | 1);
+}
+// Whether a function of this box takes the plane kernels in an element type
+// of sz bytes: its planes fit the LDS of a CU (160 KiB, less the static
+// part).  In FP64 boxes of up to about 50 points per axis do, in FP32 of
+// about 70.  The rule looks at the function's own box only, so that results
+// do not depend on the other functions of a plan.
+constexpr int64_t kPlaneLds = 160 * 1024 - 4096;
+constexpr int kPlaneMaxN = 96;    // bits of k_back_plane's row masks
+constexpr bool plane_fits(int64_t n0, int64_t n1, int64_t n2, int64_t e, int sz) {
+  return n0 <= kPlaneMaxN && n1 <= kPlaneMaxN && n2 <= kPlaneMaxN && sz * plane_lds_up(n0, n1, false, sz) <= kPlaneLds &&
+         sz * plane_lds_kin(n0, n2) <= kPlaneLds && sz * plane_lds_back(n0, n1, e) <= kPlaneLds;
+}
+
 // per-chunk launch geometry of the fused kernels, for dtype d (0 f32, 1 f64)
 struct ChunkDev {
   int32_t sf0, nsf;                // positions [sf0, sf0 + nsf) of the processing order
@@ -95,6 +134,12 @@ struct ChunkDev {
   int32_t grid_by;                 // k_back_y
   int32_t grid_bx;                 // k_back_out
   int32_t nblk_pot, nblk_kin;      // partial slots per function
+  // plane kernels, per type (0 f32, 1 f64): whether the chunk's functions take
+  // them, dynamic LDS in bytes, both a2 at once in k_up_plane
+  bool plane[2];
+  int32_t up_both[2];
+  int64_t lds_up[2], lds_ks[2], lds_bp[2];
+  int32_t grid_up, grid_ct, grid_ks, grid_bp;
 };
 
 // the apply of wvl_apply_local_ham on a workspace of `cap` bytes that the
@@ -110,6 +155,7 @@ void* plan_stream(const wvl_plan* plan);
 // load every kernel's code object before a stream capture (hipError_t as int)
 int preload_kernels();         // wvl_kernels.hip
 int preload_fused_kernels();   // wvl_fused.hip
+int preload_plane_kernels();   // wvl_planes.hip
 
 // launchers implemented in wvl_kernels.hip; all return hipError_t as int
 int launch_gather(int f64, void* stream, const SfDev* sf, const wvl_seg* seg, const int32_t* rt,
@@ -123,7 +169,7 @@ int launch_unpack(int f64, void* stream, const SfDev* sf, const wvl_seg* seg, co
 int launch_up(int f64, void* stream, int axis, const SfWork* wk, const SfDev* sf, int nsf,
               int gridx, void* ws);
 int launch_up_z(int f64, void* stream, const SfWork* wk, const SfDev* sf, int nsf, int gridx,
-                const void* ws, const int64_t* fine_off, void* fine);
+                const void* ws, const int64_t* fine_off, void* fine, int padded);
 // density: tiles of 16 x 4 x 1 fine-grid points (one 64-lane workgroup each)
 // with the functions whose fine box meets them (at most kDensMaxCover)
 // with the functions whose fine box meets them (at most kDensMaxCover),
@@ -140,7 +186,7 @@ int launch_dens_tile(int f64, void* stream, const SfDev* sf, const int64_t* foff
                      const int32_t* tord, int64_t n_one, const int* gf, void* rho);
 int launch_pot_column(int f64, void* stream, const SfDev* sf, const SfWork* wk, int sf0, int nsf,
                       int gridx, void* ws, const void* pot, int nf1, int nf2, double* epart,
-                      const double* conf, double hh);
+                      const double* conf, double hh, int padded);
 // the z part of the kinetic term on the FP64 matrix cores (banded Toeplitz)
 int launch_kin_zmfma(int f64, void* stream, const SfDev* sf, const SfWork* wk, int sf0, int nsf,
                      int gridx, void* ws, double fac, double* kpart);
@@ -151,6 +197,25 @@ int launch_back_y(int f64, void* stream, const SfDev* sf, const SfWork* wk, int 
 int launch_back_out(int f64, void* stream, const SfDev* sf, const wvl_seg* seg, const int32_t* rt,
                     const RowRun* rr, const SfWork* wk, int sf0, int nsf, int gridx,
                     const void* ws, void* out, int pot_on, int kin_on, int accumulate);
+// plane kernels (wvl_planes.hip)
+int launch_up_plane(int f64, void* stream, const SfDev* sf, const wvl_seg* seg, const int32_t* rt,
+                    const RowRun* rr, const void* psi, const SfWork* wk, int nsf, int gridx,
+                    int both, size_t lds, void* ws);
+// FP64: z passes on the matrix cores (FP32 takes k_pot_column, k_up_z)
+int launch_col_tile(void* stream, const SfDev* sf, const SfWork* wk, int nsf, int gridx, void* ws,
+                    const void* pot, int nf1, int nf2, double* epart, const double* conf,
+                    double hh);
+int launch_syn_tile(void* stream, const SfDev* sf, const SfWork* wk, int nsf, int gridx, void* ws,
+                    const int64_t* fine_off, void* fine);
+int launch_kin_slab(int f64, void* stream, const SfDev* sf, const wvl_seg* seg, const int32_t* rt,
+                    const RowRun* rr, const void* psi, const SfWork* wk, int nsf, int gridx,
+                    size_t lds, void* ws, double fac, double* kpart);
+int launch_back_plane(int f64, void* stream, const SfDev* sf, const wvl_seg* seg,
+                      const int32_t* rt, const RowRun* rr, const void* psi, const SfWork* wk,
+                      int nsf, int gridx, size_t lds, const void* ws, void* out, int pot_on,
+                      int kin_on, int accumulate, double fac, double* kpart);
+int launch_plane_energies(int f64, void* stream, const SfWork* wk, int nsf, const double* parts,
+                          double* e_kin, double* e_pot);
 int launch_finalize(void* stream, const SfWork* wk, int sf0, int nsf, const double* parts,
                     int which, int nblk, double* out);
 int launch_pattern(void* stream, const SfDev* sf, const wvl_seg* seg, const int32_t* rt, int nsf,

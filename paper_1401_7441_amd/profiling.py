@@ -47,6 +47,7 @@ def kind_of(name: str):
     name, or None for kernels that are not the library's."""
     if "k_copy" in name:
         return "copy"
+    name = name.replace("(anonymous namespace)::", "")
     m = re.search(r"wvl::k_(\w+)(?:<([^>]*)>)?", name)
     if not m:
         return None
@@ -57,6 +58,10 @@ def kind_of(name: str):
         return "uncompress"
     if base == "scatter":
         return "compress"
+    if base == "up_plane_valu":  # the FP32 form
+        return "up_plane"
+    if base == "plane_energies":
+        return "finalize"
     if base == "back_out":       # the x analysis pass, writing the compressed output
         return "back_x"
     return base          # sparse_values is split into S and H by dispatch order
