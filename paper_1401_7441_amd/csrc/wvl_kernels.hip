@@ -1031,44 +1031,74 @@ __global__ __launch_bounds__(TPB) void k_cg_init(const SfDev* __restrict__ sfs,
 // gradient: g_a = L^a [ sum_d A_ad H|phi_d> - sum_d M_ad |phi_d> ] over row a
 // of the overlap pattern (Eq. (gradient), Sec. IV.A, localized as Sec. III.A)
 // ---------------------------------------------------------------------------
-// Block = function a (four waves), the neighbours d of row a staged in LDS
-// (their box rows, row-table bases and coefficient offsets, A_ad and M_ad),
-// kGradNb at a time.  Wave w takes the rows w, w + 4, ... of a's input box;
-// for each segment of a row (the scaling coefficients of the coarse pattern,
-// then the seven wavelets of each point of the fine pattern) lane j owns the
-// elements j, j + 64, ... and sums, over the neighbours in CSR order, the
-// values of H|phi_d> and |phi_d> at its point (0 where d's pattern lacks
-// it), in double; each element of g_a is written once, by its owner.
+// Block = part of function a's rows (four waves), the neighbours d of row a
+// staged in LDS, kGradNb at a time.  A wave takes a row of a's input box; for
+// each segment of it (the scaling coefficients of the coarse pattern, then the
+// seven wavelets of each point of the fine pattern) it works in two phases per
+// 64 neighbours.  Phase 1: lane t looks up neighbour t's runs in this row (one
+// record each for H|phi_d> and |phi_d>; rows of several runs walk their
+// segments) and the runs that meet the segment go to a list in LDS, in CSR
+// order.  Phase 2: lane j owns the elements j, j + 64, ... and adds the listed
+// runs' values at its points, in double and in list order, several runs' loads
+// under way at a time.  Each element of g_a is written once, by its owner.
+// Bound by the latency of phase 2's loads and by its vector instructions.
+// 500 functions of radius 5-7 bohr at 0.037 per bohr^3, FP32: 69.0 ms with one
+// lookup and one value at a time, each waited for; 6.1 ms with the lists and 8
+// or 4 runs under way; 4.6 ms with neighbour records of 80 instead of 136 bytes
+// (five blocks per CU by LDS), 16 runs and multiply-adds under the lane mask.
 constexpr int kGradNb = 256;
+constexpr int kGradCap = 128;     // list entries per wave: 64 neighbours, two runs each
+constexpr int kGradParts = 8;     // blocks per function (and rows 4 kGradParts apart per wave)
 
+// a neighbour: its input box rows (origin, rows per plane, planes; the output
+// box is ext wider on each side), the records of its input rows (those of the
+// other patterns follow), its first coefficients, A_ad and M_ad
 struct GradNb {
-  int32_t in_y0, in_z0, in_by, in_nz;       // input box rows: origin, rows per plane, planes
-  int32_t out_y0, out_z0, out_by, out_nz;   // output box rows
-  int64_t rr_in[2], rr_out[2];              // RowRun bases (coarse, fine)
-  int64_t rt_in[2], rt_out[2];              // row-table bases (coarse, fine)
-  int64_t cin, cout, n_c, on_c;
+  int32_t y0, z0, by, nz, e, id;
+  int32_t n_c, on_c;
+  int64_t rr, cin, cout;
   double a, m;
 };
+// a run of |phi_d> or H|phi_d> in the row: points x0 .. x1, the value of
+// component comp at p[per x + comp], its coefficient
+template <typename T> struct GradRun {
+  const T* p;
+  int32_t x0, x1;
+  double c;
+};
 
-// index of global point gx in row r of a pattern (RowRun base rrb, row-table
-// base rtb), or -1
-__device__ __forceinline__ int64_t grad_find(const RowRun* __restrict__ rr,
-                                             const int32_t* __restrict__ rt,
-                                             const wvl_seg* __restrict__ seg, int64_t rrb,
-                                             int64_t rtb, int64_t r, int gx) {
-  const RowRun w = rr[rrb + r];
-  if (w.len == 0) return -1;
-  if (w.len != kMultiRun)
-    return (gx >= (int)w.x0 && gx < (int)w.x0 + (int)w.len) ? (int64_t)w.off + gx - w.x0 : -1;
-  for (int q = rt[rtb + r], q1 = rt[rtb + r + 1]; q < q1; ++q) {
-    const wvl_seg g = seg[q];
-    if (gx >= g.i1s && gx <= g.i1e) return g.off + (gx - g.i1s);
+// adds the runs list[0 .. n) to the lane's NS elements (element k at gx[k],
+// offset lc[k] = per gx + comp)
+template <typename T, int NS>
+__device__ __forceinline__ void grad_add(const GradRun<T>* list, int n, const int (&gx)[4],
+                                         const int (&lc)[4], double (&acc)[4]) {
+  constexpr int U = sizeof(T) == 4 && NS == 1 ? 16 : 8 / NS;
+  for (int i0 = 0; i0 < n; i0 += U) {
+    T v[U][NS];
+    double c[U];
+    bool in[U][NS];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const GradRun<T> e = list[min(i0 + u, n - 1)];
+      const int x1 = i0 + u < n ? e.x1 - e.x0 : -1;   // the last run repeated: no points
+      c[u] = e.c;
+#pragma unroll
+      for (int k = 0; k < NS; ++k) {
+        in[u][k] = (uint32_t)(gx[k] - e.x0) <= (uint32_t)x1 && x1 >= 0;
+        v[u][k] = T(0);
+        if (in[u][k]) v[u][k] = e.p[lc[k]];
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int k = 0; k < NS; ++k)
+        if (in[u][k]) acc[k] += c[u] * (double)v[u][k];
   }
-  return -1;
 }
 
 template <typename T>
-__global__ __launch_bounds__(256) void k_grad_rows(const SfDev* __restrict__ sfs,
+__global__ __launch_bounds__(256, 4) void k_grad_rows(const SfDev* __restrict__ sfs,
                                                    const wvl_seg* __restrict__ seg,
                                                    const int32_t* __restrict__ rt,
                                                    const RowRun* __restrict__ rr,
@@ -1080,12 +1110,16 @@ __global__ __launch_bounds__(256) void k_grad_rows(const SfDev* __restrict__ sfs
                                                    const T* __restrict__ hpsi, int sf0,
                                                    T* __restrict__ g) {
   __shared__ GradNb nb[kGradNb];
-  const int a = sf0 + blockIdx.x;
+  __shared__ GradRun<T> lists[4][kGradCap];
+  const int a = sf0 + blockIdx.y;
   const SfDev& A = sfs[a];
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  GradRun<T>* const list = lists[wv];
   const int N1 = A.n[1], N2 = A.n[2];
-  const int64_t nrows = (int64_t)N1 * N2;
+  const int nrows = N1 * N2;
   const int64_t q0 = rowptr[a], q1 = rowptr[a + 1];
+  const uint64_t below = (1ull << lane) - 1ull;
   // neighbours in batches of kGradNb: each element's sum runs over the
   // batches in order, the first batch writing g and the next ones adding to
   // it (an element has the same owner, lane and wave, in every batch; rows of
@@ -1099,56 +1133,132 @@ __global__ __launch_bounds__(256) void k_grad_rows(const SfDev* __restrict__ sfs
       const int d = col[b0 + t];
       const SfDev& D = sfs[d];
       GradNb x;
-      const int e = D.ext;
-      x.in_y0 = D.lo[1]; x.in_z0 = D.lo[2]; x.in_by = D.n[1]; x.in_nz = D.n[2];
-      x.out_y0 = D.lo[1] - e; x.out_z0 = D.lo[2] - e; x.out_by = D.n[1] + 2 * e;
-      x.out_nz = D.n[2] + 2 * e;
-      x.rr_in[0] = D.rr[0]; x.rr_in[1] = D.rr[1]; x.rr_out[0] = D.rr[2]; x.rr_out[1] = D.rr[3];
-      x.rt_in[0] = D.rt[0]; x.rt_in[1] = D.rt[1]; x.rt_out[0] = D.rt[2]; x.rt_out[1] = D.rt[3];
-      x.cin = D.cin; x.cout = D.cout; x.n_c = D.n_c; x.on_c = D.on_c;
+      x.y0 = D.lo[1]; x.z0 = D.lo[2]; x.by = D.n[1]; x.nz = D.n[2]; x.e = D.ext;
+      x.n_c = (int)D.n_c; x.on_c = (int)D.on_c;
+      x.rr = D.rr[0]; x.cin = D.cin; x.cout = D.cout;
       x.a = av[b0 + t];
       x.m = mv[b0 + t];
+      x.id = d;
       nb[t] = x;
     }
     __syncthreads();
-    for (int64_t r = wv; r < nrows; r += 4) {
-      const int y = A.lo[1] + (int)(r % N1), z = A.lo[2] + (int)(r / N1);
+    for (int r = blockIdx.x * 4 + wv; r < nrows; r += 4 * kGradParts) {
+      const int y = A.lo[1] + r % N1, z = A.lo[2] + r / N1;
 #pragma unroll
       for (int fine = 0; fine < 2; ++fine) {
         const int per = fine ? 7 : 1;
         const int64_t abase = A.cin + (fine ? A.n_c : 0);
         for (int q = rt[A.rt[fine] + r], qe = rt[A.rt[fine] + r + 1]; q < qe; ++q) {
-          const wvl_seg sa = seg[q];
-          const int len = per * (sa.i1e - sa.i1s + 1);
-          for (int j0 = 0; j0 < len; j0 += 64) {
-            const int j = j0 + lane;
-            const bool own = j < len;
-            const int pt = own ? j / per : 0;
-            const int comp = own ? j - per * pt : 0;
-            const int gx = sa.i1s + pt;
-            double acc = 0.0;
-            for (int t = 0; t < nn; ++t) {
-              const GradNb& x = nb[t];
-              // H phi_d on d's output pattern
-              const int ry = y - x.out_y0, rz = z - x.out_z0;
-              if (ry >= 0 && ry < x.out_by && rz >= 0 && rz < x.out_nz && x.a != 0.0) {
-                const int64_t k = own ? grad_find(rr, rt, seg, x.rr_out[fine], x.rt_out[fine],
-                                                  (int64_t)rz * x.out_by + ry, gx)
-                                      : -1;
-                if (k >= 0) acc += x.a * (double)hpsi[x.cout + (fine ? x.on_c : 0) + per * k + comp];
+          const int as = seg[q].i1s, ae = seg[q].i1e;
+          const int64_t aoff = seg[q].off;
+          const int len = per * (ae - as + 1);
+          for (int j0 = 0; j0 < len; j0 += 256) {
+            int gx[4], lc[4];
+            double acc[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+              const int j = j0 + 64 * k + lane;
+              const int pt = j / per, comp = j - per * pt;
+              gx[k] = j < len ? as + pt : INT32_MIN;   // meets no run
+              lc[k] = per * (as + pt) + comp;
+              acc[k] = 0.0;
+            }
+            const int ns = (min(len - j0, 256) + 63) >> 6;
+            for (int t0 = 0; t0 < nn; t0 += 64) {
+              // phase 1
+              GradRun<T> e[2];
+              bool has[2] = {false, false}, multi[2] = {false, false};
+              int64_t row[2] = {0, 0};
+              const int t = t0 + lane;
+              const GradNb& x = nb[min(t, nn - 1)];
+              if (t < nn) {
+                RowRun w[2];
+#pragma unroll
+                for (int s = 0; s < 2; ++s) {   // 0: H phi_d, output pattern; 1: phi_d, input
+                  const int o = s ? 0 : x.e, by = x.by + 2 * o, nz = x.nz + 2 * o;
+                  const int ry = y - x.y0 + o, rz = z - x.z0 + o;
+                  e[s].c = s ? -x.m : x.a;
+                  w[s] = RowRun{0, 0, 0};
+                  if (ry >= 0 && ry < by && rz >= 0 && rz < nz && e[s].c != 0.0) {
+                    row[s] = (int64_t)rz * by + ry;
+                    // the patterns' records follow each other: in-coarse,
+                    // in-fine, out-coarse, out-fine
+                    const int64_t nin = (int64_t)x.by * x.nz;
+                    w[s] = rr[x.rr + (s ? 0 : 2 * nin) + (fine ? (s ? nin : (int64_t)by * nz) : 0) +
+                              row[s]];
+                  }
+                }
+#pragma unroll
+                for (int s = 0; s < 2; ++s) {
+                  multi[s] = w[s].len == kMultiRun;
+                  e[s].x0 = w[s].x0;
+                  e[s].x1 = (int)w[s].x0 + (int)w[s].len - 1;
+                  has[s] = w[s].len != 0 && (multi[s] || (e[s].x0 <= ae && e[s].x1 >= as));
+                  e[s].p = (s ? psi + x.cin + (fine ? x.n_c : 0) : hpsi + x.cout + (fine ? x.on_c : 0)) +
+                           (int64_t)per * ((int64_t)w[s].off - (int)w[s].x0);
+                }
               }
-              // phi_d on d's input pattern
-              const int sy = y - x.in_y0, sz = z - x.in_z0;
-              if (sy >= 0 && sy < x.in_by && sz >= 0 && sz < x.in_nz && x.m != 0.0) {
-                const int64_t k = own ? grad_find(rr, rt, seg, x.rr_in[fine], x.rt_in[fine],
-                                                  (int64_t)sz * x.in_by + sy, gx)
-                                      : -1;
-                if (k >= 0) acc -= x.m * (double)psi[x.cin + (fine ? x.n_c : 0) + per * k + comp];
+              // the lane's runs in order: entry(run)
+              const bool any_multi = __any(multi[0] || multi[1]);
+              auto walk = [&](auto&& entry) {
+#pragma unroll
+                for (int s = 0; s < 2; ++s) {
+                  if (!has[s]) continue;
+                  if (!multi[s]) {
+                    entry(e[s]);
+                    continue;
+                  }
+                  const int64_t tb = sfs[x.id].rt[(s ? 0 : 2) + fine] + row[s];
+                  for (int p = rt[tb], pe = rt[tb + 1]; p < pe; ++p) {
+                    const wvl_seg h = seg[p];
+                    if (h.i1s > ae || h.i1e < as) continue;
+                    GradRun<T> m;
+                    m.x0 = h.i1s;
+                    m.x1 = h.i1e;
+                    m.c = e[s].c;
+                    m.p = (s ? psi + x.cin + (fine ? x.n_c : 0) : hpsi + x.cout + (fine ? x.on_c : 0)) +
+                          (int64_t)per * (h.off - h.i1s);
+                    entry(m);
+                  }
+                }
+              };
+              int pos, n;   // first position of the lane's runs, runs in all
+              if (!any_multi) {
+                const uint64_t m0 = __ballot(has[0]), m1 = __ballot(has[1]);
+                pos = __popcll(m0 & below) + __popcll(m1 & below);
+                n = __popcll(m0) + __popcll(m1);
+              } else {
+                int cnt = 0;
+                walk([&](const GradRun<T>&) { ++cnt; });
+                pos = cnt;   // inclusive sum over the lanes
+                for (int o = 1; o < 64; o <<= 1) {
+                  const int up = __shfl_up(pos, o, 64);
+                  if (lane >= o) pos += up;
+                }
+                n = __shfl(pos, 63, 64);
+                pos -= cnt;
+              }
+              // the list in rounds of kGradCap (one unless rows have several runs)
+              for (int base = 0; base < n; base += kGradCap) {
+                int at = pos - base;
+                walk([&](const GradRun<T>& m) {
+                  if (at >= 0 && at < kGradCap) list[at] = m;
+                  ++at;
+                });
+                wave_sync();
+                const int nr = min(kGradCap, n - base);
+                if (ns == 1) grad_add<T, 1>(list, nr, gx, lc, acc);
+                else if (ns == 2) grad_add<T, 2>(list, nr, gx, lc, acc);
+                else grad_add<T, 4>(list, nr, gx, lc, acc);
+                wave_sync();
               }
             }
-            if (own) {
-              T* o = g + abase + per * sa.off + j;
-              *o = bi == 0 ? (T)acc : (T)((double)*o + acc);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+              const int j = j0 + 64 * k + lane;
+              if (j >= len) continue;
+              T* o = g + abase + per * aoff + j;
+              *o = bi == 0 ? (T)acc[k] : (T)((double)*o + acc[k]);
             }
           }
         }
@@ -1436,11 +1546,11 @@ int launch_grad_rows(int f64, void* stream, const SfDev* sf, const wvl_seg* seg,
                      const void* hpsi, int sf0, int nsf, void* g) {
   if (nsf == 0) return 0;
   if (f64)
-    hipLaunchKernelGGL(k_grad_rows<double>, dim3((unsigned)nsf), dim3(256), 0, (hipStream_t)stream,
+    hipLaunchKernelGGL(k_grad_rows<double>, dim3(kGradParts, (unsigned)nsf), dim3(256), 0, (hipStream_t)stream,
                        sf, seg, rt, rr, rowptr, col, av, mv, (const double*)psi,
                        (const double*)hpsi, sf0, (double*)g);
   else
-    hipLaunchKernelGGL(k_grad_rows<float>, dim3((unsigned)nsf), dim3(256), 0, (hipStream_t)stream,
+    hipLaunchKernelGGL(k_grad_rows<float>, dim3(kGradParts, (unsigned)nsf), dim3(256), 0, (hipStream_t)stream,
                        sf, seg, rt, rr, rowptr, col, av, mv, (const float*)psi,
                        (const float*)hpsi, sf0, (float*)g);
   return (int)hipGetLastError();
