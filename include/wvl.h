@@ -272,8 +272,8 @@ wvl_status wvl_synthesize(wvl_plan* plan, wvl_dtype dt, const void* psi_c, void*
  * [2 n2 + 29][2 n1 + 29][2 n0 + 29] (z, y, x), every point written (0 where
  * no fine box reaches).  work: unused (may be NULL).  Sums run in double
  * in an order fixed by the plan and K (per point: the functions meeting its
- * tile in increasing index, each with its row of K in stored order), so the
- * result is reproducible bitwise.  The first call builds the plan's tile
+ * tile of 16 x 4 x 4 points in increasing index, K^ab and K^ba added first),
+ * so the result is reproducible bitwise.  The first call builds the plan's tile
  * lists (synchronizes once).  Errors: WVL_EINVAL for null buffers or
  * k_nnz < 0; WVL_EUNSUPPORTED when more than 1024 fine boxes meet one tile
  * of 16 x 4 x 1 fine-grid points, or the plan has 2^24 or more functions. */

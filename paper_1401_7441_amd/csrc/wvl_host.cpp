@@ -265,8 +265,6 @@ struct wvl_plan {
   int64_t max_fine = 0;               // largest fine box (elements)
   int64_t* d_cptr = nullptr;          // density: functions meeting each k_dens_tile tile
   int32_t* d_csf = nullptr;
-  int32_t* d_tord[2] = {nullptr, nullptr};   // tiles, one-chunk ones first (FP32, FP64)
-  int64_t dens_one[2] = {0, 0};              // how many of them have one chunk
   wvl_plan_info info{};
   PatternCache pat[2];
   std::unique_ptr<FoeCoef> foe_coef;  // Chebyshev node table of the last wvl_foe degree
@@ -702,8 +700,6 @@ void wvl_plan_destroy(wvl_plan* plan) {
   if (plan->d_foff) (void)hipFree(plan->d_foff);
   if (plan->d_cptr) (void)hipFree(plan->d_cptr);
   if (plan->d_csf) (void)hipFree(plan->d_csf);
-  for (int d = 0; d < 2; ++d)
-    if (plan->d_tord[d]) (void)hipFree(plan->d_tord[d]);
   if (plan->d_rt) (void)hipFree(plan->d_rt);
   if (plan->d_rr) (void)hipFree(plan->d_rr);
   if (plan->d_wk) (void)hipFree(plan->d_wk);
@@ -1543,34 +1539,28 @@ static wvl_status ensure_cover(wvl_plan* P) {
           }
     }
   }
+  // the limit is on the functions that meet one plane of a tile
   int64_t maxc = 0;
-  for (int64_t t = 0; t < ntile; ++t) maxc = std::max(maxc, cptr[t + 1] - cptr[t]);
+  for (int64_t t = 0; t < ntile; ++t) {
+    if (cptr[t + 1] - cptr[t] <= kDensMaxCover) continue;
+    const int z0 = (int)(t / ((int64_t)nt[0] * nt[1])) * kDensTile[2];
+    for (int z = z0; z < std::min(gf[2], z0 + kDensTile[2]); ++z) {
+      int64_t c = 0;
+      for (int64_t q = cptr[t]; q < cptr[t + 1]; ++q) {
+        const SfDev& S = P->h_sf[csf[q]];
+        c += z >= 2 * S.lo[2] && z <= 2 * S.lo[2] + 2 * S.n[2] + 28;
+      }
+      maxc = std::max(maxc, c);
+    }
+  }
   if (maxc > kDensMaxCover)
     return fail(ctx, WVL_EUNSUPPORTED,
                 "density: %lld fine boxes meet one tile (at most %d are supported)",
                 (long long)maxc, kDensMaxCover);
   if (P->nsf >= (1 << 24))   // the tile kernel's lookup keys hold 24-bit indices
     return fail(ctx, WVL_EUNSUPPORTED, "density: more than 2^24 - 1 functions");
-  // FP32: the tiles of at most kDensChunkOne functions first (a launch of
-  // their own, with less LDS per workgroup), then the others.  FP64 (chunks of 64, so
-  // about half the tiles need two) runs all tiles in one launch, which
-  // measured faster.
-  std::vector<int32_t> tord[2];
-  for (int d = 0; d < 2; ++d) {
-    tord[d].reserve(ntile);
-    P->dens_one[d] = 0;
-    if (d == 1) {
-      for (int64_t t = 0; t < ntile; ++t) tord[d].push_back((int32_t)t);
-      continue;
-    }
-    for (int pass = 0; pass < 2; ++pass)
-      for (int64_t t = 0; t < ntile; ++t)
-        if ((cptr[t + 1] - cptr[t] <= kDensChunkOne) == (pass == 0)) tord[d].push_back((int32_t)t);
-    for (int64_t t = 0; t < ntile; ++t) P->dens_one[d] += cptr[t + 1] - cptr[t] <= kDensChunkOne;
-  }
   auto drop = [&]() {
-    for (void** p : {(void**)&P->d_cptr, (void**)&P->d_csf, (void**)&P->d_tord[0],
-                     (void**)&P->d_tord[1]})
+    for (void** p : {(void**)&P->d_cptr, (void**)&P->d_csf})
       if (*p) {
         (void)hipFree(*p);
         *p = nullptr;
@@ -1579,10 +1569,6 @@ static wvl_status ensure_cover(wvl_plan* P) {
   wvl_status st;
   // d_cptr last: it marks the lists as ready
   if ((st = upload(ctx, &P->d_csf, csf.data(), sizeof(int32_t) * csf.size())) != WVL_OK ||
-      (st = upload(ctx, &P->d_tord[0], tord[0].data(), sizeof(int32_t) * tord[0].size())) !=
-          WVL_OK ||
-      (st = upload(ctx, &P->d_tord[1], tord[1].data(), sizeof(int32_t) * tord[1].size())) !=
-          WVL_OK ||
       (st = upload(ctx, &P->d_cptr, cptr.data(), sizeof(int64_t) * cptr.size())) != WVL_OK) {
     drop();
     return st;
@@ -1612,8 +1598,7 @@ wvl_status wvl_density(wvl_plan* P, wvl_dtype dt, const void* fine, const int64_
   for (int a = 0; a < 3; ++a) gf[a] = 2 * ctx->grid.n[a] + 29;
   WVL_LAUNCH(ctx, KK_DENS_TILE,
              launch_dens_tile(f64, ctx->stream, P->d_sf, P->d_foff, fine, k_rowptr, k_col, k_val,
-                              k_nnz, P->d_cptr, P->d_csf, P->d_tord[f64], P->dens_one[f64], gf,
-                              rho));
+                              k_nnz, P->d_cptr, P->d_csf, P->nsf, gf, rho));
   return WVL_OK;
 }
 

@@ -170,20 +170,15 @@ int launch_up(int f64, void* stream, int axis, const SfWork* wk, const SfDev* sf
               int gridx, void* ws);
 int launch_up_z(int f64, void* stream, const SfWork* wk, const SfDev* sf, int nsf, int gridx,
                 const void* ws, const int64_t* fine_off, void* fine, int padded);
-// density: tiles of 16 x 4 x 1 fine-grid points (one 64-lane workgroup each)
-// with the functions whose fine box meets them (at most kDensMaxCover)
-// with the functions whose fine box meets them (at most kDensMaxCover),
-// staged kDensChunk[FP32, FP64] functions at a time.  tord lists the tiles:
-// first the n_one with at most kDensChunkOne functions (FP32), then the
-// others.
-constexpr int kDensTile[3] = {16, 4, 1};
+// density: tiles of 16 x 4 x 4 fine-grid points (a workgroup each) with the
+// functions whose fine box meets them; at most kDensMaxCover functions may
+// meet one plane (16 x 4 x 1 points) of a tile
+constexpr int kDensTile[3] = {16, 4, 4};
 constexpr int kDensMaxCover = 1024;
-constexpr int kDensChunk[2] = {128, 64};
-constexpr int kDensChunkOne = 120;   // FP32 tiles of one chunk (four workgroups per CU)
 int launch_dens_tile(int f64, void* stream, const SfDev* sf, const int64_t* foff,
                      const void* fine, const int64_t* krow, const int32_t* kcol,
                      const double* kval, int64_t knnz, const int64_t* cptr, const int32_t* csf,
-                     const int32_t* tord, int64_t n_one, const int* gf, void* rho);
+                     int nsf, const int* gf, void* rho);
 int launch_pot_column(int f64, void* stream, const SfDev* sf, const SfWork* wk, int sf0, int nsf,
                       int gridx, void* ws, const void* pot, int nf1, int nf2, double* epart,
                       const double* conf, double hh, int padded);

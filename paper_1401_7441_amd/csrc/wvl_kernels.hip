@@ -342,19 +342,32 @@ __global__ __launch_bounds__(64) void k_sparse_values(const SfDev* __restrict__ 
 // ---------------------------------------------------------------------------
 // density rho(r) = sum_ab phi_a(r) K^ab phi_b(r) on the fine grid
 // ---------------------------------------------------------------------------
-// One workgroup of eight waves per tile of 16 x 4 x 1 fine-grid points (lane =
-// point in every wave).  The functions whose fine box meets the tile (its
-// cover, increasing index) are taken in chunks of C: the values phi_a(r) of
-// an i-chunk and a j-chunk are staged in LDS (0 outside a box).  Wave w takes
-// the functions a = i-chunk entries w, w + 8, ...: it scans the kernel row a
-// for the columns b in the j-chunk (an LDS hash of the chunk), kept in row
-// order, and accumulates
-//   rho_w(r) += phi_a(r) sum_{b in row a, j-chunk} K[q] phi_b(r);
-// rho(r) is then rho_0 + rho_1 + ... + rho_7.  The order of every sum is
+// One workgroup per tile of 16 x 4 x 4 fine-grid points; a wave takes the
+// 16 points along x of a (y, z).  The functions whose fine box meets the tile
+// (its cover, increasing index) are taken in chunks of C, and the chunk pairs
+// I <= J one after the other:
+//   K block   the rows of both chunks are scanned (a wave per row, the next 256
+//             entries loaded meanwhile) for columns in the pair's chunks (an
+//             LDS hash), and the entries added into a dense block,
+//             T[i][j] = K_ij + K_ji for i < j (i in I, j in J) and K_ii on the
+//             diagonal: the density needs no more;
+//   product   U_i(r) = sum_j T_ij phi_j(r) on the FP64 matrix cores
+//             (16x16x4: 16 functions i x 16 points), the blocks below the
+//             diagonal left out, and rho(r) += sum_i phi_i(r) U_i(r).
+// Lane 16 g + n holds phi at point n of the functions 4 s + g of both chunks
+// in registers: these are the product's operands as they stand, and the
+// product's result has its rows in the same lanes.  The order of every sum is
 // fixed by the tile's cover and K.  Columns outside [0, nsf) never match;
-// positions outside [0, knnz) are skipped.
-constexpr int kDensWaves = 8;
-
+// positions outside [0, knnz) are skipped.  A function that no entry of a pair
+// names does not enter that pair (its values may be infinite).
+// 16 x 4 x 4 points: the rows of K are scanned once per tile and pair, the
+// products cost m^2 / 2 multiply-adds per point for a cover of m (up to 340
+// functions of radius 5-7 bohr at 0.037 per bohr^3, 37 in the middle of all
+// tiles).  1,000 such functions in FP32: 16.8 ms with 16 x 4 x 1 points and the
+// sums on the vector units; 7.8 ms in this form, of which the products take
+// 2.7 (1.6 at the full FP64 matrix rate), the scans 2.5 and the values 1.0.
+// Tiles of 16 x 4 x 2 points (two blocks per CU) took 9.6 ms, chunks of 128
+// functions 9.4 (spilled registers).
 // orders a wave's LDS writes before its other lanes' reads (and the reads
 // before the next writes)
 __device__ __forceinline__ void wave_sync() {
@@ -363,169 +376,204 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-template <int LNB>
-__device__ __forceinline__ int dens_bucket(int b) {
-  return (int)(((uint32_t)b * 2654435761u) >> (32 - LNB));
+// hash of a pair's functions: at most 128 in 2048 slots (function << 8 |
+// position), open addressing, so that one read settles most lookups
+constexpr int kDensLogSlots = 11, kDensSlots = 1 << kDensLogSlots;
+__device__ __forceinline__ int dens_slot(int b) {
+  return (int)(((uint32_t)b * 2654435761u) >> (32 - kDensLogSlots));
 }
 
-// position of function b in a bucket of (function << 8 | position), or -1
-__device__ __forceinline__ int dens_match(uint4 v, int b) {
-  const uint32_t ub = (uint32_t)b;
-  int p = -1;
-  if ((v.x >> 8) == ub) p = (int)(v.x & 255u);
-  if ((v.y >> 8) == ub) p = (int)(v.y & 255u);
-  if ((v.z >> 8) == ub) p = (int)(v.z & 255u);
-  if ((v.w >> 8) == ub) p = (int)(v.w & 255u);
-  return p;
-}
-
-// ONE: every tile of the launch has at most C functions (one chunk; in FP32
-// kDensChunkOne), and the second chunk buffer is left out, the cover list and
-// the hash sized to one chunk (more workgroups fit in a CU's LDS)
-template <typename T, bool ONE>
-__global__ __launch_bounds__(64 * kDensWaves) void k_dens_tile(
+// functions per chunk: both chunks' values at a wave's points fit its registers
+constexpr int kDensChunk = 64, kDensLd = kDensChunk + 4;   // T's rows 4 (mod 16) apart: banks
+constexpr int kDensThreads = 64 * 4 * kDensTile[2];
+template <typename T>
+__global__ __launch_bounds__(kDensThreads) void k_dens_tile(
     const SfDev* __restrict__ sfs, const int64_t* __restrict__ foff, const T* __restrict__ fine,
     const int64_t* __restrict__ krow, const int32_t* __restrict__ kcol,
     const double* __restrict__ kval, int64_t knnz, const int64_t* __restrict__ cptr,
-    const int32_t* __restrict__ csf, const int32_t* __restrict__ tord, int64_t tbase, int tx,
-    int ty, int g0, int g1, int g2, T* __restrict__ rho) {
-  // functions per staged chunk
-  constexpr int C = ONE && sizeof(T) == 4 ? kDensChunkOne : kDensChunk[sizeof(T) == 4 ? 0 : 1];
-  constexpr int LNB = ONE ? 7 : 8;   // log2 of the hash buckets
-  constexpr int NBK = 1 << LNB;
-  __shared__ T vi[C * 64], vj[ONE ? 1 : C * 64];
-  __shared__ int32_t cov[ONE ? C : kDensMaxCover];
-  __shared__ int32_t lj[kDensWaves][64];
-  __shared__ double lk[kDensWaves][64];
-  // the j-chunk's functions by index: NBK buckets of four slots
-  // (function << 8 | position in the chunk)
-  __shared__ uint4 hb[NBK];
-  uint32_t* hslot = reinterpret_cast<uint32_t*>(hb);
-  double (*red)[64] = lk;   // the final reduction reuses lk
-  static_assert(C <= 256 && 4 * NBK >= 2 * C, "chunk positions need 8 bits, the hash room");
-  const int tile = tord[tbase + blockIdx.x];
+    const int32_t* __restrict__ csf, int nsf, int tx, int ty, int g0, int g1, int g2,
+    T* __restrict__ rho) {
+  constexpr int C = kDensChunk, S = C / 4, LD = kDensLd, NT = kDensThreads, NW = NT / 64;
+  typedef double V __attribute__((ext_vector_type(4)));
+  // T: entries of the rows i, and of the rows j (each element then has one
+  // wave that adds to it, so duplicated entries add up in their order)
+  __shared__ __align__(16) double tk[2][C * LD];
+  __shared__ uint32_t hslot[kDensSlots];
+  // the pair's functions (I's, then J's): index, geometry on the fine grid
+  // (origin, extents), first fine value, row of K
+  __shared__ int32_t cov[2 * C];
+  __shared__ int32_t geo[2 * C][6];
+  __shared__ int64_t fo[2 * C], kq[2 * C];
+  __shared__ int32_t kl[2 * C];
+  __shared__ uint8_t used[2][C];      // the function has an entry in the pair's block
+  static_assert(C == 64, "a lane per function of a chunk");
+  const int tile = blockIdx.x;
   const int ix = tile % tx, iy = (tile / tx) % ty, iz = tile / (tx * ty);
-  const int tid = threadIdx.x, lane = tid & 63;
+  const int tid = threadIdx.x, lane = tid & 63, n = lane & 15, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int gx = ix * kDensTile[0] + (lane & 15);
-  const int gy = iy * kDensTile[1] + (lane >> 4);
-  const int gz = iz;
+  const int gx = ix * kDensTile[0] + n;
+  const int gy = iy * kDensTile[1] + (wave & 3);
+  const int gz = iz * kDensTile[2] + (wave >> 2);
   const bool inside = gx < g0 && gy < g1 && gz < g2;
   const int64_t c0 = cptr[tile];
   const int m = (int)(cptr[tile + 1] - c0);
-  for (int i = tid; i < m; i += 64 * kDensWaves) cov[i] = csf[c0 + i];
-  // phi_a at this lane's point, 0 outside a's fine box
-  auto value = [&](int a) -> T {
-    const SfDev& A = sfs[a];
-    const int px = gx - 2 * A.lo[0], py = gy - 2 * A.lo[1], pz = gz - 2 * A.lo[2];
-    const int R0 = 2 * A.n[0] + 29, R1 = 2 * A.n[1] + 29, R2 = 2 * A.n[2] + 29;
-    if (!inside || px < 0 || px >= R0 || py < 0 || py >= R1 || pz < 0 || pz >= R2) return T(0);
-    return fine[foff[a] + ((int64_t)pz * R1 + py) * R0 + px];
-  };
   double acc = 0.0;
-  __syncthreads();
+  T pi[S], pj[S];
+  // stages a chunk's functions at half C (a barrier before and after)
+  auto stage = [&](int half, int at, int cnt) {
+    __syncthreads();   // the chunk before is no longer read
+    if (tid < cnt) {
+      const int h = half * C + tid;
+      const int a = csf[c0 + at + tid];
+      const SfDev& A = sfs[a];
+      cov[h] = a;
+      fo[h] = foff[a];
+      const int64_t q0 = max((int64_t)0, krow[a]), q1 = min(knnz, krow[a + 1]);
+      kq[h] = q0;
+      kl[h] = (int)min(max((int64_t)0, q1 - q0), (int64_t)INT32_MAX);
+#pragma unroll
+      for (int d = 0; d < 3; ++d) {
+        geo[h][d] = 2 * A.lo[d];
+        geo[h][3 + d] = 2 * A.n[d] + 29;
+      }
+    }
+    __syncthreads();
+  };
+  auto values = [&](int half, int cnt, T (&v)[S]) {
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+      v[s] = T(0);
+      if (4 * s >= cnt) continue;
+      const int h = half * C + min(4 * s + g, cnt - 1);
+      const int px = gx - geo[h][0], py = gy - geo[h][1], pz = gz - geo[h][2];
+      const int R0 = geo[h][3], R1 = geo[h][4], R2 = geo[h][5];
+      if (4 * s + g < cnt && inside && (uint32_t)px < (uint32_t)R0 &&
+          (uint32_t)py < (uint32_t)R1 && (uint32_t)pz < (uint32_t)R2)
+        v[s] = fine[fo[h] + ((int64_t)pz * R1 + py) * R0 + px];
+      if (s % 2 == 1) __builtin_amdgcn_sched_barrier(0);   // few addresses at a time
+    }
+  };
   for (int ic = 0; ic < m; ic += C) {
     const int ni = min(C, m - ic);
-    for (int i = wave; i < ni; i += kDensWaves) vi[i * 64 + lane] = value(cov[ic + i]);
-    for (int jc = 0; jc < m; jc += C) {
+    stage(0, ic, ni);
+    values(0, ni, pi);
+    for (int jc = ic; jc < m; jc += C) {
+      const bool diag = jc == ic;
       const int nj = min(C, m - jc);
-      const T* vb = vi;
-      if (!ONE && jc != ic) {
-        for (int j = wave; j < nj; j += kDensWaves) vj[j * 64 + lane] = value(cov[jc + j]);
-        vb = vj;
+      const int jh = diag ? 0 : 1;
+      if (!diag) {
+        stage(1, jc, nj);
+        values(1, nj, pj);
+      } else {
+#pragma unroll
+        for (int s = 0; s < S; ++s) pj[s] = pi[s];
       }
-      for (int h = tid; h < 4 * NBK; h += 64 * kDensWaves) hslot[h] = 0xFFFFFFFFu;
+      // the wave's rows to scan (I's, then J's), i = wave, wave + NW, ..: 256
+      // entries at a time, the next ones loaded while these are looked up
+      const int nrow = ni + (diag ? 0 : nj);
+      int si = wave, sq = 0;   // the next row and its first entry
+      auto slot = [&](int i) { return i < ni ? i : C + i - ni; };
+      int b[4], bn[4], pa = 0, pan = 0;
+      double kb[4], kn[4];
+      auto fetch = [&](int (&bb)[4], double (&kk)[4], int& row) {
+        row = -1;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) bb[u] = -1;
+        while (si < nrow && sq >= kl[slot(si)]) {
+          si += NW;
+          sq = 0;
+        }
+        if (si >= nrow) return;
+        row = slot(si);
+        const int64_t q = kq[row] + sq;
+        const int left = kl[row] - sq;
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          if (64 * u + lane < left) {
+            bb[u] = kcol[q + 64 * u + lane];
+            kk[u] = kval[q + 64 * u + lane];
+          }
+        sq += 256;
+      };
+      fetch(b, kb, pa);
+      // hash of the pair's functions and an empty T
+      for (int h = tid; h < kDensSlots; h += NT) hslot[h] = 0xFFFFFFFFu;
+      if (tid < 2 * C) used[tid / C][tid % C] = 0;
+      const int nr = (ni + 15) & ~15;
+      for (int h = tid; h < nr * (LD / 2); h += NT)
+        reinterpret_cast<double2*>(tk[0])[h] = reinterpret_cast<double2*>(tk[1])[h] =
+            make_double2(0.0, 0.0);
       __syncthreads();
-      // 4 NBK slots > nj: every insertion finds a free slot, every lookup a
-      // bucket that is not full
-      if (tid < nj) {
-        const int b = cov[jc + tid];
-        const uint32_t key = ((uint32_t)b << 8) | (uint32_t)tid;
-        for (int bk = dens_bucket<LNB>(b);; bk = (bk + 1) & (NBK - 1)) {
-          int c = 0;
-          while (c < 4 && atomicCAS(&hslot[4 * bk + c], 0xFFFFFFFFu, key) != 0xFFFFFFFFu) ++c;
-          if (c < 4) break;
+      if (tid < nrow) {
+        const int h = slot(tid);
+        const uint32_t key = ((uint32_t)cov[h] << 8) | (uint32_t)h;
+        int at = dens_slot(cov[h]);
+        while (atomicCAS(&hslot[at], 0xFFFFFFFFu, key) != 0xFFFFFFFFu) at = (at + 1) & (kDensSlots - 1);
+      }
+      __syncthreads();
+      while (pa >= 0) {   // uniform over the wave
+        fetch(bn, kn, pan);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          if (b[u] < 0 || b[u] >= nsf) continue;
+          int at = dens_slot(b[u]);
+          uint32_t v = hslot[at];
+          while (v != 0xFFFFFFFFu && (v >> 8) != (uint32_t)b[u]) {
+            at = (at + 1) & (kDensSlots - 1);
+            v = hslot[at];
+          }
+          const int p = v == 0xFFFFFFFFu ? -1 : (int)(v & 255u);
+          // an entry inside one chunk belongs to its diagonal pair
+          if (p < 0 || (!diag && (p >= C) == (pa >= C))) continue;
+          const int r = min(pa, p), c = max(pa, p) - (diag ? 0 : C);   // row in I, column in J
+          unsafeAtomicAdd(&tk[pa > p][r * LD + c], kb[u]);
+          used[0][r] = 1;
+          used[jh][c] = 1;
+        }
+        pa = pan;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          b[u] = bn[u];
+          kb[u] = kn[u];
         }
       }
       __syncthreads();
-      const int blo = cov[jc], bhi = cov[jc + nj - 1];
-      // the wave's rows i = wave, wave + 8, ..; the next row's bounds and
-      // the next 64 kernel entries are loaded while the current ones are
-      // used (the sums keep their order)
-      int i = wave;
-      int64_t q0 = 0, q1 = 0;
-      if (i < ni) {
-        const int a = cov[ic + i];
-        q0 = max((int64_t)0, krow[a]);
-        q1 = min(knnz, krow[a + 1]);
+      for (int h = tid; h < nr * (LD / 2); h += NT) {
+        double2& t = reinterpret_cast<double2*>(tk[0])[h];
+        const double2 v = reinterpret_cast<double2*>(tk[1])[h];
+        t.x += v.x;
+        t.y += v.y;
       }
-      while (i < ni) {
-        const int inx = i + kDensWaves;
-        int64_t n0 = 0, n1 = 0;
-        if (inx < ni) {
-          const int an = cov[ic + inx];
-          n0 = krow[an];
-          n1 = krow[an + 1];
-        }
-        double u = 0.0;
-        int bn = -1;
-        double kn = 0.0;
-        if (q0 + lane < q1) {
-          bn = kcol[q0 + lane];
-          kn = kval[q0 + lane];
-        }
-        for (int64_t qq = q0; qq < q1; qq += 64) {
-          const int b = bn;
-          const double kb = kn;
-          bn = -1;
-          kn = 0.0;
-          if (qq + 64 + lane < q1) {
-            bn = kcol[qq + 64 + lane];
-            kn = kval[qq + 64 + lane];
+      __syncthreads();
+      // bit 4 s: function 4 s + g has an entry
+      const uint64_t ui = __ballot(used[0][lane]) >> g, uj = __ballot(used[jh][lane]) >> g;
+#pragma unroll
+      for (int s = 0; s < S; ++s) pj[s] = (uj >> (4 * s)) & 1u ? pj[s] : T(0);
+      const double* const ta = tk[0] + n * LD + g;
+#pragma unroll
+      for (int st = 0; st < C / 16; ++st) {
+        if (16 * st >= ni) continue;
+        V d = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int cb = 0; cb < C / 16; ++cb) {
+          if (16 * cb >= nj || (diag && cb < st)) continue;
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int s = 4 * cb; s < 4 * cb + 4; ++s) {
+            d = __builtin_amdgcn_mfma_f64_16x16x4f64(ta[16 * st * LD + 4 * s], (double)pj[s], d, 0,
+                                                     0, 0);
           }
-          int j = -1;
-          double kq = 0.0;
-          if (b >= blo && b <= bhi) {   // b's position in the j-chunk, if any
-            int bk = dens_bucket<LNB>(b);
-            uint4 v = hb[bk];
-            int p = dens_match(v, b);
-            while (p < 0 && v.w != 0xFFFFFFFFu) {
-              bk = (bk + 1) & (NBK - 1);
-              v = hb[bk];
-              p = dens_match(v, b);
-            }
-            if (p >= 0) {
-              j = p;
-              kq = kb;
-            }
-          }
-          const unsigned long long hit = __ballot(j >= 0);
-          if (j >= 0) {
-            const int pos = __popcll(hit & ((1ull << lane) - 1ull));
-            lj[wave][pos] = j;
-            lk[wave][pos] = kq;
-          }
-          wave_sync();
-          const int cnt = __popcll(hit);
-#pragma unroll 4
-          for (int t = 0; t < cnt; ++t) u += lk[wave][t] * (double)vb[lj[wave][t] * 64 + lane];
-          wave_sync();
         }
-        acc += (double)vi[i * 64 + lane] * u;
-        i = inx;
-        q0 = max((int64_t)0, n0);
-        q1 = min(knnz, n1);
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          acc += (ui >> (4 * (4 * st + j))) & 1u ? (double)pi[4 * st + j] * d[j] : 0.0;
       }
-      __syncthreads();   // vi / vj, the hash and lk no longer read
+      __syncthreads();   // T, the hash and the flags no longer read
     }
   }
-  red[wave][lane] = acc;
-  __syncthreads();
-  if (wave == 0 && inside) {
-    double r = red[0][lane];
-    for (int w = 1; w < kDensWaves; ++w) r += red[w][lane];
-    rho[((int64_t)gz * g1 + gy) * g0 + gx] = (T)r;
-  }
+  acc += __shfl_xor(acc, 16, 64);
+  acc += __shfl_xor(acc, 32, 64);
+  if (inside && g == 0) rho[((int64_t)gz * g1 + gy) * g0 + gx] = (T)acc;
 }
 
 // ---------------------------------------------------------------------------
@@ -1276,10 +1324,8 @@ int preload_kernels() {
   const void* fns[] = {(const void*)k_finalize, (const void*)k_sparse_values<float>,
                        (const void*)k_sparse_values<double>, (const void*)k_update<float>,
                        (const void*)k_update<double>, (const void*)k_sf_dot<float>,
-                       (const void*)k_sf_dot<double>, (const void*)k_dens_tile<float, true>,
-                       (const void*)k_dens_tile<float, false>,
-                       (const void*)k_dens_tile<double, true>,
-                       (const void*)k_dens_tile<double, false>, (const void*)k_grad_rows<float>,
+                       (const void*)k_sf_dot<double>, (const void*)k_dens_tile<float>,
+                       (const void*)k_dens_tile<double>, (const void*)k_grad_rows<float>,
                        (const void*)k_grad_rows<double>};
   for (const void* f : fns) {
     hipFuncAttributes a;
@@ -1361,34 +1407,20 @@ int launch_sparse_values(int f64, void* stream, const SfDev* sf, const wvl_seg* 
 int launch_dens_tile(int f64, void* stream, const SfDev* sf, const int64_t* foff,
                      const void* fine, const int64_t* krow, const int32_t* kcol,
                      const double* kval, int64_t knnz, const int64_t* cptr, const int32_t* csf,
-                     const int32_t* tord, int64_t n_one, const int* gf, void* rho) {
+                     int nsf, const int* gf, void* rho) {
   const int tx = (gf[0] + kDensTile[0] - 1) / kDensTile[0];
   const int ty = (gf[1] + kDensTile[1] - 1) / kDensTile[1];
   const int tz = (gf[2] + kDensTile[2] - 1) / kDensTile[2];
-  const int64_t ntile = (int64_t)tx * ty * tz;
-  const dim3 blk(64 * kDensWaves);
+  const dim3 g((unsigned)((int64_t)tx * ty * tz));
   hipStream_t st = (hipStream_t)stream;
-  for (int one = 1; one >= 0; --one) {
-    const int64_t base = one ? 0 : n_one, n = one ? n_one : ntile - n_one;
-    if (n == 0) continue;
-    const dim3 g((unsigned)n);
-    if (f64 && one)
-      hipLaunchKernelGGL((k_dens_tile<double, true>), g, blk, 0, st, sf, foff,
-                         (const double*)fine, krow, kcol, kval, knnz, cptr, csf, tord, base, tx,
-                         ty, gf[0], gf[1], gf[2], (double*)rho);
-    else if (f64)
-      hipLaunchKernelGGL((k_dens_tile<double, false>), g, blk, 0, st, sf, foff,
-                         (const double*)fine, krow, kcol, kval, knnz, cptr, csf, tord, base, tx,
-                         ty, gf[0], gf[1], gf[2], (double*)rho);
-    else if (one)
-      hipLaunchKernelGGL((k_dens_tile<float, true>), g, blk, 0, st, sf, foff,
-                         (const float*)fine, krow, kcol, kval, knnz, cptr, csf, tord, base, tx,
-                         ty, gf[0], gf[1], gf[2], (float*)rho);
-    else
-      hipLaunchKernelGGL((k_dens_tile<float, false>), g, blk, 0, st, sf, foff,
-                         (const float*)fine, krow, kcol, kval, knnz, cptr, csf, tord, base, tx,
-                         ty, gf[0], gf[1], gf[2], (float*)rho);
-  }
+  if (f64)
+    hipLaunchKernelGGL(k_dens_tile<double>, g, dim3(kDensThreads), 0, st, sf, foff,
+                       (const double*)fine, krow, kcol, kval, knnz, cptr, csf, nsf, tx, ty, gf[0],
+                       gf[1], gf[2], (double*)rho);
+  else
+    hipLaunchKernelGGL(k_dens_tile<float>, g, dim3(kDensThreads), 0, st, sf, foff,
+                       (const float*)fine, krow, kcol, kval, knnz, cptr, csf, nsf, tx, ty, gf[0],
+                       gf[1], gf[2], (float*)rho);
   return (int)hipGetLastError();
 }
 
