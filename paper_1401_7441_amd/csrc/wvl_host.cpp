@@ -1745,6 +1745,30 @@ wvl_status wvl_foe(wvl_plan* P, const double* s_val, const double* h_val, int32_
   auto axpby = [&](double a, const double* x, double b, const double* y, double d, double* o) {
     return launch_foe_axpby(s, nnz, a, x, b, y, rw, cl, d, o);
   };
+  // With few enough functions a row of the running matrix fits the LDS, and
+  // products run from the right by a symmetric matrix (k_foe_rmul): products
+  // from the left on the transposes.  The Chebyshev matrices T^i (i > 1) and
+  // K' are then held transposed; their traces are the same.  Per product
+  // against k_foe_mm: 1,000 functions 43 / 70 us, 4,000 34 / 54, 6,000 58 /
+  // 79, 8,000 106 / 110 (two blocks left per CU): the line lies where the
+  // gain ends and the row still fits 64 KiB.
+  const bool spread = (int64_t)n + pc.maxdeg <= kFoeSpread;
+  auto rmul = [&](double al, const double* R, const double* A, double be, const double* D, double* C) {
+    return launch_foe_rmul(s, n, pc.d_foe_rows, rp, cl, al, R, A, be, D, C, pc.maxdeg);
+  };
+  // o = ((Sh M)|_P Sh)|_P for the symmetric Sh, from M or (spread) M^T; o is
+  // neither M nor X, which is overwritten
+  auto two_sided = [&](const double* M, double* o) -> wvl_status {
+    if (spread) {
+      WVL_LAUNCH(ctx, KK_FOE, rmul(1.0, M, Sh, 0.0, nullptr, o));
+      WVL_LAUNCH(ctx, KK_FOE, launch_foe_gather(s, nnz, tp, o, X));
+      WVL_LAUNCH(ctx, KK_FOE, rmul(1.0, X, Sh, 0.0, nullptr, o));
+    } else {
+      WVL_LAUNCH(ctx, KK_FOE, mm(1.0, Sh, M, 0.0, nullptr, X));
+      WVL_LAUNCH(ctx, KK_FOE, mm(1.0, X, Sh, 0.0, nullptr, o));
+    }
+    return WVL_OK;
+  };
   // S and H on the overlap pattern, symmetric parts (they are symmetric in
   // exact arithmetic); S^-1/2 ~ (3 I - S) / 2, the first-order Taylor form
   WVL_LAUNCH(ctx, KK_FOE, launch_foe_sym(s, nnz, tp, s_val, Ss));
@@ -1755,8 +1779,7 @@ wvl_status wvl_foe(wvl_plan* P, const double* s_val, const double* h_val, int32_
   // spectral bounds: Gershgorin discs of S^-1/2 H S^-1/2 unless given
   // (Sh and Hs are symmetric: they are their own transposes)
   if (eps_min >= eps_max) {
-    WVL_LAUNCH(ctx, KK_FOE, mm(1.0, Sh, Hs, 0.0, nullptr, X));
-    WVL_LAUNCH(ctx, KK_FOE, mm(1.0, X, Sh, 0.0, nullptr, Tm(0)));
+    if ((st = two_sided(Hs, Tm(0))) != WVL_OK) return st;
     WVL_LAUNCH(ctx, KK_FOE, launch_foe_sym(s, nnz, tp, Tm(0), Ht));
     // X and T^0 are free here, and each holds nnz >= n doubles
     WVL_LAUNCH(ctx, KK_FOE, launch_foe_gersh(s, n, rp, cl, Ht, X, Tm(0), red));
@@ -1770,8 +1793,7 @@ wvl_status wvl_foe(wvl_plan* P, const double* s_val, const double* h_val, int32_
   const double sigma = 2.0 / (eps_max - eps_min), tau = 0.5 * (eps_min + eps_max);
   // H~ = sigma (H - tau S), then H~' = S^-1/2 H~ S^-1/2 (symmetric part)
   WVL_LAUNCH(ctx, KK_FOE, axpby(sigma, Hs, -sigma * tau, Ss, 0.0, Hs));
-  WVL_LAUNCH(ctx, KK_FOE, mm(1.0, Sh, Hs, 0.0, nullptr, X));
-  WVL_LAUNCH(ctx, KK_FOE, mm(1.0, X, Sh, 0.0, nullptr, Tm(0)));
+  if ((st = two_sided(Hs, Tm(0))) != WVL_OK) return st;
   WVL_LAUNCH(ctx, KK_FOE, launch_foe_sym(s, nnz, tp, Tm(0), Ht));
   // Spectrum guard: with the Taylor S^-1/2, S^-1/2 S S^-1/2 is not I, so
   // H~' can reach outside [-1, 1] even for exact bounds, and T^i then grows
@@ -1796,6 +1818,11 @@ wvl_status wvl_foe(wvl_plan* P, const double* s_val, const double* h_val, int32_
     }
   }
   const double sig_f = sigma / gr, tau_f = tau + gc / sigma;
+  // T^{j+1} from T^j and T^{j-1}
+  auto next = [&](int j) {
+    return spread ? rmul(2.0, Tm(j), Ht, -1.0, Tm(j - 1), Tm(j + 1))
+                  : mm(2.0, Ht, Tm(j), -1.0, Tm(j - 1), Tm(j + 1));
+  };
   // pass 1: traces of the Chebyshev matrices T^0 .. T^npl
   auto start = [&]() -> wvl_status {
     WVL_LAUNCH(ctx, KK_FOE, axpby(0.0, nullptr, 0.0, nullptr, 1.0, Tm(0)));
@@ -1809,7 +1836,7 @@ wvl_status wvl_foe(wvl_plan* P, const double* s_val, const double* h_val, int32_
     WVL_LAUNCH(ctx, KK_FOE, trace(1));
   }
   for (int j = 1; j < npl; ++j) {
-    WVL_LAUNCH(ctx, KK_FOE_MM, mm(2.0, Ht, Tm(j), -1.0, Tm(j - 1), Tm(j + 1)));
+    WVL_LAUNCH(ctx, KK_FOE_MM, next(j));
     if (!keep) WVL_LAUNCH(ctx, KK_FOE, trace(j + 1));
   }
   if (keep) WVL_LAUNCH(ctx, KK_FOE, launch_foe_trace(s, n, pc.d_dpos, Tall, nnz, npl + 1, tr, 0));
@@ -1849,13 +1876,12 @@ wvl_status wvl_foe(wvl_plan* P, const double* s_val, const double* h_val, int32_
     WVL_LAUNCH(ctx, KK_FOE, axpby(coef[1], Ht, 0.0, nullptr, 0.5 * coef[0], Kp));
     if ((st = start()) != WVL_OK) return st;
     for (int j = 1; j < npl; ++j) {
-      WVL_LAUNCH(ctx, KK_FOE_MM, mm(2.0, Ht, Tm(j), -1.0, Tm(j - 1), Tm(j + 1)));
+      WVL_LAUNCH(ctx, KK_FOE_MM, next(j));
       WVL_LAUNCH(ctx, KK_FOE, axpby(1.0, Kp, coef[j + 1], Tm(j + 1), 0.0, Kp));
     }
   }
   // K = S^-1/2 K' S^-1/2 (symmetric part); E_BS = Tr(K H~) / sigma + tau Tr(K S)
-  WVL_LAUNCH(ctx, KK_FOE, mm(1.0, Sh, Kp, 0.0, nullptr, X));
-  WVL_LAUNCH(ctx, KK_FOE, mm(1.0, X, Sh, 0.0, nullptr, Tm(0)));
+  if ((st = two_sided(Kp, Tm(0))) != WVL_OK) return st;
   WVL_LAUNCH(ctx, KK_FOE, launch_foe_sym(s, nnz, tp, Tm(0), k_val));
   WVL_LAUNCH(ctx, KK_FOE, launch_foe_dot(s, nnz, k_val, Hs, X, red, 2));
   WVL_LAUNCH(ctx, KK_FOE, launch_foe_dot(s, nnz, k_val, Ss, X, red, 3));

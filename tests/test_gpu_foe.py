@@ -153,6 +153,47 @@ def test_foe_on_long_rows(m):
     assert np.array_equal(res[0][0], res[1][0]) and res[0][1:] == res[1][1:]
 
 
+@pytest.mark.parametrize("sizes", [(5, 5, 6), (5, 6, 6)])
+def test_foe_both_product_kernels(sizes):
+    """511 and 481 equal groups of 16 and 17 functions: 8,176 functions with
+    rows of up to 16, the most whose products take rows spread out in LDS, and
+    8,177 with rows of up to 17, which take the hash tables.  A group is a chain of three clusters (pattern: clusters
+    differ by at most one), groups share no points; with the same S and H in
+    each, K and mu are those of one group with its share of n_occ."""
+    m = sum(sizes)
+    ng = {16: 511, 17: 481}[m]
+    n = ng * m
+    _print(f"case: FOE, {ng} groups of {m} ({n} functions)")
+    cl = np.repeat(np.arange(3), sizes)
+    lrs = []
+    for q in range(ng):
+        y, z = 8 * (q % 23), 8 * (q // 23)
+        lrs += [LR.box_locreg((8 * c, y, z), (11, 7, 7), (8 * c + 3, y + 2, z + 2),
+                              (8 * c + 6, y + 4, z + 4)) for c in cl]
+    plan = W.Plan(W.Context(0.45, (32, 192, 192)), *to_abi(lrs))
+    mask = np.abs(cl[:, None] - cl[None, :]) <= 1
+    rows, cols = np.nonzero(mask)
+    zin = torch.zeros(max(1, plan.info["in_coefs"]), dtype=torch.float64, device="cuda")
+    prp, pcl, _ = W.sparse_overlap(plan, zin, zin, False, values=False)
+    want_rp = np.concatenate([[0], np.cumsum(np.tile(mask.sum(1), ng))])
+    want_cl = (np.arange(ng)[:, None] * m + cols[None, :]).ravel()
+    assert np.array_equal(prp.cpu().numpy(), want_rp) and np.array_equal(pcl.cpu().numpy(), want_cl)
+    rng = np.random.default_rng(4200 + m)
+    R1, R2 = rng.standard_normal((m, m)), rng.standard_normal((m, m))
+    S = (np.eye(m) + 0.2 / np.sqrt(m) * 0.5 * (R1 + R1.T)) * mask
+    H = (np.diag(np.linspace(-1.0, 1.0, m)) + 0.5 / np.sqrt(m) * (R2 + R2.T)) * mask
+    npl, delta, nocc = 30, 0.4, 0.5 * m
+    K, mu, ebs, bnd = F.foe(S, H, mask, npl, delta, nocc)
+    ktol, mtol = _tolerances(bnd, delta)
+    kv, gmu, gebs = W.foe(plan, torch.tensor(np.tile(S[rows, cols], ng), device="cuda"),
+                          torch.tensor(np.tile(H[rows, cols], ng), device="cuda"), npl, delta,
+                          ng * nocc)
+    err = np.max(np.abs(kv.cpu().numpy().reshape(ng, -1) - K[rows, cols]))
+    _print(f"  K err {err:.2e} of max |K| {np.max(np.abs(K)):.2f}, mu err {abs(gmu - mu):.2e}")
+    assert err <= ktol * np.max(np.abs(K))
+    assert abs(gmu - mu) <= mtol and abs(gebs - ng * ebs) <= 1e-10 * ng * max(1.0, abs(ebs))
+
+
 def test_foe_full_size_lattice():
     """The bench's FOE configuration (1,000 functions, npl = 100, delta = 1,
     n_occ = n/2, Gershgorin bounds) on a 10 x 10 x 10 lattice of 11^3 boxes
