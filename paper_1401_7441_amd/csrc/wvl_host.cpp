@@ -1461,7 +1461,7 @@ wvl_status wvl_sparse_overlap(wvl_plan* P, const void* bra_c, int ket_is_output,
                                     P->d_rr, ket_is_output, bra_c, ket_c, pc.d_row, pc.d_col,
                                     half ? pc.d_order_u : pc.d_order,
                                     half ? pc.d_mirror_u : nullptr, half ? pc.nnz_u : pc.nnz,
-                                    val));
+                                    pc.nnz, val));
   }
   return WVL_OK;
 }
@@ -2096,7 +2096,7 @@ static wvl_status capture_step(wvl_plan* P, wvl_dtype dt, uint32_t terms, const 
                                          psi_c, ket_out ? hpsi_c : psi_c, pc.d_row, pc.d_col,
                                          half ? pc.d_order_u : pc.d_order,
                                          half ? pc.d_mirror_u : nullptr,
-                                         half ? pc.nnz_u : pc.nnz, val);
+                                         half ? pc.nnz_u : pc.nnz, pc.nnz, val);
       if (e != 0) st = hip_fail(ctx, "graph capture", "launch of sparse_values", (hipError_t)e);
     }
   }

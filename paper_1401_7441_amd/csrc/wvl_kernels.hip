@@ -195,13 +195,21 @@ __global__ __launch_bounds__(64) void k_pattern(const SfDev* __restrict__ sfs,
   if (rowptr == nullptr && lane == 0) count[a] = n;
 }
 
-// one wavefront per nonzero (a, b), in two phases per batch of 64 rows of the
-// box where both patterns may meet.  Phase 1: lane r resolves row r (row
-// tables, segment lists) to the first overlapping run of each kind (scaling /
-// wavelet) and keeps it in LDS; further runs of the same row, which sphere
-// patterns never produce, are summed by that lane directly.  Phase 2: four
-// 16-lane groups stream the kept runs with contiguous loads.  Every lane's
-// partial sum and the final shuffle tree have an order fixed by the pair.
+// One block of W waves per nonzero (a, b): batches of 64 rows of the box where
+// both patterns may meet, dealt to the waves in turn.  Phase 1: lane r resolves
+// row r (run records; the segment lists where a row holds several runs) to the
+// first overlapping run of each kind (scaling / wavelet) and one further run of
+// either; more, which sphere patterns hardly produce, are summed by that lane
+// directly.  Phase 2: four 16-lane groups stream the coarse runs, four rows of
+// each under way; then the whole wave takes the fine runs (seven wavelets per
+// point: 70 values on average) and the further ones, four under way.  Every
+// lane's partial sum and the final tree have an order fixed by the pair.
+// Bound by the latency of each wave's chain of loads and by the lines that L1
+// and L2 keep for the others (half of the requests of 1,000 functions miss L2),
+// so that registers stay below those that let eight waves run per SIMD.  H of
+// 1,000 functions of radius 5-7 bohr (303,083 entries) in FP64: 5.62 ms with
+// one wave per pair and 16 lanes per fine run, 5.28 in this form; FP32, 4,000
+// functions: 9.37 and 8.02 ms; S of 56 functions: 187 and 34 us.
 // mirror (may be NULL): for the pair at processing position s, the CSR
 // position that receives the same value as well (the transposed pair of a
 // symmetric matrix), or -1.
@@ -213,8 +221,49 @@ __device__ __forceinline__ double run_dot(const T* __restrict__ pa, const T* __r
   return acc;
 }
 
+// orders a wave's LDS writes before its other lanes' reads (and the reads
+// before the next writes)
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// The runs of all lanes (starts a, b, length n; 0: none), one after the other
+// by the whole wave: lane l takes the positions l, l + 64, ...
 template <typename T>
-__global__ __launch_bounds__(64) void k_sparse_values(const SfDev* __restrict__ sfs,
+__device__ __forceinline__ void fine_runs(const T* __restrict__ bra, const T* __restrict__ ket,
+                                          int a, int b, int n, double& acc) {
+  constexpr int R = 4;   // runs under way
+  const int lane = threadIdx.x & 63;
+  uint64_t m = __ballot(n > 0);
+  while (m) {
+    int l[R];
+    const T *pa[R], *pk[R];
+    T va[R], vk[R];
+#pragma unroll
+    for (int u = 0; u < R; ++u) {
+      const int q = m ? __builtin_ctzll(m) : 0;
+      l[u] = m ? __builtin_amdgcn_readlane(n, q) : 0;
+      pa[u] = bra + __builtin_amdgcn_readlane(a, q);
+      pk[u] = ket + __builtin_amdgcn_readlane(b, q);
+      m &= m - 1;
+      va[u] = vk[u] = T(0);
+      if (lane < l[u]) {
+        va[u] = pa[u][lane];
+        vk[u] = pk[u][lane];
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < R; ++u) acc += (double)va[u] * (double)vk[u];
+#pragma unroll
+    for (int u = 0; u < R; ++u)
+      for (int x = lane + 64; x < l[u]; x += 64) acc += (double)pa[u][x] * (double)pk[u][x];
+  }
+}
+
+template <typename T, int W>
+__global__ __launch_bounds__(64 * W, 8) void k_sparse_values(const SfDev* __restrict__ sfs,
                                                       const wvl_seg* __restrict__ seg,
                                                       const int32_t* __restrict__ rt,
                                                       const RowRun* __restrict__ rr, int ket_out,
@@ -225,8 +274,9 @@ __global__ __launch_bounds__(64) void k_sparse_values(const SfDev* __restrict__ 
                                                       const int32_t* __restrict__ order,
                                                       const int32_t* __restrict__ mirror,
                                                       int64_t nnz, double* __restrict__ val) {
-  __shared__ int64_t ea[2][64], eb[2][64];   // run start offsets (bra, ket) per kind
-  __shared__ int32_t el[2][64];              // run lengths (0: none)
+  // coarse runs of a wave's rows: starts (bra, ket), lengths (0: none)
+  __shared__ int32_t ea_[W][64], eb_[W][64], el_[W][64];
+  __shared__ double part[W];
   // Workgroups are dealt to the 8 XCDs in turn: block b runs on XCD b % 8.
   // Each XCD walks its own contiguous eighth of the processing order, so the
   // pairs resident on one XCD share rows (and, rows being in spatial order,
@@ -235,7 +285,8 @@ __global__ __launch_bounds__(64) void k_sparse_values(const SfDev* __restrict__ 
   const int64_t s = (int64_t)(blockIdx.x % 8) * per + blockIdx.x / 8;
   if (s >= nnz) return;
   const int64_t k = order[s];
-  const int lane = threadIdx.x;
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  int32_t *const ea = ea_[wv], *const eb = eb_[wv], *const el = el_[wv];
   const int grp = lane >> 4, gl = lane & 15;
   const SfDev& A = sfs[rowi[k]];
   const SfDev& B = sfs[coli[k]];
@@ -244,96 +295,114 @@ __global__ __launch_bounds__(64) void k_sparse_values(const SfDev* __restrict__ 
   const int z0 = max(A.bb_in[4], bb[4]), z1 = min(A.bb_in[5], bb[5]);
   const PatBox pb = pat_box(B, ket_out);
   const int pc = ket_out ? 2 : 0, pf = ket_out ? 3 : 1;
-  const int64_t bc = ket_out ? B.cout : B.cin;
-  const int64_t bnc = ket_out ? B.on_c : B.n_c;
+  const T* const pbra = bra + A.cin;
+  const T* const pket = ket + (ket_out ? B.cout : B.cin);
+  const int bnc = (int)(ket_out ? B.on_c : B.n_c);
   const int ny = y1 - y0 + 1;
   const int nrows = (y1 >= y0 && z1 >= z0) ? ny * (z1 - z0 + 1) : 0;
   double acc = 0.0;
-  for (int r0 = 0; r0 < nrows; r0 += 64) {
+  for (int r0 = 64 * wv; r0 < nrows; r0 += 64 * W) {
     // phase 1
     const int r = r0 + lane;
+    const bool in = r < nrows;
+    const int y = y0 + (in ? r : 0) % ny, z = z0 + (in ? r : 0) / ny;
+    const int64_t ra = (int64_t)(z - A.lo[2]) * A.n[1] + (y - A.lo[1]);
+    const int64_t rb = (int64_t)(z - pb.oz) * pb.by + (y - pb.oy);
+    // compact row runs: one 8-byte record per row, kind and side
+    RowRun wa[2], wb[2];
 #pragma unroll
     for (int fine = 0; fine < 2; ++fine) {
-      el[fine][lane] = 0;
-      if (r < nrows) {
-        const int y = y0 + r % ny, z = z0 + r / ny;
-        const int64_t ra = (int64_t)(z - A.lo[2]) * A.n[1] + (y - A.lo[1]);
-        const int64_t rb = (int64_t)(z - pb.oz) * pb.by + (y - pb.oy);
-        const int pB = fine ? pf : pc;
-        // compact row runs: one 8-byte record per row and side
-        const RowRun wa = rr[A.rr[fine] + ra], wb = rr[B.rr[pB] + rb];
-        if (wa.len == 0 || wb.len == 0) continue;
-        if (wa.len != kMultiRun && wb.len != kMultiRun) {
-          const int x0 = max((int)wa.x0, (int)wb.x0);
-          const int x1 = min((int)wa.x0 + wa.len, (int)wb.x0 + wb.len) - 1;
-          if (x0 <= x1) {
-            // fine points hold their seven wavelets contiguously
-            const int sc = fine ? 7 : 1;
-            ea[fine][lane] = A.cin + (fine ? A.n_c : 0) + sc * (wa.off + (x0 - wa.x0));
-            eb[fine][lane] = bc + (fine ? bnc : 0) + sc * (wb.off + (x0 - wb.x0));
-            el[fine][lane] = sc * (x1 - x0 + 1);
-          }
-          continue;
-        }
-        // a row with several runs on either side: merge the segment lists
-        int qa = rt[A.rt[fine] + ra];
-        const int qa1 = rt[A.rt[fine] + ra + 1];
-        int qb = rt[B.rt[pB] + rb];
-        const int qb1 = rt[B.rt[pB] + rb + 1];
-        bool first = true;
-        while (qa < qa1 && qb < qb1) {
-          const wvl_seg sa = seg[qa], sb = seg[qb];
-          const int x0 = max(sa.i1s, sb.i1s), x1 = min(sa.i1e, sb.i1e);
-          if (x0 <= x1) {
-            const int sc = fine ? 7 : 1;
-            const int64_t oa = A.cin + (fine ? A.n_c : 0) + sc * (sa.off + (x0 - sa.i1s));
-            const int64_t ob = bc + (fine ? bnc : 0) + sc * (sb.off + (x0 - sb.i1s));
-            if (first) {
-              ea[fine][lane] = oa;
-              eb[fine][lane] = ob;
-              el[fine][lane] = sc * (x1 - x0 + 1);
-              first = false;
-            } else {
-              acc += run_dot<T>(bra + oa, ket + ob, sc * (x1 - x0 + 1));
-            }
-          }
-          if (sa.i1e < sb.i1e) ++qa; else ++qb;
-        }
+      wa[fine] = wb[fine] = RowRun{0, 0, 0};
+      if (in) {
+        wa[fine] = rr[A.rr[fine] + ra];
+        wb[fine] = rr[B.rr[fine ? pf : pc] + rb];
       }
     }
-    __syncthreads();
-    // phase 2
+    // coarse, fine and second run, from the functions' first coefficients
+    int sa0[3] = {0, 0, 0}, sb0[3] = {0, 0, 0}, len[3] = {0, 0, 0};
+#pragma unroll
+    for (int fine = 0; fine < 2; ++fine) {
+      if (wa[fine].len == 0 || wb[fine].len == 0) continue;
+      // fine points hold their seven wavelets contiguously
+      const int sc = fine ? 7 : 1;
+      const int ba = fine ? (int)A.n_c : 0, bk = fine ? bnc : 0;
+      if (wa[fine].len != kMultiRun && wb[fine].len != kMultiRun) {
+        const int x0 = max((int)wa[fine].x0, (int)wb[fine].x0);
+        const int x1 = min((int)wa[fine].x0 + wa[fine].len, (int)wb[fine].x0 + wb[fine].len) - 1;
+        if (x0 <= x1) {
+          sa0[fine] = ba + sc * (wa[fine].off + (x0 - wa[fine].x0));
+          sb0[fine] = bk + sc * (wb[fine].off + (x0 - wb[fine].x0));
+          len[fine] = sc * (x1 - x0 + 1);
+        }
+        continue;
+      }
+      // a row with several runs on either side: merge the segment lists
+      int qa = rt[A.rt[fine] + ra];
+      const int qa1 = rt[A.rt[fine] + ra + 1];
+      int qb = rt[B.rt[fine ? pf : pc] + rb];
+      const int qb1 = rt[B.rt[fine ? pf : pc] + rb + 1];
+      while (qa < qa1 && qb < qb1) {
+        const wvl_seg sa = seg[qa], sb = seg[qb];
+        const int x0 = max(sa.i1s, sb.i1s), x1 = min(sa.i1e, sb.i1e);
+        if (x0 <= x1) {
+          const int oa = ba + sc * (sa.off + (x0 - sa.i1s));
+          const int ob = bk + sc * (sb.off + (x0 - sb.i1s));
+          const int n = sc * (x1 - x0 + 1);
+          if (len[fine] == 0) {
+            sa0[fine] = oa;
+            sb0[fine] = ob;
+            len[fine] = n;
+          } else if (len[2] == 0) {
+            sa0[2] = oa;
+            sb0[2] = ob;
+            len[2] = n;
+          } else {
+            acc += run_dot<T>(pbra + oa, pket + ob, n);
+          }
+        }
+        if (sa.i1e < sb.i1e) ++qa; else ++qb;
+      }
+    }
+    ea[lane] = sa0[0];
+    eb[lane] = sb0[0];
+    el[lane] = len[0];
+    wave_sync();
+    // phase 2, coarse runs
     const int nb = min(64, nrows - r0);
-    // each run (coarse, or fine with the seven wavelets of its points) is
-    // one contiguous stretch on both sides
-    for (int q = grp; q < nb; q += 4) {
+    constexpr int R = 4;   // rows under way
+    for (int q0 = grp; q0 < nb; q0 += 4 * R) {
+      T va[R], vk[R];
+      int l[R];
 #pragma unroll
-      for (int fine = 0; fine < 2; ++fine) {
-        const int l = el[fine][q];
-        const T* pa = bra + ea[fine][q];
-        const T* pk = ket + eb[fine][q];
-        // FP64: four positions of the lane loaded before they are added, in
-        // the order x, x + 16, x + 32, x + 48 (the order of the plain loop);
-        // FP32 runs faster with one (fewer requests in flight per CU)
-        constexpr int U = sizeof(T) == 8 ? 4 : 1;
-        for (int x = gl; x < l; x += 16 * U) {
-          T va[U], vk[U];
+      for (int u = 0; u < R; ++u) {
+        const int q = min(q0 + 4 * u, 63);
+        l[u] = q0 + 4 * u < nb ? el[q] : 0;
+        va[u] = vk[u] = T(0);
+        if (gl < l[u]) {
+          va[u] = pbra[ea[q] + gl];
+          vk[u] = pket[eb[q] + gl];
+        }
+      }
 #pragma unroll
-          for (int u = 0; u < U; ++u) {
-            const bool in = x + 16 * u < l;
-            va[u] = in ? pa[x + 16 * u] : T(0);
-            vk[u] = in ? pk[x + 16 * u] : T(0);
-          }
-#pragma unroll
-          for (int u = 0; u < U; ++u)
-            if (x + 16 * u < l) acc += (double)va[u] * (double)vk[u];
+      for (int u = 0; u < R; ++u) {
+        acc += (double)va[u] * (double)vk[u];
+        for (int x = gl + 16; x < l[u]; x += 16) {
+          const int q = q0 + 4 * u;
+          acc += (double)pbra[ea[q] + x] * (double)pket[eb[q] + x];
         }
       }
     }
-    __syncthreads();
+    // fine runs, then the second runs: the whole wave takes a run
+    fine_runs<T>(pbra, pket, sa0[1], sb0[1], len[1], acc);
+    fine_runs<T>(pbra, pket, sa0[2], sb0[2], len[2], acc);
+    wave_sync();
   }
   for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 64);
-  if (lane == 0) {
+  if (lane == 0) part[wv] = acc;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    acc = 0.0;
+    for (int w = 0; w < W; ++w) acc += part[w];
     val[k] = acc;
     if (mirror != nullptr && mirror[s] >= 0) val[mirror[s]] = acc;
   }
@@ -368,14 +437,6 @@ __global__ __launch_bounds__(64) void k_sparse_values(const SfDev* __restrict__ 
 // 2.7 (1.6 at the full FP64 matrix rate), the scans 2.5 and the values 1.0.
 // Tiles of 16 x 4 x 2 points (two blocks per CU) took 9.6 ms, chunks of 128
 // functions 9.4 (spilled registers).
-// orders a wave's LDS writes before its other lanes' reads (and the reads
-// before the next writes)
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // hash of a pair's functions: at most 128 in 2048 slots (function << 8 |
 // position), open addressing, so that one read settles most lookups
 constexpr int kDensLogSlots = 11, kDensSlots = 1 << kDensLogSlots;
@@ -1377,8 +1438,11 @@ static inline dim3 grid2(int64_t maxvol, int nsf) {
 
 // Loads the code objects of the kernels a captured step may launch.
 int preload_kernels() {
-  const void* fns[] = {(const void*)k_finalize, (const void*)k_sparse_values<float>,
-                       (const void*)k_sparse_values<double>, (const void*)k_update<float>,
+  const void* fns[] = {(const void*)k_finalize, (const void*)k_sparse_values<float, 2>,
+                       (const void*)k_sparse_values<float, 4>, (const void*)k_sparse_values<float, 8>,
+                       (const void*)k_sparse_values<double, 2>,
+                       (const void*)k_sparse_values<double, 4>,
+                       (const void*)k_sparse_values<double, 8>, (const void*)k_update<float>,
                        (const void*)k_update<double>, (const void*)k_sf_dot<float>,
                        (const void*)k_sf_dot<double>, (const void*)k_dens_tile<float>,
                        (const void*)k_dens_tile<double>, (const void*)k_grad_rows<float>,
@@ -1446,17 +1510,33 @@ int launch_pattern(void* stream, const SfDev* sf, const wvl_seg* seg, const int3
 int launch_sparse_values(int f64, void* stream, const SfDev* sf, const wvl_seg* seg,
                          const int32_t* rt, const RowRun* rr, int ket_out, const void* bra,
                          const void* ket, const int32_t* row, const int32_t* col,
-                         const int32_t* order, const int32_t* mirror, int64_t nnz, double* val) {
+                         const int32_t* order, const int32_t* mirror, int64_t nnz, int64_t pairs,
+                         double* val) {
   if (nnz == 0) return 0;
   const unsigned nblk = (unsigned)(8 * ((nnz + 7) / 8));
+  auto go = [&](auto kernel, int w, auto t) {
+    using T = decltype(t);
+    hipLaunchKernelGGL(kernel, dim3(nblk), dim3(64 * w), 0, (hipStream_t)stream, sf, seg, rt, rr,
+                       ket_out, (const T*)bra, (const T*)ket, row, col, order, mirror, nnz, val);
+  };
+  // Waves per pair: the chip holds 8,192 waves.  With fewer pairs than that
+  // one wave's chain of loads is the time, so a pair's rows are dealt to more:
+  // S of 56 functions (2,516 H entries, FP32) takes 139 us with one wave, 82
+  // with two, 51 with four, 34 with eight; 120 functions (12,949) 153 / 87 /
+  // 69 / 76, H 346 / 296 / 277 / 341.  With many pairs the waves of a pair read
+  // the same lines together: FP64 H of 1,000 functions (303,083) 5.53 / 5.28 /
+  // 5.31 / 6.95 ms, but FP32 of 4,000 7.84 / 8.02 / 8.87 / 13.97.  The
+  // line is drawn on the entries of the pattern, not on the pairs summed, so
+  // that S has the same bits however it is called.
+  const int w = pairs <= 4096 ? 8 : pairs <= 32768 ? 4 : 2;
   if (f64)
-    hipLaunchKernelGGL(k_sparse_values<double>, dim3(nblk), dim3(64), 0, (hipStream_t)stream, sf,
-                       seg, rt, rr, ket_out, (const double*)bra, (const double*)ket, row, col,
-                       order, mirror, nnz, val);
+    w == 8   ? go(k_sparse_values<double, 8>, w, 0.0)
+    : w == 4 ? go(k_sparse_values<double, 4>, w, 0.0)
+             : go(k_sparse_values<double, 2>, w, 0.0);
   else
-    hipLaunchKernelGGL(k_sparse_values<float>, dim3(nblk), dim3(64), 0, (hipStream_t)stream, sf,
-                       seg, rt, rr, ket_out, (const float*)bra, (const float*)ket, row, col,
-                       order, mirror, nnz, val);
+    w == 8   ? go(k_sparse_values<float, 8>, w, 0.0f)
+    : w == 4 ? go(k_sparse_values<float, 4>, w, 0.0f)
+             : go(k_sparse_values<float, 2>, w, 0.0f);
   return (int)hipGetLastError();
 }
 
