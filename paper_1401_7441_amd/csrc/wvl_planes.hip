@@ -639,7 +639,7 @@ __global__ __launch_bounds__(256) void k_col_tile(const SfDev* __restrict__ sfs,
 // SEG outputs per lane, i' = i0 + 14 .. i0 + 13 + SEG, of both channels:
 //   r_a = fac sum_j sum_b K_ab[j] x_b(i' + j)
 // from the LDS column x_b(i) = S[lx + i st + b D], 0 <= i < NA, zero
-// elsewhere (S[0] and S[D] hold zeros); i0 is the same in all lanes of a wave.
+// elsewhere (S[0] and S[D] hold zeros); the lanes of a wave have i0 = ia .. ib.
 // The taps run in the outer loop and a ring of inputs slides with them, so
 // each tap is moved into scalar registers once for SEG outputs; the two
 // channels of a point are one LDS read, issued two taps ahead, and pairs of
@@ -647,8 +647,8 @@ __global__ __launch_bounds__(256) void k_col_tile(const SfDev* __restrict__ sfs,
 // FP32: the scaling channel (exact as doubles) and the centre taps are summed
 // in double with FP64 taps, the wavelet channel's other taps in FP32.
 template <typename T, int SEG, int D>
-__device__ __forceinline__ void kin_taps(const T* S, int lx, int st, int i0, int NA, double fac,
-                                         double (&r0)[SEG], double (&r1)[SEG]) {
+__device__ __forceinline__ void kin_taps(const T* S, int lx, int st, int i0, int ia, int ib, int NA,
+                                         double fac, double (&r0)[SEG], double (&r1)[SEG]) {
   constexpr int GT = 2, NG = (29 + GT - 1) / GT, RS = SEG + GT;
   double x0[RS], s0[SEG], s1[SEG];
   T x1[RS], w0[SEG], w1[SEG], n0[GT], n1[GT];
@@ -678,7 +678,7 @@ __device__ __forceinline__ void kin_taps(const T* S, int lx, int st, int i0, int
 #pragma unroll
       for (int k = 0; k < GT; ++k) fetch(n0[k], n1[k]);
     }
-    if (i0 + GT * gr + GT + SEG - 2 >= 0 && i0 + GT * gr < NA) {   // not only zeros
+    if (ib + GT * gr + GT + SEG - 2 >= 0 && ia + GT * gr < NA) {   // not only zeros
 #pragma unroll
       for (int t = GT * gr; t < GT * gr + GT; ++t) {
         if (t >= 29) continue;
@@ -763,7 +763,7 @@ __global__ __launch_bounds__(kPlaneThreads, sizeof(T) == 4 ? 4 : 2) void k_kin_s
     const int lx = 4 + 4 * x + 2 * a1, st = kin_row(N0);
     double r0[8], r1[8];
     const int ip = 8 * sg - e;   // first output
-    kin_taps<T, 8, 1>(S, lx, st, ip - 14, N2, fac, r0, r1);
+    kin_taps<T, 8, 1>(S, lx, st, ip - 14, ip - 14, ip - 14, N2, fac, r0, r1);
     if (!act) continue;
     const uint32_t o0 = (uint32_t)((a1 + 2 * a2) * ocomp + (8 * sg * N1 + y) * N0 + x) * SZ;
     const uint32_t o1 = o0 + 4u * (uint32_t)ocomp * SZ;
@@ -937,16 +937,24 @@ __global__ __launch_bounds__(back_threads<T>(), 4) void k_back_plane(
     load_rows<T, 4>(N1, 4 * a3, 2, sf, seg, rt, rr, psi, z * N1, 1,
                     [&](int j, int x, const T* v) { put_kin(Q, N0, j, x, v); });
     __syncthreads();
-    // x part: the rows (y, a2) of the strip inside the box x 8 outputs x' per wave
+    // x part: an item is a row (y, a2) of the strip inside the box and 8 outputs
+    // x'.  FP32: the waves take 64 consecutive items, so that the usual 48 rows
+    // x 5 segments are one round of four waves (two before: 4.02 -> 3.82 ms for
+    // 700 functions); FP64, with eight waves, a segment each (items of several
+    // segments cost registers: 8.24 -> 8.51 ms for 1,000).
     const int ya = max(0, s0 - e), nyb = max(0, min(N1, s0 + ns - e) - ya);
     const int nsx = (O0 + 7) >> 3;
-    for (int job = wave; job < nsx; job += NW) {
-      const bool act = lane < 2 * nyb;
-      const int a2 = lane & 1, y = ya + (act ? lane >> 1 : 0);
-      const int lx = 4 + min(y, N1 - 1) * kin_row(N0) + a2;
+    const int px = sizeof(T) == 4 ? 2 * nyb : nyb > 0 ? 64 : 0;   // items per segment
+    for (int it = 64 * wave; it < nsx * px; it += 64 * NW) {
+      const int ca = it / px, cb = sizeof(T) == 4 ? min(it + 63, nsx * px - 1) / px : ca;
+      const int item = it + lane, job = sizeof(T) == 4 ? min(item / px, nsx - 1) : ca;
+      const bool act = item - job * px < 2 * nyb;
+      const int row = act ? item - job * px : 0;
+      const int a2 = row & 1, y = ya + (row >> 1);
+      const int lx = 4 + y * kin_row(N0) + a2;
       double r0[8], r1[8];
       const int ip = 8 * job - e;
-      kin_taps<T, 8, 2>(Q, lx, 4, ip - 14, N0, fac, r0, r1);
+      kin_taps<T, 8, 2>(Q, lx, 4, ip - 14, 8 * ca - e - 14, 8 * cb - e - 14, N0, fac, r0, r1);
       if (!act) continue;
       T* const o0 = OUT + 2 * a2 * och + (y + e - s0) * ldo + 8 * job;
 #pragma unroll
@@ -963,14 +971,16 @@ __global__ __launch_bounds__(back_threads<T>(), 4) void k_back_plane(
     __syncthreads();
   }
   if (kin_on) {
-    // y + z parts: 64 columns (x, a1) x 8 outputs y' per wave
-    const int ngrp = (2 * N0 + 63) >> 6, ocomp = O2 * N1 * N0;
+    // y + z parts: items of a column (x, a1) and 8 outputs y'
+    const int nsy = (ns + 7) >> 3, ocomp = O2 * N1 * N0;
     const Buf<T> oz(ws + w.oz, 8ll * ocomp);
-    for (int job = wave; job < (kStrip / 8) * ngrp; job += NW) {
-      const int sg = job % (kStrip / 8), ci = (job / (kStrip / 8)) * 64 + lane;
-      if (8 * sg >= ns) continue;
-      const bool act = ci < 2 * N0;
-      const int a1 = ci & 1, x = act ? ci >> 1 : 0;
+    const int py = sizeof(T) == 4 ? 2 * N0 : (2 * N0 + 63) & ~63;   // items per segment
+    for (int it = 64 * wave; it < nsy * py; it += 64 * NW) {
+      const int ca = it / py, cb = sizeof(T) == 4 ? min(it + 63, nsy * py - 1) / py : ca;
+      const int item = it + lane, sg = sizeof(T) == 4 ? min(item / py, nsy - 1) : ca;
+      const bool act = item - sg * py < 2 * N0;
+      const int ci = act ? item - sg * py : 0;
+      const int a1 = ci & 1, x = ci >> 1;
       const int ip = s0 + 8 * sg - e;
       const int zb = (4 * a3 + a1) * ocomp + (zp * N1 + ip) * N0 + x;   // oz of output 0, a2 = 0
       T z0[8], z1[8];
@@ -983,7 +993,8 @@ __global__ __launch_bounds__(back_threads<T>(), 4) void k_back_plane(
       double r0[8], r1[8];
       const int lx = 4 + 4 * x + 2 * a1, st = kin_row(N0);
       if (kin) {
-        kin_taps<T, 8, 1>(Q, lx, st, ip - 14, N1, fac, r0, r1);
+        kin_taps<T, 8, 1>(Q, lx, st, ip - 14, s0 + 8 * ca - e - 14, s0 + 8 * cb - e - 14, N1, fac, r0,
+                          r1);
       } else {
 #pragma unroll
         for (int o = 0; o < 8; ++o) r0[o] = r1[o] = 0.0;
