@@ -1133,6 +1133,15 @@ static wvl_status apply_args(wvl_plan* P, wvl_dtype dt, uint32_t terms, const vo
 }
 
 // Enqueues the stages of chunk c on stream st.
+// Blocks of the up pass and the z part of the kinetic term that go in one
+// launch: as many as the chip holds at four per CU.  Both only read psi, so a
+// small call saves a launch and its latency: apply of 1 / 4 / 16 functions in
+// FP32 78 -> 69, 100 -> 90, 173 -> 168 us, FP64 62 -> 53, 100 -> 92, 265 -> 263
+// (1,664 blocks).  With more, blocks of one kind held back by the registers
+// and the LDS of the other cost more than the launch: FP64, 56 functions 831
+// -> 852 us, FP32, 60 of 16-48 points per axis 1.08 -> 1.21 ms.
+constexpr int64_t kUpKinBlocks = 1024;
+
 static wvl_status apply_chunk(wvl_plan* P, size_t c, int f64, uint32_t terms, const void* psi_c,
                               const void* pot, void* hpsi_c, double* e_kin, double* e_pot,
                               void* workspace, int accumulate, hipStream_t st,
@@ -1147,10 +1156,18 @@ static wvl_status apply_chunk(wvl_plan* P, size_t c, int f64, uint32_t terms, co
   const SfWork* wk = P->d_wk + ch.sf0;
   double* parts = (double*)((char*)workspace + align_bytes(P->lay.elems_span * sz));
   if (ch.plane[d]) {
-    if (pot_on) {
+    // the up pass and the z part of the kinetic term side by side in one launch
+    const bool side = pot_on && kin_on && (int64_t)ch.nsf * (ch.grid_up + ch.grid_ks) <= kUpKinBlocks;
+    if (side)
       WVL_LAUNCH(ctx, KK_UP_PLANE,
-                 launch_up_plane(f64, st, P->d_sf, P->d_seg, P->d_rt, P->d_rr, psi_c, wk, ch.nsf,
-                                 ch.grid_up, ch.up_both[d], (size_t)ch.lds_up[d], workspace));
+                 launch_up_kin(f64, st, P->d_sf, P->d_seg, P->d_rt, P->d_rr, psi_c, wk, ch.nsf,
+                               ch.grid_up, ch.grid_ks, ch.up_both[d],
+                               (size_t)std::max(ch.lds_up[d], ch.lds_ks[d]), workspace, fac, parts));
+    if (pot_on) {
+      if (!side)
+        WVL_LAUNCH(ctx, KK_UP_PLANE,
+                   launch_up_plane(f64, st, P->d_sf, P->d_seg, P->d_rt, P->d_rr, psi_c, wk, ch.nsf,
+                                   ch.grid_up, ch.up_both[d], (size_t)ch.lds_up[d], workspace));
       if (f64)
         WVL_LAUNCH(ctx, KK_COL_TILE,
                    launch_col_tile(st, P->d_sf, wk, ch.nsf, ch.grid_ct, workspace, pot, nf1, nf2,
@@ -1160,7 +1177,7 @@ static wvl_status apply_chunk(wvl_plan* P, size_t c, int f64, uint32_t terms, co
                    launch_pot_column(f64, st, P->d_sf, wk, ch.sf0, ch.nsf, ch.grid_b, workspace,
                                      pot, nf1, nf2, parts, conf, 0.5 * ctx->grid.h, 1));
     }
-    if (kin_on)
+    if (kin_on && !side)
       WVL_LAUNCH(ctx, KK_KIN_SLAB,
                  launch_kin_slab(f64, st, P->d_sf, P->d_seg, P->d_rt, P->d_rr, psi_c, wk, ch.nsf,
                                  ch.grid_ks, (size_t)ch.lds_ks[d], workspace, fac, parts));

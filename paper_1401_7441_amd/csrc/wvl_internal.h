@@ -202,6 +202,10 @@ int launch_col_tile(void* stream, const SfDev* sf, const SfWork* wk, int nsf, in
                     double hh);
 int launch_syn_tile(void* stream, const SfDev* sf, const SfWork* wk, int nsf, int gridx, void* ws,
                     const int64_t* fine_off, void* fine);
+// both in one launch (lds: the larger of the two)
+int launch_up_kin(int f64, void* stream, const SfDev* sf, const wvl_seg* seg, const int32_t* rt,
+                  const RowRun* rr, const void* psi, const SfWork* wk, int nsf, int nup, int nkin,
+                  int both, size_t lds, void* ws, double fac, double* kpart);
 int launch_kin_slab(int f64, void* stream, const SfDev* sf, const wvl_seg* seg, const int32_t* rt,
                     const RowRun* rr, const void* psi, const SfWork* wk, int nsf, int gridx,
                     size_t lds, void* ws, double fac, double* kpart);

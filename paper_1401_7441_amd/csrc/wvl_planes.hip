@@ -18,7 +18,7 @@
 // instead of nine: 17 instead of 38 GB of traffic for 1,000 functions of radius
 // 5-7 bohr in FP32 (13.0 -> 8.1 ms; FP64 25.2 -> 14.7 ms), and one launch of a
 // single function waits for four short kernels instead of nine serial chains
-// (FP64 442 -> 62 us).
+// (FP64 442 -> 52 us).
 //
 // The down passes, and in FP64 the up passes, are products with banded Toeplitz
 // matrices and run on the matrix cores (16x16x4): an output tile is 16 fine
@@ -244,19 +244,19 @@ __device__ __forceinline__ void load_rows(int nrows, int cb, int cs, const SfDev
 // LDS strides: rows of X 4 (mod 8) apart and rows of Y 4 (mod 16) put the 16
 // rows x 4 points of an operand on distinct banks; the channels of Y are
 // 16 (mod 32) apart, so that the two channels of a y operand are too.
-__global__ __launch_bounds__(256) void k_up_plane(const SfDev* __restrict__ sfs,
-                                                  const wvl_seg* __restrict__ seg,
-                                                  const int32_t* __restrict__ rt,
-                                                  const RowRun* __restrict__ rr,
-                                                  const double* __restrict__ psi,
-                                                  const SfWork* __restrict__ wk,
-                                                  double* __restrict__ ws, int both) {
+__device__ __forceinline__ void up_plane(int bx, const SfDev* __restrict__ sfs,
+                                         const wvl_seg* __restrict__ seg,
+                                         const int32_t* __restrict__ rt,
+                                         const RowRun* __restrict__ rr,
+                                         const double* __restrict__ psi,
+                                         const SfWork* __restrict__ wk, double* __restrict__ ws,
+                                         int both) {
   using T = double;
   extern __shared__ __align__(32) unsigned char smem_raw[];
   const SfWork& w = wk[blockIdx.y];
   const SfDev& sf = sfs[w.id];
   const int N0 = sf.n[0], N1 = sf.n[1], N2 = sf.n[2];
-  const int z = blockIdx.x >> 1, a3 = blockIdx.x & 1;
+  const int z = bx >> 1, a3 = bx & 1;
   if (z >= N2) return;   // uniform over the block
   const int R1 = 2 * N1 + 29, P0 = pad16(2 * N0 + 29);
   const int ldx = plane_ldx(N0), ldy = P0 + 4, ych = plane_ych(N0, N1);
@@ -431,15 +431,17 @@ __device__ __forceinline__ void up_item(const float* S, int lx, int st, int q0, 
   }
 }
 
-__global__ __launch_bounds__(256, 4) void k_up_plane_valu(
-    const SfDev* __restrict__ sfs, const wvl_seg* __restrict__ seg, const int32_t* __restrict__ rt,
-    const RowRun* __restrict__ rr, const float* __restrict__ psi, const SfWork* __restrict__ wk,
-    float* __restrict__ ws) {
+__device__ __forceinline__ void up_plane(int bx, const SfDev* __restrict__ sfs,
+                                         const wvl_seg* __restrict__ seg,
+                                         const int32_t* __restrict__ rt,
+                                         const RowRun* __restrict__ rr,
+                                         const float* __restrict__ psi,
+                                         const SfWork* __restrict__ wk, float* __restrict__ ws, int) {
   extern __shared__ __align__(32) unsigned char smem_raw[];
   const SfWork& w = wk[blockIdx.y];
   const SfDev& sf = sfs[w.id];
   const int N0 = sf.n[0], N1 = sf.n[1], N2 = sf.n[2];
-  const int z = blockIdx.x >> 1, a3 = blockIdx.x & 1;
+  const int z = bx >> 1, a3 = bx & 1;
   if (z >= N2) return;   // uniform over the block
   const int R0 = 2 * N0 + 29, R1 = 2 * N1 + 29, P0 = pad16(R0);
   const int ldx = 2 * N0 + 1, ldy = 2 * R0 + 1;
@@ -733,15 +735,17 @@ __device__ __forceinline__ void put_kin(T* S, int n0, int j, int x, const T* v) 
 // The x-z slab of four components -> OZ[c][z'][y][x]; a wave takes 64 columns
 // (x, a1) and 8 outputs z'.
 template <typename T>
-__global__ __launch_bounds__(kPlaneThreads, sizeof(T) == 4 ? 4 : 2) void k_kin_slab(
-    const SfDev* __restrict__ sfs, const wvl_seg* __restrict__ seg,
-    const int32_t* __restrict__ rt, const RowRun* __restrict__ rr, const T* __restrict__ psi,
-    const SfWork* __restrict__ wk, T* __restrict__ ws, double fac, double* __restrict__ kpart) {
+__device__ __forceinline__ void kin_slab(int bx, const SfDev* __restrict__ sfs,
+                                         const wvl_seg* __restrict__ seg,
+                                         const int32_t* __restrict__ rt,
+                                         const RowRun* __restrict__ rr, const T* __restrict__ psi,
+                                         const SfWork* __restrict__ wk, T* __restrict__ ws,
+                                         double fac, double* __restrict__ kpart) {
   extern __shared__ __align__(32) unsigned char smem_raw[];
   const SfWork& w = wk[blockIdx.y];
   const SfDev& sf = sfs[w.id];
   const int N0 = sf.n[0], N1 = sf.n[1], N2 = sf.n[2], e = sf.ext;
-  const int y = blockIdx.x >> 1, a2 = blockIdx.x & 1;
+  const int y = bx >> 1, a2 = bx & 1;
   if (y >= N1) return;   // uniform over the block
   const int O2 = N2 + 2 * e;
   T* const S = reinterpret_cast<T*>(smem_raw);
@@ -779,7 +783,44 @@ __global__ __launch_bounds__(kPlaneThreads, sizeof(T) == 4 ? 4 : 2) void k_kin_s
     }
   }
   const double b = plane_block_sum(eacc);
-  if (threadIdx.x == 0) kpart[w.kpart + 2 * N2 * plane_strips(N1 + 2 * e) + blockIdx.x] = b;
+  if (threadIdx.x == 0) kpart[w.kpart + 2 * N2 * plane_strips(N1 + 2 * e) + bx] = b;
+}
+
+__global__ __launch_bounds__(256) void k_up_plane(
+    const SfDev* __restrict__ sfs, const wvl_seg* __restrict__ seg, const int32_t* __restrict__ rt,
+    const RowRun* __restrict__ rr, const double* __restrict__ psi, const SfWork* __restrict__ wk,
+    double* __restrict__ ws, int both) {
+  up_plane(blockIdx.x, sfs, seg, rt, rr, psi, wk, ws, both);
+}
+__global__ __launch_bounds__(256, 4) void k_up_plane_valu(
+    const SfDev* __restrict__ sfs, const wvl_seg* __restrict__ seg, const int32_t* __restrict__ rt,
+    const RowRun* __restrict__ rr, const float* __restrict__ psi, const SfWork* __restrict__ wk,
+    float* __restrict__ ws) {
+  up_plane(blockIdx.x, sfs, seg, rt, rr, psi, wk, ws, 1);
+}
+template <typename T>
+__global__ __launch_bounds__(kPlaneThreads, sizeof(T) == 4 ? 4 : 2) void k_kin_slab(
+    const SfDev* __restrict__ sfs, const wvl_seg* __restrict__ seg,
+    const int32_t* __restrict__ rt, const RowRun* __restrict__ rr, const T* __restrict__ psi,
+    const SfWork* __restrict__ wk, T* __restrict__ ws, double fac, double* __restrict__ kpart) {
+  kin_slab<T>(blockIdx.x, sfs, seg, rt, rr, psi, wk, ws, fac, kpart);
+}
+
+// ---------------------------------------------------------------------------
+// k_up_kin: both of the above, which only read psi, in one launch
+// ---------------------------------------------------------------------------
+// Blocks 0 .. nup - 1 of a function are those of the up pass, the others those
+// of the z part.  For calls that leave the chip idle (see kUpKinBlocks).
+template <typename T>
+__global__ __launch_bounds__(kPlaneThreads, sizeof(T) == 4 ? 4 : 2) void k_up_kin(
+    const SfDev* __restrict__ sfs, const wvl_seg* __restrict__ seg,
+    const int32_t* __restrict__ rt, const RowRun* __restrict__ rr, const T* __restrict__ psi,
+    const SfWork* __restrict__ wk, T* __restrict__ ws, int nup, int both, double fac,
+    double* __restrict__ kpart) {
+  if ((int)blockIdx.x < nup)
+    up_plane(blockIdx.x, sfs, seg, rt, rr, psi, wk, ws, both);
+  else
+    kin_slab<T>(blockIdx.x - nup, sfs, seg, rt, rr, psi, wk, ws, fac, kpart);
 }
 
 // ---------------------------------------------------------------------------
@@ -1088,6 +1129,7 @@ int preload_plane_kernels() {
   const void* fns[] = {(const void*)k_up_plane_valu,          (const void*)k_up_plane,
                        (const void*)k_col_tile<false>,        (const void*)k_col_tile<true>,
                        (const void*)k_kin_slab<float>,        (const void*)k_kin_slab<double>,
+                       (const void*)k_up_kin<float>,          (const void*)k_up_kin<double>,
                        (const void*)k_back_plane<float>,      (const void*)k_back_plane<double>,
                        (const void*)k_plane_energies};
   for (const void* f : fns) {
@@ -1111,6 +1153,22 @@ int launch_up_plane(int f64, void* stream, const SfDev* sf, const wvl_seg* seg, 
   else
     hipLaunchKernelGGL(k_up_plane_valu, g, dim3(256), lds, (hipStream_t)stream, sf, seg, rt, rr,
                        (const float*)psi, wk, (float*)ws);
+  return (int)hipGetLastError();
+}
+
+int launch_up_kin(int f64, void* stream, const SfDev* sf, const wvl_seg* seg, const int32_t* rt,
+                  const RowRun* rr, const void* psi, const SfWork* wk, int nsf, int nup, int nkin,
+                  int both, size_t lds, void* ws, double fac, double* kpart) {
+  if (nsf == 0) return 0;
+  const dim3 g((unsigned)(nup + nkin), (unsigned)nsf);
+  hipError_t e = f64 ? allow_lds(k_up_kin<double>, lds) : allow_lds(k_up_kin<float>, lds);
+  if (e != hipSuccess) return (int)e;
+  if (f64)
+    hipLaunchKernelGGL(k_up_kin<double>, g, dim3(kPlaneThreads), lds, (hipStream_t)stream, sf, seg,
+                       rt, rr, (const double*)psi, wk, (double*)ws, nup, both, fac, kpart);
+  else
+    hipLaunchKernelGGL(k_up_kin<float>, g, dim3(kPlaneThreads), lds, (hipStream_t)stream, sf, seg,
+                       rt, rr, (const float*)psi, wk, (float*)ws, nup, both, fac, kpart);
   return (int)hipGetLastError();
 }
 

@@ -58,7 +58,7 @@ def kind_of(name: str):
         return "uncompress"
     if base == "scatter":
         return "compress"
-    if base == "up_plane_valu":  # the FP32 form
+    if base in ("up_plane_valu", "up_kin"):  # the FP32 form; with the kinetic z part
         return "up_plane"
     if base == "plane_energies":
         return "finalize"

@@ -61,3 +61,22 @@ def test_plane_kernels(dims, ext):
     W.set_schedule(plan, 1, 1)
     _, _, b, _, eb = case.run(torch.float32, terms=W.POT, plan=plan)
     assert np.array_equal(a, b) and np.array_equal(ea, eb)
+
+
+@pytest.mark.parametrize("n", [8, 9])
+def test_up_and_kinetic_in_one_launch(n):
+    """Eight of these boxes have 944 blocks of the up pass and the z part (one
+    launch, at most 1,024), nine have 1,062 (two launches)."""
+    one = _case((5, 7, 52), 8)
+    g = one.g
+    g.centers = np.repeat(g.centers, n, axis=0)
+    g.envelope_sigma = np.full(n, 100.0)
+    case = Case(g, [one.lrs[0]] * n)
+    _print(f"case: {n} boxes (5, 7, 52)")
+    for dtype, tol in ((torch.float64, 1e-12), (torch.float32, 1e-5)):
+        _, _, out, ek, ep = case.run(dtype)
+        for k in (0, n - 1):
+            ref, rk, rp = case.oracle(k)
+            assert rel_err(out[case.out_slice(k)], ref) < tol
+            assert abs(ek[k] - rk) <= tol * max(1.0, abs(rk))
+            assert abs(ep[k] - rp) <= tol * max(1.0, abs(rp))
