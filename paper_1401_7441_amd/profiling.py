@@ -89,7 +89,8 @@ def stats_markdown(trace_csv: str, command: str) -> str:
             k = "sparse_s" if nsparse % 2 == 0 else "sparse_h"
             nsparse += 1
         d = (int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e6
-        per.setdefault(k, {"name": re.sub(r"\(.*", "", r["Kernel_Name"]).replace("void ", ""),
+        per.setdefault(k, {"name": re.sub(r"\(.*", "", r["Kernel_Name"].replace(
+            "(anonymous namespace)::", "")).replace("void ", ""),
                            "ms": []})["ms"].append(d)
         cfg.setdefault(k, {}).setdefault((r.get("Grid_Size_X"), r.get("Grid_Size_Y")),
                                          []).append(d)
