@@ -1270,6 +1270,13 @@ wvl_status wvl::plan_error(wvl_plan* P, wvl_status st, const char* msg) {
   return fail(P ? P->ctx : nullptr, st, "%s", msg);
 }
 
+int wvl::preload_all() {
+  int e = preload_kernels();
+  if (e == 0) e = preload_fused_kernels();
+  if (e == 0) e = preload_plane_kernels();
+  return e;
+}
+
 void* wvl::plan_stream(const wvl_plan* P) { return P ? (void*)P->ctx->stream : nullptr; }
 
 extern "C" {
@@ -2048,10 +2055,7 @@ static wvl_status capture_step(wvl_plan* P, wvl_dtype dt, uint32_t terms, const 
   const size_t nch = P->lay.chunks.size();
   // kernels are loaded lazily on first use; a load (which also uploads the
   // constant filter tables) must not happen inside the capture
-  int pe = preload_kernels();
-  if (pe == 0) pe = preload_fused_kernels();
-  if (pe == 0) pe = preload_plane_kernels();
-  if (pe != 0)
+  if (const int pe = preload_all(); pe != 0)
     return hip_fail(ctx, "graph capture", "kernel preload (hipFuncGetAttributes)",
                     (hipError_t)pe);
   const size_t nbr = P->lay.disjoint ? std::min<size_t>(nch, 4) : 0;

@@ -35,8 +35,7 @@ hipError_t scratch_on(int dev, void** out) {
     if (e != hipSuccess) return e;
     if (cur != dev && (e = hipSetDevice(dev)) != hipSuccess) return e;
     // the kernels' code objects are loaded here, never inside a capture
-    int pe = wvl::preload_kernels();
-    if (pe == 0) pe = wvl::preload_fused_kernels();
+    const int pe = wvl::preload_all();
     void* p = nullptr;
     e = pe != 0 ? (hipError_t)pe : hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
     if (cur != dev) {
