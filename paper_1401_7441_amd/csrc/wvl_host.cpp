@@ -1062,6 +1062,10 @@ wvl_status wvl_plan_create(wvl_ctx* ctx, int32_t nsf, const wvl_locreg* lr, cons
     wvl_plan_destroy(P);
     return hip_fail(ctx, "plan upload", "hipStreamSynchronize", e);
   }
+  if (const int pe = preload_all(); pe != 0) {
+    wvl_plan_destroy(P);
+    return hip_fail(ctx, "plan creation", "kernel preload", (hipError_t)pe);
+  }
   if (workspace_bytes) *workspace_bytes = (size_t)best_f64;
   *plan_out = P;
   return WVL_OK;

@@ -152,8 +152,9 @@ wvl_status plan_error(wvl_plan* plan, wvl_status st, const char* msg);
 // the HIP stream of the plan's context
 void* plan_stream(const wvl_plan* plan);
 
-// Loads every kernel's code object on the current device (hipError_t as int):
-// before a stream capture, or anything else that must not load one
+// Loads every kernel's code object on the current device and sets the kernels'
+// LDS limits there (hipError_t as int): at plan creation, and before a stream
+// capture or anything else that must not load one
 int preload_all();             // wvl_host.cpp: all of the following
 int preload_kernels();         // wvl_kernels.hip
 int preload_fused_kernels();   // wvl_fused.hip

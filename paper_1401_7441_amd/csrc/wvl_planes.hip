@@ -1112,30 +1112,32 @@ __global__ __launch_bounds__(256) void k_plane_energies(const SfWork* __restrict
   }
 }
 
-// more than 64 KiB of dynamic LDS has to be asked for
-template <typename F>
-hipError_t allow_lds(F f, size_t lds) {
-  if (lds <= 64 * 1024) return hipSuccess;
-  return hipFuncSetAttribute((const void*)f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-}
-
 }  // namespace
 
 // ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
 
+// More than 64 KiB of dynamic LDS has to be asked for.  The limit belongs to the
+// kernel on a device, not to a launch: it is set here to the most that any plan
+// may use, and never to a launch's own size, which a launch of another thread
+// (or a captured one) may exceed.
 int preload_plane_kernels() {
-  const void* fns[] = {(const void*)k_up_plane_valu,          (const void*)k_up_plane,
-                       (const void*)k_col_tile<false>,        (const void*)k_col_tile<true>,
-                       (const void*)k_kin_slab<float>,        (const void*)k_kin_slab<double>,
-                       (const void*)k_up_kin<float>,          (const void*)k_up_kin<double>,
-                       (const void*)k_back_plane<float>,      (const void*)k_back_plane<double>,
+  const void* fns[] = {(const void*)k_col_tile<false>, (const void*)k_col_tile<true>,
                        (const void*)k_plane_energies};
-  for (const void* f : fns) {
-    hipFuncAttributes a;
-    const hipError_t e = hipFuncGetAttributes(&a, f);
-    if (e != hipSuccess) return (int)e;
+  const void* lds[] = {(const void*)k_up_plane_valu,     (const void*)k_up_plane,
+                       (const void*)k_kin_slab<float>,   (const void*)k_kin_slab<double>,
+                       (const void*)k_up_kin<float>,     (const void*)k_up_kin<double>,
+                       (const void*)k_back_plane<float>, (const void*)k_back_plane<double>};
+  hipError_t e = hipSuccess;
+  hipFuncAttributes a;
+  for (const void* f : fns)
+    if ((e = hipFuncGetAttributes(&a, f)) != hipSuccess) return (int)e;
+  for (const void* f : lds) {
+    if ((e = hipFuncGetAttributes(&a, f)) != hipSuccess) return (int)e;
+    if ((e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                 (int)kPlaneLds)) != hipSuccess)
+      return (int)e;
   }
   return 0;
 }
@@ -1145,8 +1147,6 @@ int launch_up_plane(int f64, void* stream, const SfDev* sf, const wvl_seg* seg, 
                     int both, size_t lds, void* ws) {
   if (nsf == 0 || gridx == 0) return 0;
   const dim3 g((unsigned)gridx, (unsigned)nsf);
-  hipError_t e = f64 ? allow_lds(k_up_plane, lds) : allow_lds(k_up_plane_valu, lds);
-  if (e != hipSuccess) return (int)e;
   if (f64)
     hipLaunchKernelGGL(k_up_plane, g, dim3(256), lds, (hipStream_t)stream, sf, seg, rt, rr,
                        (const double*)psi, wk, (double*)ws, both);
@@ -1161,8 +1161,6 @@ int launch_up_kin(int f64, void* stream, const SfDev* sf, const wvl_seg* seg, co
                   int both, size_t lds, void* ws, double fac, double* kpart) {
   if (nsf == 0) return 0;
   const dim3 g((unsigned)(nup + nkin), (unsigned)nsf);
-  hipError_t e = f64 ? allow_lds(k_up_kin<double>, lds) : allow_lds(k_up_kin<float>, lds);
-  if (e != hipSuccess) return (int)e;
   if (f64)
     hipLaunchKernelGGL(k_up_kin<double>, g, dim3(kPlaneThreads), lds, (hipStream_t)stream, sf, seg,
                        rt, rr, (const double*)psi, wk, (double*)ws, nup, both, fac, kpart);
@@ -1196,8 +1194,6 @@ int launch_kin_slab(int f64, void* stream, const SfDev* sf, const wvl_seg* seg, 
                     size_t lds, void* ws, double fac, double* kpart) {
   if (nsf == 0 || gridx == 0) return 0;
   const dim3 g((unsigned)gridx, (unsigned)nsf);
-  hipError_t e = f64 ? allow_lds(k_kin_slab<double>, lds) : allow_lds(k_kin_slab<float>, lds);
-  if (e != hipSuccess) return (int)e;
   if (f64)
     hipLaunchKernelGGL(k_kin_slab<double>, g, dim3(kPlaneThreads), lds, (hipStream_t)stream, sf,
                        seg, rt, rr, (const double*)psi, wk, (double*)ws, fac, kpart);
@@ -1213,8 +1209,6 @@ int launch_back_plane(int f64, void* stream, const SfDev* sf, const wvl_seg* seg
                       int kin_on, int accumulate, double fac, double* kpart) {
   if (nsf == 0 || gridx == 0) return 0;
   const dim3 g((unsigned)gridx, (unsigned)nsf);
-  hipError_t e = f64 ? allow_lds(k_back_plane<double>, lds) : allow_lds(k_back_plane<float>, lds);
-  if (e != hipSuccess) return (int)e;
   if (f64)
     hipLaunchKernelGGL(k_back_plane<double>, g, dim3(back_threads<double>()), lds, (hipStream_t)stream, sf,
                        seg, rt, rr, (const double*)psi, wk, (const double*)ws, (double*)out,
