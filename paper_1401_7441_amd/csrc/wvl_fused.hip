@@ -354,7 +354,7 @@ __global__ __launch_bounds__(256) void k_up_z(const SfDev* __restrict__ sfs,
   if (col >= plane) return;
   // (padded: the plane kernels' G1 rows)
   const int64_t ld = padded ? pad16(R0) : R0, gplane = R1 * ld;
-  const T* in0 = ws + w.g1 + (col / R0) * ld + col % R0;   // a3 = 0
+  const T* in0 = ws + (padded ? w.p1 : w.g1) + (col / R0) * ld + col % R0;   // a3 = 0
   const T* in1 = in0 + (int64_t)N2 * gplane;                // a3 = 1
   T* out = fine + fine_off[w.id] + col;
   constexpr int PF = pf_up_y<T>();   // the same stream shape as k_up_y
@@ -421,9 +421,9 @@ __global__ __launch_bounds__(256) void k_pot_column(const SfDev* __restrict__ sf
     const int px = (int)(col % R0), py = (int)(col / R0);
     // G1 and G2 rows R0 apart (padded, the plane kernels': pad16(R0))
     const int64_t ld = padded ? pad16(R0) : R0, pst = R1 * ld;
-    const T* in0 = ws + w.g1 + py * ld + px;
+    const T* in0 = ws + (padded ? w.p1 : w.g1) + py * ld + px;
     const T* in1 = in0 + (int64_t)N2 * pst;
-    T* out0 = ws + w.g2 + py * ld + px;
+    T* out0 = ws + (padded ? w.p2 : w.g2) + py * ld + px;
     T* out1 = out0 + (int64_t)O2 * pst;
     const int64_t vstride = (int64_t)nf1 * nf2;
     // no potential array: V = 0 (the confinement alone)

@@ -248,7 +248,9 @@ struct wvl_plan {
   wvl_ctx* ctx = nullptr;
   int nsf = 0;
   std::vector<SfDev> h_sf;
-  std::vector<int32_t> order;         // processing position -> function index
+  // processing position -> function index: by kernel family and size, and (the
+  // layouts of the column kernels) by size alone
+  std::vector<int32_t> order[2];
   size_t max_ws = 0;                  // the caller's workspace bound (0: none)
   Layout lay;
   int64_t ws_cap[2] = {0, 0};         // workspace bytes reported (F32, F64)
@@ -712,17 +714,46 @@ void wvl_plan_destroy(wvl_plan* plan) {
 // bin counts the autotuner tries (the plan's workspace covers all of them)
 static const int kTuneBins[] = {1, 2, 3, 4, 6, 8};
 
-// workspace elements of one function's arrays; slim: the plane kernels' only
-static int64_t sf_elems(const SfDev& S, bool slim) {
-  const int64_t n0 = S.n[0], n1 = S.n[1], n2 = S.n[2], e = S.ext;
-  const int64_t r0 = 2 * n0 + 29, r1 = 2 * n1 + 29, p0 = pad16((int)r0);
-  const int64_t o0 = n0 + 2 * e, o1 = n1 + 2 * e, o2 = n2 + 2 * e;
-  const int64_t pl = align64(2 * n2 * p0 * r1) + align64(2 * o2 * p0 * r1) + align64(8 * o2 * n0 * n1);
-  if (slim) return pl;
-  return pl + 2 * align64(8 * n0 * n1 * n2) + align64(4 * o2 * r0 * qrow_stride((int)o1)) +
-         align64(8 * n2 * o0 * n1) + align64(8 * n2 * qrow_stride((int)o1) * n0) +
-         align64(4 * n2 * n1 * r0);
+// workspace elements of one function's arrays: those of the plane kernels, of
+// the column kernels, and of a function that takes the plane kernels in the
+// types of `bits` (one type only: both sets, in the same place)
+static int64_t plane_elems(const SfDev& S) {
+  const int64_t n0 = S.n[0], n1 = S.n[1], n2 = S.n[2], r1 = 2 * n1 + 29, o2 = n2 + 2 * S.ext;
+  const int64_t p0 = pad16((int)(2 * n0 + 29));
+  return align64(2 * n2 * p0 * r1) + align64(2 * o2 * p0 * r1) + align64(8 * o2 * n0 * n1);
 }
+static int64_t column_elems(const SfDev& S) {
+  const int64_t n0 = S.n[0], n1 = S.n[1], n2 = S.n[2], e = S.ext;
+  const int64_t r0 = 2 * n0 + 29, r1 = 2 * n1 + 29;
+  const int64_t o0 = n0 + 2 * e, o1 = n1 + 2 * e, o2 = n2 + 2 * e;
+  return 2 * align64(8 * n0 * n1 * n2) + align64(2 * n2 * r0 * r1) + align64(2 * o2 * r0 * r1) +
+         align64(4 * o2 * r0 * qrow_stride((int)o1)) + align64(8 * n2 * o0 * n1) +
+         align64(8 * n2 * qrow_stride((int)o1) * n0) +
+         align64(8 * o2 * n0 * n1) + align64(4 * n2 * n1 * r0);
+}
+static int64_t sf_elems(const SfDev& S, int bits) {
+  return bits == 3 ? plane_elems(S)
+         : bits == 0 ? column_elems(S) : std::max(plane_elems(S), column_elems(S));
+}
+
+// Energy partials (e_pot, e_kin) that functions need in the kernels they take;
+// a launch has the grids of the largest, so each slot count is the largest too
+struct PartSlots {
+  int64_t pot = 0, kx = 0, ky = 0, kz = 0, kpl = 0;
+  void add(const SfDev& S, int bits, bool zmfma) {
+    const int64_t r0 = 2 * S.n[0] + 29, r1 = 2 * S.n[1] + 29;
+    pot = std::max(pot, (r0 * r1 + 255) / 256);   // k_pot_column
+    if (bits & 2) pot = std::max(pot, (r1 * (pad16((int)r0) / 16) + 3) / 4);   // k_col_tile
+    if (bits != 3) {
+      kx = std::max<int64_t>(kx, kin_blocks(0, S.n[0], S.n[1], S.n[2]));
+      ky = std::max<int64_t>(ky, kin_blocks(1, S.n[0], S.n[1], S.n[2]));
+      kz = std::max<int64_t>(kz, kin_blocks(2, S.n[0], S.n[1], S.n[2], zmfma));
+    }
+    if (bits != 0)
+      kpl = std::max<int64_t>(kpl, 2ll * S.n[2] * plane_strips(S.n[1] + 2 * S.ext) + 2 * S.n[1]);
+  }
+  int64_t kin() const { return std::max(kx + ky + kz, kpl); }
+};
 
 // types in which a function takes the plane kernels (bit 0 FP32, bit 1 FP64)
 static int plane_bits(const SfDev& S) {
@@ -742,9 +773,13 @@ static int back_blocks(const SfDev& S) {
 constexpr int kLdsSplit = 64;
 
 // Builds the layout for `nbins` bins; false (with a message) when a box
-// does not fit the kernels' LDS stages.
+// does not fit the kernels' LDS stages.  With a workspace bound, the chunks of
+// the plane kernels keep within the column kernels' workspace as well
+// (P->ws_cap, from the layouts with zmfma, which are made first): what a plan
+// reports is then what the column kernels need, for every layout.
 static bool make_layout(const wvl_plan* P, int nbins, bool zmfma, Layout* L, std::string* err) {
   const int nsf = P->nsf;
+  const std::vector<int32_t>& order = P->order[zmfma ? 1 : 0];
   L->chunks.clear();
   L->wk.assign(nsf, SfWork{});
   L->nbins = nbins;
@@ -761,32 +796,41 @@ static bool make_layout(const wvl_plan* P, int nbins, bool zmfma, Layout* L, std
       ChunkDev ch{};
       ch.sf0 = k;
       int64_t elems = 0;
+      PartSlots most;
       int j = k;
       // the matrix-core z part belongs to the column kernels; a chunk's
       // functions take the same kernels
-      const int bits = zmfma ? 0 : plane_bits(P->h_sf[P->order[k]]);
-      const bool slim = bits == 3;
+      const int bits = zmfma ? 0 : plane_bits(P->h_sf[order[k]]);
       ch.plane[0] = bits & 1;
       ch.plane[1] = bits & 2;
       for (; j < b1; ++j) {
-        if (!zmfma && plane_bits(P->h_sf[P->order[j]]) != bits) break;
+        if (!zmfma && plane_bits(P->h_sf[order[j]]) != bits) break;
         // one launch has one LDS size: smaller boxes, of which more blocks fit
         // a CU, get a launch of their own where there are enough of either
         if (j - k >= kLdsSplit && b1 - j >= kLdsSplit && bits &&
-            back_blocks(P->h_sf[P->order[j]]) != back_blocks(P->h_sf[P->order[k]]))
+            back_blocks(P->h_sf[order[j]]) != back_blocks(P->h_sf[order[k]]))
           break;
-        const int64_t need = sf_elems(P->h_sf[P->order[j]], slim);
+        const int64_t need = sf_elems(P->h_sf[order[j]], bits);
+        PartSlots top = most;
+        top.add(P->h_sf[order[j]], bits, zmfma);
         // partial slots are at most a few per 256 output points
         const int64_t bytes = align_bytes((elems + need) * 8) + (int64_t)(j - k + 1) * 4096 * 8;
         if (j > k && P->max_ws > 0 && (size_t)bytes > P->max_ws) break;
+        if (j > k && P->max_ws > 0 && !zmfma) {
+          const int64_t pb = (j - k + 1) * (top.pot + top.kin()) * 8;
+          if (align_bytes((elems + need) * 4) + pb > P->ws_cap[0] ||
+              align_bytes((elems + need) * 8) + pb > P->ws_cap[1])
+            break;
+        }
         if (j - k >= 65535) break;
         elems += need;
+        most = top;
       }
       ch.nsf = j - k;
       int64_t off = L->disjoint ? ebase : 0;
       const int64_t off0 = off;
       for (int q = k; q < j; ++q) {
-        const int id = P->order[q];
+        const int id = order[q];
         const SfDev& S = P->h_sf[id];
         const int64_t n0 = S.n[0], n1 = S.n[1], n2 = S.n[2], e = S.ext;
         const int64_t r0 = 2 * n0 + 29, r1 = 2 * n1 + 29;
@@ -794,17 +838,25 @@ static bool make_layout(const wvl_plan* P, int nbins, bool zmfma, Layout* L, std
         SfWork& W = L->wk[q];
         const int64_t p0 = pad16((int)r0);
         W.id = id;
-        W.g1 = off;  off += align64(2 * n2 * p0 * r1);
-        W.g2 = off;  off += align64(2 * o2 * p0 * r1);
-        W.oz = off;  off += align64(8 * o2 * n0 * n1);
-        if (!slim) {
-          W.c8 = off;  off += align64(8 * n0 * n1 * n2);
-          W.c8x = off; off += align64(8 * n0 * n1 * n2);
-          W.q = off;   off += align64(4 * o2 * r0 * qrow_stride((int)o1));
-          W.ox = off;  off += align64(8 * n2 * o0 * n1);
-          W.oy = off;  off += align64(8 * n2 * qrow_stride((int)o1) * n0);
-          W.gx = off;  off += align64(4 * n2 * n1 * r0);
+        if (bits) {
+          int64_t o = off;
+          W.p1 = o; o += align64(2 * n2 * p0 * r1);
+          W.p2 = o; o += align64(2 * o2 * p0 * r1);
+          W.pz = o;
         }
+        if (bits != 3) {
+          int64_t o = off;
+          W.c8 = o;  o += align64(8 * n0 * n1 * n2);
+          W.c8x = o; o += align64(8 * n0 * n1 * n2);
+          W.g1 = o;  o += align64(2 * n2 * r0 * r1);
+          W.g2 = o;  o += align64(2 * o2 * r0 * r1);
+          W.q = o;   o += align64(4 * o2 * r0 * qrow_stride((int)o1));
+          W.ox = o;  o += align64(8 * n2 * o0 * n1);
+          W.oy = o;  o += align64(8 * n2 * qrow_stride((int)o1) * n0);
+          W.oz = o;  o += align64(8 * o2 * n0 * n1);
+          W.gx = o;
+        }
+        off += sf_elems(S, bits);
         // plane kernels: partials counted on the function's own box
         const int ns = plane_strips((int)o1);
         W.nepart_pl[0] = (r0 * r1 + 255) / 256;
@@ -814,7 +866,6 @@ static bool make_layout(const wvl_plan* P, int nbins, bool zmfma, Layout* L, std
         ch.grid_ct = (int32_t)std::max<int64_t>(ch.grid_ct, W.nepart_pl[1]);
         ch.grid_ks = (int32_t)std::max<int64_t>(ch.grid_ks, 2 * n1);
         ch.grid_bp = (int32_t)std::max<int64_t>(ch.grid_bp, 8 * ((o2 + 7) / 8) * 2 * ns);
-        ch.nblk_kin = (int32_t)std::max<int64_t>(ch.nblk_kin, W.nkpart_pl);
         for (int d = 0; d < 2; ++d) {
           const int sz = d ? 8 : 4;
           if (!ch.plane[d]) continue;
@@ -854,16 +905,16 @@ static bool make_layout(const wvl_plan* P, int nbins, bool zmfma, Layout* L, std
       }
       for (int d = 0; d < 2; ++d)
         for (int q = k; ch.plane[d] && q < j; ++q) {
-          const SfDev& S = P->h_sf[P->order[q]];
+          const SfDev& S = P->h_sf[order[q]];
           ch.lds_up[d] = std::max<int64_t>(ch.lds_up[d], (d ? 8 : 4) * plane_lds_up(S.n[0], S.n[1],
                                                                                   ch.up_both[d],
                                                                                   d ? 8 : 4));
         }
-      ch.nblk_pot = std::max(ch.grid_b, ch.grid_ct);
-      ch.nblk_kin = std::max(ch.nblk_kin, ch.grid_kx + ch.grid_ky + ch.grid_kz);
+      ch.nblk_pot = (int32_t)most.pot;
+      ch.nblk_kin = (int32_t)most.kin();
       int64_t poff = L->disjoint ? pbase : 0;
       for (int q = k; q < j; ++q) {
-        const SfDev& S = P->h_sf[P->order[q]];
+        const SfDev& S = P->h_sf[order[q]];
         SfWork& W = L->wk[q];
         W.epart = poff;
         poff += ch.nblk_pot;
@@ -1005,21 +1056,25 @@ wvl_status wvl_plan_create(wvl_ctx* ctx, int32_t nsf, const wvl_locreg* lr, cons
     bbox(segs, L.oseg_c, L.noseg_c, S.bb_out);
   }
   // processing order: the functions of the column kernels first, then the
-  // largest boxes, ties by index
-  P->order.resize(nsf);
-  for (int k = 0; k < nsf; ++k) P->order[k] = k;
-  std::stable_sort(P->order.begin(), P->order.end(), [&](int a, int b) {
-    const SfDev &A = P->h_sf[a], &B = P->h_sf[b];
-    const int pa = plane_bits(A), pb = plane_bits(B);
-    if (pa != pb) return pa < pb;
-    return (int64_t)A.n[0] * A.n[1] * A.n[2] > (int64_t)B.n[0] * B.n[1] * B.n[2];
-  });
+  // largest boxes, ties by index; for the layouts of the column kernels the
+  // largest boxes first
+  for (int c = 0; c < 2; ++c) {
+    std::vector<int32_t>& order = P->order[c];
+    order.resize(nsf);
+    for (int k = 0; k < nsf; ++k) order[k] = k;
+    std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
+      const SfDev &A = P->h_sf[a], &B = P->h_sf[b];
+      const int pa = plane_bits(A), pb = plane_bits(B);
+      if (c == 0 && pa != pb) return pa < pb;
+      return (int64_t)A.n[0] * A.n[1] * A.n[2] > (int64_t)B.n[0] * B.n[1] * B.n[2];
+    });
+  }
   P->max_ws = max_workspace_bytes;
   P->in_sub_out = in_sub_out;
   for (int k = 0; k < nsf; ++k)
     P->max_in_segs = std::max<int64_t>(P->max_in_segs, lr[k].nseg_c + lr[k].nseg_f);
   // the workspace reported covers every layout the autotuner may pick
-  for (int zm = 0; zm < 2; ++zm)
+  for (int zm = 1; zm >= 0; --zm)
     for (int nb : kTuneBins) {
       Layout L;
       std::string err;

@@ -56,17 +56,21 @@ constexpr int kBackOutRows = 16;
 //   c8x  dense input box, y fastest      [8][N2][N0][N1]
 //   g1   after the x, y up passes        [2][N2][R1][R0]
 //   g2   after the z column pass         [2][O2][R1][R0]
-//        (plane kernels: rows pad16(R0) apart)
 //   q    after the y down pass           [4][O2][R0][O1]   (channel a2 + 2 a3)
 //   ox   x part of the kinetic term      [8][N2][O0][N1]
 //   oy   y part of the kinetic term      [8][N2][N0][O1]
-//   oz   z part of the kinetic term      [8][O2][N0][N1] (plane kernels:
-//        [8][O2][N1][N0])
+//   oz   z part of the kinetic term      [8][O2][N0][N1]
 //   gx   after the x up pass             [4][N2][N1][R0]   (channel a2 + 2 a3)
-// A function of the plane kernels (in both types) has g1, g2 and oz only.
+// and of the plane kernels:
+//   p1   after the x, y up passes        [2][N2][R1][pad16(R0)]
+//   p2   after the z column pass         [2][O2][R1][pad16(R0)]
+//   pz   z part of the kinetic term      [8][O2][N1][N0]
+// A function that takes the plane kernels in both types has the last three
+// only; one that does so in one type has both sets in the same place.
 struct SfWork {
   int64_t id;         // the function's index in the plan (SfDev array, outputs)
   int64_t c8, c8x, g1, g2, q, ox, oy, oz, gx;
+  int64_t p1, p2, pz;
   int64_t epart;      // offset (in doubles) of its e_pot partials
   int64_t kpart;      // offset (in doubles) of its e_kin partials
   int64_t nkpart;     // number of e_kin partials: its own k_kin_col blocks

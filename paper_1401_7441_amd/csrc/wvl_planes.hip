@@ -337,7 +337,7 @@ __device__ __forceinline__ void up_plane(int bx, const SfDev* __restrict__ sfs,
   T A[12];
   load_band(A, kUpPair, lane);
   const int ny = (R1 + 15) >> 4, nch = (ny + 2) / 3;
-  const Buf<T> o0(ws + w.g1 + ((int64_t)a3 * N2 + z) * ((int64_t)R1 * P0), R1 * P0);
+  const Buf<T> o0(ws + w.p1 + ((int64_t)a3 * N2 + z) * ((int64_t)R1 * P0), R1 * P0);
   for (int job = wave; job < nx * nch; job += NW) {
     const int tx = job % nx, t0 = 3 * (job / nx), t1 = min(ny, t0 + 3);
     const T* const yb = Y + (g & 1) * ych + 16 * tx + n;
@@ -471,7 +471,7 @@ __device__ __forceinline__ void up_plane(int bx, const SfDev* __restrict__ sfs,
   }
   __syncthreads();
   const int nq1 = (R1 + 15) >> 4;
-  const Buf<float> o0(ws + w.g1 + ((int64_t)a3 * N2 + z) * ((int64_t)R1 * P0), R1 * P0);
+  const Buf<float> o0(ws + w.p1 + ((int64_t)a3 * N2 + z) * ((int64_t)R1 * P0), R1 * P0);
   for (int it = tid & ~63; it < R0 * nq1; it += 256) {
     const int i = min(it + (tid & 63), R0 * nq1 - 1);
     const int sg = i / R0, px = i - sg * R0;
@@ -520,7 +520,7 @@ __global__ __launch_bounds__(256) void k_col_tile(const SfDev* __restrict__ sfs,
   if (item < items) {
     const int py = item / nx, px = 16 * (item - py * nx) + n;
     const int plane = R1 * P0, col = py * P0 + px;
-    const Buf<T> in0(ws + w.g1, (int64_t)N2 * plane), in1(ws + w.g1 + (int64_t)N2 * plane,
+    const Buf<T> in0(ws + w.p1, (int64_t)N2 * plane), in1(ws + w.p1 + (int64_t)N2 * plane,
                                                           (int64_t)N2 * plane);
     const bool pin = px < R0;
     const int sh = SYN ? 0 : e;
@@ -553,7 +553,7 @@ __global__ __launch_bounds__(256) void k_col_tile(const SfDev* __restrict__ sfs,
     for (int ks = 0; ks < 4; ++ks) fetch(ks + 2);
     const int nu = SYN ? (R2 + 15) >> 4 : ((O2 + 7) >> 3) + 2;
     const int fplane = R1 * R0;
-    const Buf<T> out(SYN ? fine + fine_off[w.id] : ws + w.g2,
+    const Buf<T> out(SYN ? fine + fine_off[w.id] : ws + w.p2,
                      SYN ? (int64_t)fplane * R2 : 2ll * O2 * plane);
     // of this lane's element 0
     uint32_t ob = SYN ? (uint32_t)(g * fplane + py * R0 + px) * SZ : (uint32_t)(g * plane + col) * SZ;
@@ -757,7 +757,7 @@ __device__ __forceinline__ void kin_slab(int bx, const SfDev* __restrict__ sfs,
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int nseg = (O2 + 7) >> 3, ngrp = (2 * N0 + 63) >> 6;
   const int ocomp = O2 * N1 * N0, zst = N1 * N0;
-  const Buf<T> oz(ws + w.oz, 8ll * ocomp);
+  const Buf<T> oz(ws + w.pz, 8ll * ocomp);
   constexpr uint32_t SZ = sizeof(T);
   double eacc = 0.0;
   for (int job = wave; job < nseg * ngrp; job += kPlaneThreads / 64) {
@@ -907,7 +907,7 @@ __global__ __launch_bounds__(back_threads<T>(), 4) void k_back_plane(
     // the outputs s0 .. s0 + 23 of both channels.  Q column of px: px + qs (qs
     // aligns the x pass' groups of four points for odd ext), zeros beside.
     const int qs = (2 * e) & 3;
-    const Buf<T> g2(ws + w.g2 + (int64_t)(a3 * O2 + zp) * (R1 * P0), R1 * P0);
+    const Buf<T> g2(ws + w.p2 + (int64_t)(a3 * O2 + zp) * (R1 * P0), R1 * P0);
     for (int tx = wave; tx < P0 >> 4; tx += NW) {
       constexpr int NB = 4 * (kStrip / 8 + 2);
       T B[NB];
@@ -1014,7 +1014,7 @@ __global__ __launch_bounds__(back_threads<T>(), 4) void k_back_plane(
   if (kin_on) {
     // y + z parts: items of a column (x, a1) and 8 outputs y'
     const int nsy = (ns + 7) >> 3, ocomp = O2 * N1 * N0;
-    const Buf<T> oz(ws + w.oz, 8ll * ocomp);
+    const Buf<T> oz(ws + w.pz, 8ll * ocomp);
     const int py = sizeof(T) == 4 ? 2 * N0 : (2 * N0 + 63) & ~63;   // items per segment
     for (int it = 64 * wave; it < nsy * py; it += 64 * NW) {
       const int ca = it / py, cb = sizeof(T) == 4 ? min(it + 63, nsy * py - 1) / py : ca;
