@@ -417,20 +417,18 @@ void wvl_graph_destroy(wvl_graph* graph);
 
 /* Autotuner over the plan's schedule: for every bin count in
  * {1, 2, 3, 4, 6, 8} (functions sorted by box volume, cut into that many
- * launches per stage) and both forms of the kinetic term's z part (the
- * register-window stencil on the vector units, or banded-Toeplitz products
- * on the FP64 matrix cores), runs the apply `reps` times (after one warm-up)
- * and keeps the fastest layout.  Buffers as for wvl_apply_local_ham (hpsi_c is overwritten; the
- * workspace is the size wvl_plan_create reported, which covers every
- * candidate).  tried (host, may be NULL) receives up to max_tried points,
- * *ntried the number timed, *best the chosen one.  Synchronous; the plan
- * must not be in use on another stream meanwhile.  A change of bin count
- * alone leaves later results bitwise unchanged; the matrix-core z part sums
- * in another order and agrees with the vector form to the parity
- * tolerances. */
+ * launches per stage), and, when a box is too large for the plane kernels in
+ * dt, also for the schedules with kin_mfma (see wvl_plan_set_schedule), runs
+ * the apply `reps` times (after one warm-up) and keeps the fastest layout.
+ * Buffers as for wvl_apply_local_ham (hpsi_c is overwritten; the workspace is
+ * the size wvl_plan_create reported, which covers every schedule).  tried
+ * (host, may be NULL) receives up to max_tried points, *ntried the number
+ * timed, *best the chosen one.  Synchronous; the plan must not be in use on
+ * another stream meanwhile.  A change of bin count alone leaves later results
+ * bitwise unchanged. */
 typedef struct {
   int32_t nbins;      /* bins of the size-sorted functions */
-  int32_t kin_mfma;   /* 1: z part of the kinetic term on the matrix cores */
+  int32_t kin_mfma;   /* 1: column kernels, kinetic z part on the matrix cores */
   double ms;          /* mean duration of one apply */
 } wvl_tune_point;
 wvl_status wvl_plan_autotune(wvl_plan* plan, wvl_dtype dt, uint32_t terms, const void* psi_c,
@@ -438,12 +436,15 @@ wvl_status wvl_plan_autotune(wvl_plan* plan, wvl_dtype dt, uint32_t terms, const
                              wvl_tune_point* tried, int32_t max_tried, int32_t* ntried,
                              wvl_tune_point* best);
 
-/* Sets the plan's schedule directly (a point wvl_plan_autotune tries): nbins
- * bins of the size-sorted functions, kin_mfma 1 for the z part of the
- * kinetic term on the matrix cores.  Synchronous; graphs captured before are
- * rejected afterwards.  Results agree with every other schedule to the
- * parity tolerances (bitwise for a change of nbins alone).  Errors:
- * WVL_EINVAL for nbins < 1, kin_mfma outside {0, 1}, or a schedule that
+/* Sets the plan's schedule directly (a point wvl_plan_autotune may try): nbins
+ * bins of the size-sorted functions; kin_mfma 0: functions whose box planes
+ * fit the LDS of a compute unit in the call's type run the plane kernels, the
+ * others the column kernels; kin_mfma 1: every function runs the column
+ * kernels, with the z part of the kinetic term as banded-Toeplitz products on
+ * the FP64 matrix cores (applies and wvl_synthesize).  Synchronous; graphs
+ * captured before are rejected afterwards.  Results agree with every other
+ * schedule to the parity tolerances (bitwise for a change of nbins alone).
+ * Errors: WVL_EINVAL for nbins < 1, kin_mfma outside {0, 1}, or a schedule that
  * needs more workspace than the plan reported (bins beyond 8 may). */
 wvl_status wvl_plan_set_schedule(wvl_plan* plan, int32_t nbins, int32_t kin_mfma);
 

@@ -2287,9 +2287,14 @@ wvl_status wvl_plan_autotune(wvl_plan* P, wvl_dtype dt, uint32_t terms, const vo
     (void)hipEventDestroy(e0);
     return hip_fail(ctx, "wvl_plan_autotune", "hipEventCreate", he);
   }
+  // the column kernels (kin_mfma 1) are slower than the plane kernels wherever
+  // these fit (1,000 functions of radius 5-7 bohr: 13.0 against 8.0 ms in FP32,
+  // 25 against 14.8 in FP64), so they are tried only if a function needs them
+  bool column = false;
+  for (const SfDev& S : P->h_sf) column = column || !(plane_bits(S) >> (sz == 8) & 1);
   wvl_tune_point top{0, 0, 1e300};
   int n = 0;
-  for (int zm = 0; zm < 2; ++zm)
+  for (int zm = 0; zm < (column ? 2 : 1); ++zm)
   for (int nb : kTuneBins) {
     Layout L;
     std::string err;

@@ -102,3 +102,18 @@ def test_plan_just_below_the_static_workspace():
         torch.cuda.synchronize()
         outs.append(out.cpu().numpy())
     assert np.any(outs[0]) and np.array_equal(outs[0], outs[1])
+
+
+@pytest.mark.parametrize("name,dtype,points", [("small", "float64", 6), ("wide in f64", "float32", 6),
+                                               ("wide in f64", "float64", 12), ("wide", "float32", 12)])
+def test_autotuner_tries_the_column_kernels_only_where_a_box_needs_them(name, dtype, points):
+    _print(f"case: autotuner candidates, {name}, {dtype}")
+    case = _case(BOXES[name])
+    dt = getattr(torch, dtype)
+    plan = W.Plan(W.Context(case.g.h, case.g.grid_n), case.rec, case.segs)
+    psi = torch.tensor(case.psi, dtype=dt, device="cuda")
+    pot = torch.tensor(case.pot, dtype=dt, device="cuda")
+    out = torch.zeros(plan.info["out_coefs"], dtype=dt, device="cuda")
+    best, tried = W.autotune(plan, psi, pot, out, plan.new_workspace(dt), reps=1)
+    assert len(tried) == points and best in tried
+    assert sorted({t["kin_mfma"] for t in tried}) == ([0] if points == 6 else [0, 1])
