@@ -39,6 +39,8 @@
 // padding on the vector unit.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "wvl_filters.h"
 #include "wvl_internal.h"
 
@@ -122,6 +124,42 @@ __device__ __forceinline__ void load_band(T (&A)[12], int kind, int lane) {
     else
       A[k] = gBands32.v[kind][k][lane];
   }
+}
+
+// The products give every output the whole window, with zeros for the points
+// that none of its taps meets, and zero times an infinity is NaN.  An output
+// must not depend on such points: a wave whose products hold a value that is
+// not finite (one value per lane and tile tells, since every point of a window
+// enters every output of its row) runs its tiles once more with the outputs
+// formed from the taps alone (operands B[at], B[at + 1], ..), in the order of
+// the instructions.  The second run is code of its own (`again`), so that the
+// first pays for a comparison per tile only.
+template <typename T> __device__ __forceinline__ bool not_finite(T v) {
+  return !__builtin_isfinite(v);
+}
+template <typename T, int NB>
+__device__ __forceinline__ typename Mma<T>::V taps_only(const T (&B)[NB], int at, int kind,
+                                                        int lane) {
+  asm volatile("" : "+v"(lane));   // keeps what follows out of the loops around it
+  const int n = lane & 15, g = lane >> 4;
+  typename Mma<T>::V s = {T(0), T(0), T(0), T(0)};
+#pragma unroll
+  for (int k = 0; k < 12; ++k) {
+#pragma unroll 1
+    for (int h = 0; h < 4; ++h) {
+      const T x = __shfl(B[at + k], 16 * h + n, 64);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        T c;
+        if constexpr (sizeof(T) == 8)
+          c = gBands64.v[kind][k][16 * h + Mma<T>::row(r, g)];
+        else
+          c = gBands32.v[kind][k][16 * h + Mma<T>::row(r, g)];
+        if (c != T(0)) s[r] = __builtin_fma(c, x, s[r]);
+      }
+    }
+  }
+  return s;
 }
 
 // A buffer in global memory: loads beyond its bytes (negative offsets among
@@ -289,47 +327,55 @@ __device__ __forceinline__ void up_plane(int bx, const SfDev* __restrict__ sfs,
       }
       if (a2 == 0 || !both) __syncthreads();
       const T* const Xa = X + (both ? 2 * a2 * N1 * ldx : 0);
-      for (int job = wave; job < NSP * nrt; job += NW) {
-        const int y = (job / NSP) * 16 + n;
-        const T* const x0 = Xa + min(y, N1 - 1) * ldx;   // rows past N1: not stored
-        const T* const x1 = x0 + N1 * ldx;
-        T* const yo = Y + a2 * ych + y * ldy;
-        const int t0 = (job % NSP) * len, t1 = min(nx, t0 + len);
-        T B[12];
-        auto fetch = [&](int ks, int t, int slot) {   // points 8 t - 16 + 4 ks + g
-          const int q0 = 8 * t - 16 + 4 * ks, q = q0 + g;
-          if (q0 >= 0 && q0 + 3 < N0) {
-            B[2 * slot] = x0[q];
-            B[2 * slot + 1] = x1[q];
-          } else {
-            const bool ok = q >= 0 && q < N0;
-            const int k = ok ? q : 0;
-            const T v0 = x0[k], v1 = x1[k];
-            B[2 * slot] = ok ? v0 : T(0);
-            B[2 * slot + 1] = ok ? v1 : T(0);
-          }
-        };
+      auto pass = [&](auto again_) {
+        constexpr bool again = decltype(again_)::value;
+        bool bad = false;
+        for (int job = wave; job < NSP * nrt; job += NW) {
+          const int y = (job / NSP) * 16 + n;
+          const T* const x0 = Xa + min(y, N1 - 1) * ldx;   // rows past N1: not stored
+          const T* const x1 = x0 + N1 * ldx;
+          T* const yo = Y + a2 * ych + y * ldy;
+          const int t0 = (job % NSP) * len, t1 = min(nx, t0 + len);
+          T B[12];
+          auto fetch = [&](int ks, int t, int slot) {   // points 8 t - 16 + 4 ks + g
+            const int q0 = 8 * t - 16 + 4 * ks, q = q0 + g;
+            if (q0 >= 0 && q0 + 3 < N0) {
+              B[2 * slot] = x0[q];
+              B[2 * slot + 1] = x1[q];
+            } else {
+              const bool ok = q >= 0 && q < N0;
+              const int k = ok ? q : 0;
+              const T v0 = x0[k], v1 = x1[k];
+              B[2 * slot] = ok ? v0 : T(0);
+              B[2 * slot + 1] = ok ? v1 : T(0);
+            }
+          };
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks) fetch(ks, t0, ks + 2);
-        for (int t = t0; t < t1; ++t) {
+          for (int ks = 0; ks < 4; ++ks) fetch(ks, t0, ks + 2);
+          for (int t = t0; t < t1; ++t) {
 #pragma unroll
-          for (int k = 0; k < 8; ++k) B[k] = B[k + 4];
-          fetch(4, t, 4);
-          fetch(5, t, 5);
-          V d = {T(0), T(0), T(0), T(0)};
+            for (int k = 0; k < 8; ++k) B[k] = B[k + 4];
+            fetch(4, t, 4);
+            fetch(5, t, 5);
+            V d = {T(0), T(0), T(0), T(0)};
 #pragma unroll
-          for (int ks = 0; ks < 6; ++ks) {
-            const int q = 8 * t - 16 + 4 * ks;
-            if (q + 3 < 0 || q >= N0) continue;   // no input there
-            d = Mma<T>::mma(A[2 * ks], B[2 * ks], d);
-            d = Mma<T>::mma(A[2 * ks + 1], B[2 * ks + 1], d);
-          }
-          if (y < N1) {
+            for (int ks = 0; !again && ks < 6; ++ks) {
+              const int q = 8 * t - 16 + 4 * ks;
+              if (q + 3 < 0 || q >= N0) continue;   // no input there
+              d = Mma<T>::mma(A[2 * ks], B[2 * ks], d);
+              d = Mma<T>::mma(A[2 * ks + 1], B[2 * ks + 1], d);
+            }
+            if (again) d = taps_only<T>(B, 0, kUp, lane);
+            bad |= not_finite(d[0]);
+            if (y < N1) {
 #pragma unroll
-            for (int r = 0; r < 4; ++r) yo[16 * t + Mma<T>::row(r, g)] = d[r];
+              for (int r = 0; r < 4; ++r) yo[16 * t + Mma<T>::row(r, g)] = d[r];
+            }
           }
         }
-      }
+        return __any(bad) != 0;
+      };
+      if (__builtin_expect(pass(std::false_type{}), 0)) pass(std::true_type{});
       __syncthreads();
     }
   }
@@ -338,48 +384,56 @@ __device__ __forceinline__ void up_plane(int bx, const SfDev* __restrict__ sfs,
   load_band(A, kUpPair, lane);
   const int ny = (R1 + 15) >> 4, nch = (ny + 2) / 3;
   const Buf<T> o0(ws + w.p1 + ((int64_t)a3 * N2 + z) * ((int64_t)R1 * P0), R1 * P0);
-  for (int job = wave; job < nx * nch; job += NW) {
-    const int tx = job % nx, t0 = 3 * (job / nx), t1 = min(ny, t0 + 3);
-    const T* const yb = Y + (g & 1) * ych + 16 * tx + n;
-    T B[12];
-    auto fetch = [&](int ks, int t, int slot) {
-      const int q0 = 8 * t - 16 + 4 * ks;
-      if (q0 >= 0 && q0 + 3 < N1) {
-        const T* const y = yb + (q0 + (g >> 1)) * ldy;
-        B[2 * slot] = y[0];
-        B[2 * slot + 1] = y[2 * ldy];
-        return;
-      }
+  auto pass = [&](auto again_) {
+    constexpr bool again = decltype(again_)::value;
+    bool bad = false;
+    for (int job = wave; job < nx * nch; job += NW) {
+      const int tx = job % nx, t0 = 3 * (job / nx), t1 = min(ny, t0 + 3);
+      const T* const yb = Y + (g & 1) * ych + 16 * tx + n;
+      T B[12];
+      auto fetch = [&](int ks, int t, int slot) {
+        const int q0 = 8 * t - 16 + 4 * ks;
+        if (q0 >= 0 && q0 + 3 < N1) {
+          const T* const y = yb + (q0 + (g >> 1)) * ldy;
+          B[2 * slot] = y[0];
+          B[2 * slot + 1] = y[2 * ldy];
+          return;
+        }
 #pragma unroll
-      for (int c = 0; c < 2; ++c) {
-        const int q = q0 + 2 * c + (g >> 1);
-        const bool ok = q >= 0 && q < N1;
-        const T v = yb[(ok ? q : 0) * ldy];
-        B[2 * slot + c] = ok ? v : T(0);
-      }
-    };
+        for (int c = 0; c < 2; ++c) {
+          const int q = q0 + 2 * c + (g >> 1);
+          const bool ok = q >= 0 && q < N1;
+          const T v = yb[(ok ? q : 0) * ldy];
+          B[2 * slot + c] = ok ? v : T(0);
+        }
+      };
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks) fetch(ks, t0, ks + 2);
-    for (int t = t0; t < t1; ++t) {
+      for (int ks = 0; ks < 4; ++ks) fetch(ks, t0, ks + 2);
+      for (int t = t0; t < t1; ++t) {
 #pragma unroll
-      for (int k = 0; k < 8; ++k) B[k] = B[k + 4];
-      fetch(4, t, 4);
-      fetch(5, t, 5);
-      V d = {T(0), T(0), T(0), T(0)};
+        for (int k = 0; k < 8; ++k) B[k] = B[k + 4];
+        fetch(4, t, 4);
+        fetch(5, t, 5);
+        V d = {T(0), T(0), T(0), T(0)};
 #pragma unroll
-      for (int ks = 0; ks < 6; ++ks) {
-        const int q = 8 * t - 16 + 4 * ks;
-        if (q + 3 < 0 || q >= N1) continue;
-        d = Mma<T>::mma(A[2 * ks], B[2 * ks], d);
-        d = Mma<T>::mma(A[2 * ks + 1], B[2 * ks + 1], d);
-      }
+        for (int ks = 0; !again && ks < 6; ++ks) {
+          const int q = 8 * t - 16 + 4 * ks;
+          if (q + 3 < 0 || q >= N1) continue;
+          d = Mma<T>::mma(A[2 * ks], B[2 * ks], d);
+          d = Mma<T>::mma(A[2 * ks + 1], B[2 * ks + 1], d);
+        }
+        if (again) d = taps_only<T>(B, 0, kUpPair, lane);
+        bad |= not_finite(d[0]);
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int py = 16 * t + Mma<T>::row(r, g);   // rows past R1: dropped
-        o0.put((uint32_t)(py * P0 + 16 * tx + n) * (uint32_t)sizeof(T), d[r]);
+        for (int r = 0; r < 4; ++r) {
+          const int py = 16 * t + Mma<T>::row(r, g);   // rows past R1: dropped
+          o0.put((uint32_t)(py * P0 + 16 * tx + n) * (uint32_t)sizeof(T), d[r]);
+        }
       }
     }
-  }
+    return __any(bad) != 0;
+  };
+  if (__builtin_expect(pass(std::false_type{}), 0)) pass(std::true_type{});
 }
 
 // ---------------------------------------------------------------------------
@@ -528,9 +582,9 @@ __global__ __launch_bounds__(256) void k_col_tile(const SfDev* __restrict__ sfs,
     constexpr int kRow = 4;   // row(r + 1, g) - row(r, g)
     const int64_t vstride = (int64_t)nf1 * nf2;
     const bool von = !SYN && pot != nullptr;
-    const T* vq = von ? pot + ((int64_t)(2 * sf.lo[2] - 2 * sh + Mma<T>::row(0, g)) * nf2 +
-                               (2 * sf.lo[1] + py)) * nf1 + (2 * sf.lo[0] + (pin ? px : 0))
-                      : nullptr;
+    const T* const vcol = von ? pot + ((int64_t)(2 * sf.lo[2] - 2 * sh + Mma<T>::row(0, g)) * nf2 +
+                                     (2 * sf.lo[1] + py)) * nf1 + (2 * sf.lo[0] + (pin ? px : 0))
+                              : nullptr;
     const double ca = (!SYN && conf) ? conf[w.id] : 0.0;
     const double cdx = (double)(2 * sf.lo[0] + px - 14) * hh - sf.c[0];
     const double cdy = (double)(2 * sf.lo[1] + py - 14) * hh - sf.c[1];
@@ -540,94 +594,107 @@ __global__ __launch_bounds__(256) void k_col_tile(const SfDev* __restrict__ sfs,
     load_band(Au, kUp, lane);
     if constexpr (!SYN) load_band(Ad, kDownReg, lane);
     // points q = 8 u - sh - 16 + 4 ks + g; 0 outside [0, N2)
-    uint32_t inb = (uint32_t)((g - sh - 16) * plane + col) * SZ;   // of ks = 0, u = 0
+    uint32_t inb;
     const uint32_t kstep = 4u * (uint32_t)plane * SZ;
     auto fetch = [&](int slot) {
       B[2 * slot] = in0.at(inb);
       B[2 * slot + 1] = in1.at(inb);
       inb += kstep;
     };
-#pragma unroll
-    for (int k = 0; k < 12; ++k) B[k] = G[k] = T(0);
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks) fetch(ks + 2);
     const int nu = SYN ? (R2 + 15) >> 4 : ((O2 + 7) >> 3) + 2;
     const int fplane = R1 * R0;
     const Buf<T> out(SYN ? fine + fine_off[w.id] : ws + w.p2,
                      SYN ? (int64_t)fplane * R2 : 2ll * O2 * plane);
-    // of this lane's element 0
-    uint32_t ob = SYN ? (uint32_t)(g * fplane + py * R0 + px) * SZ : (uint32_t)(g * plane + col) * SZ;
-    for (int u = 0; u < nu; ++u) {
-      const int p0 = 16 * u - 2 * sh;
+    auto pass = [&](auto again_) {
+      constexpr bool again = decltype(again_)::value;
+      bool bad = false;
+      eacc = 0.0;
+      const T* vq = vcol;
+      inb = (uint32_t)((g - sh - 16) * plane + col) * SZ;   // of ks = 0, u = 0
+      // of this lane's element 0
+      uint32_t ob = SYN ? (uint32_t)(g * fplane + py * R0 + px) * SZ : (uint32_t)(g * plane + col) * SZ;
 #pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        B[k] = B[k + 4];
-        G[k] = G[k + 4];
-      }
-      fetch(4);
-      fetch(5);
-      V d = {T(0), T(0), T(0), T(0)};
-      if (p0 + 15 >= 0 && p0 < R2) {
-        T v[4];
-        if constexpr (!SYN) {
+      for (int k = 0; k < 12; ++k) B[k] = G[k] = T(0);
 #pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const int p = p0 + Mma<T>::row(r, g);
-            T x = T(0);
-            if (von && ((p0 >= 0 && p0 + 15 < R2) || (p >= 0 && p < R2)))
-              x = vq[(int64_t)(r * kRow) * vstride];
-            v[r] = pin ? x : T(0);
-          }
-          if (ca != 0.0) {
+      for (int ks = 0; ks < 4; ++ks) fetch(ks + 2);
+      for (int u = 0; u < nu; ++u) {
+        const int p0 = 16 * u - 2 * sh;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+          B[k] = B[k + 4];
+          G[k] = G[k + 4];
+        }
+        fetch(4);
+        fetch(5);
+        V d = {T(0), T(0), T(0), T(0)};
+        if (p0 + 15 >= 0 && p0 < R2) {
+          T v[4];
+          if constexpr (!SYN) {
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
               const int p = p0 + Mma<T>::row(r, g);
-              const double dz = cz0 + (double)p * hh, r2 = cxy + dz * dz;
-              if (pin && p >= 0 && p < R2) v[r] = (T)((double)v[r] + ca * r2 * r2);
+              T x = T(0);
+              if (von && ((p0 >= 0 && p0 + 15 < R2) || (p >= 0 && p < R2)))
+                x = vq[(int64_t)(r * kRow) * vstride];
+              v[r] = pin ? x : T(0);
+            }
+            if (ca != 0.0) {
+#pragma unroll
+              for (int r = 0; r < 4; ++r) {
+                const int p = p0 + Mma<T>::row(r, g);
+                const double dz = cz0 + (double)p * hh, r2 = cxy + dz * dz;
+                if (pin && p >= 0 && p < R2) v[r] = (T)((double)v[r] + ca * r2 * r2);
+              }
+            }
+          }
+#pragma unroll
+          for (int ks = 0; !again && ks < 6; ++ks) {
+            const int q = 8 * u - sh - 16 + 4 * ks;
+            if (q + 3 < 0 || q >= N2) continue;
+            d = Mma<T>::mma(Au[2 * ks], B[2 * ks], d);
+            d = Mma<T>::mma(Au[2 * ks + 1], B[2 * ks + 1], d);
+          }
+          if (again) d = taps_only<T>(B, 0, kUp, lane);
+          bad |= not_finite(d[0]);
+          if constexpr (SYN) {
+            if (pin) {   // rows past R2: dropped
+#pragma unroll
+              for (int r = 0; r < 4; ++r)
+                out.put(ob + (uint32_t)(r * kRow * fplane) * SZ, d[r]);
+            }
+            ob += (uint32_t)(16 * fplane) * SZ;
+          } else {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              eacc += (double)v[r] * (double)d[r] * (double)d[r];
+              d[r] *= v[r];
             }
           }
         }
+        if constexpr (!SYN) {
+          vq += 16 * vstride;
 #pragma unroll
-        for (int ks = 0; ks < 6; ++ks) {
-          const int q = 8 * u - sh - 16 + 4 * ks;
-          if (q + 3 < 0 || q >= N2) continue;
-          d = Mma<T>::mma(Au[2 * ks], B[2 * ks], d);
-          d = Mma<T>::mma(Au[2 * ks + 1], B[2 * ks + 1], d);
-        }
-        if constexpr (SYN) {
-          if (pin) {   // rows past R2: dropped
+          for (int r = 0; r < 4; ++r) G[8 + r] = d[r];
+          if (u >= 2) {   // outputs 8 (u - 2) .. + 7 of both channels
+            V o = {T(0), T(0), T(0), T(0)};
 #pragma unroll
-            for (int r = 0; r < 4; ++r)
-              out.put(ob + (uint32_t)(r * kRow * fplane) * SZ, d[r]);
+            for (int k = 0; !again && k < 12; ++k) o = Mma<T>::mma(Ad[k], G[k], o);
+            if (again) o = taps_only<T>(G, 0, kDownReg, lane);
+            bad |= not_finite(o[0]);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              // m = 8 a + i: i = g + 4 (r & 1), a = r >> 1
+              const int i = Mma<T>::row(r, g) & 7, or_ = 4 * (r & 1) + (r >> 1) * O2;
+              if (8 * (u - 2) + 7 < O2 || 8 * (u - 2) + i < O2)
+                out.put(ob + (uint32_t)(or_ * plane) * SZ, o[r]);
+            }
+            ob += (uint32_t)(8 * plane) * SZ;
           }
-          ob += (uint32_t)(16 * fplane) * SZ;
-        } else {
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            eacc += (double)v[r] * (double)d[r] * (double)d[r];
-            d[r] *= v[r];
-          }
-        }
-      }
-      if constexpr (!SYN) {
-        vq += 16 * vstride;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) G[8 + r] = d[r];
-        if (u >= 2) {   // outputs 8 (u - 2) .. + 7 of both channels
-          V o = {T(0), T(0), T(0), T(0)};
-#pragma unroll
-          for (int k = 0; k < 12; ++k) o = Mma<T>::mma(Ad[k], G[k], o);
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            // m = 8 a + i: i = g + 4 (r & 1), a = r >> 1
-            const int i = Mma<T>::row(r, g) & 7, or_ = 4 * (r & 1) + (r >> 1) * O2;
-            if (8 * (u - 2) + 7 < O2 || 8 * (u - 2) + i < O2)
-              out.put(ob + (uint32_t)(or_ * plane) * SZ, o[r]);
-          }
-          ob += (uint32_t)(8 * plane) * SZ;
         }
       }
-    }
+      return __any(bad) != 0;
+    };
+    if (__builtin_expect(pass(std::false_type{}), 0)) pass(std::true_type{});
   }
   if constexpr (!SYN) {
     const double b = plane_block_sum(eacc);
@@ -908,25 +975,33 @@ __global__ __launch_bounds__(back_threads<T>(), 4) void k_back_plane(
     // aligns the x pass' groups of four points for odd ext), zeros beside.
     const int qs = (2 * e) & 3;
     const Buf<T> g2(ws + w.p2 + (int64_t)(a3 * O2 + zp) * (R1 * P0), R1 * P0);
-    for (int tx = wave; tx < P0 >> 4; tx += NW) {
-      constexpr int NB = 4 * (kStrip / 8 + 2);
-      T B[NB];
-      const uint32_t o = 16 * tx + n < 2 * N0 + 29
-                             ? (uint32_t)((2 * (s0 - e) + g) * P0 + 16 * tx + n) * SZ : kNone;
+    auto y_pass = [&](auto again_) {
+      constexpr bool again = decltype(again_)::value;
+      bool bad = false;
+      for (int tx = wave; tx < P0 >> 4; tx += NW) {
+        constexpr int NB = 4 * (kStrip / 8 + 2);
+        T B[NB];
+        const uint32_t o = 16 * tx + n < 2 * N0 + 29
+                               ? (uint32_t)((2 * (s0 - e) + g) * P0 + 16 * tx + n) * SZ : kNone;
 #pragma unroll
-      for (int k = 0; k < NB; ++k) B[k] = g2.at(o + (uint32_t)(4 * k * P0) * SZ);
-      T* const qo = Q + (sizeof(T) == 4 ? (g >> 1) * kStrip + 4 * (g & 1) : g) * ldq + 16 * tx + n + qs;
+        for (int k = 0; k < NB; ++k) B[k] = g2.at(o + (uint32_t)(4 * k * P0) * SZ);
+        T* const qo = Q + (sizeof(T) == 4 ? (g >> 1) * kStrip + 4 * (g & 1) : g) * ldq + 16 * tx + n + qs;
 #pragma unroll
-      for (int t = 0; t < kStrip / 8; ++t) {
-        V d = {T(0), T(0), T(0), T(0)};
+        for (int t = 0; t < kStrip / 8; ++t) {
+          V d = {T(0), T(0), T(0), T(0)};
 #pragma unroll
-        for (int k = 0; k < 12; ++k) d = Mma<T>::mma(A[k], B[4 * t + k], d);
-        // m = 8 a2 + i: f32 i = 4 (g & 1) + r, a2 = g >> 1; f64 i = g + 4 (r & 1), a2 = r >> 1
+          for (int k = 0; !again && k < 12; ++k) d = Mma<T>::mma(A[k], B[4 * t + k], d);
+          if (again) d = taps_only<T>(B, 4 * t, kDown, lane);
+          bad |= not_finite(d[0]);
+          // m = 8 a2 + i: f32 i = 4 (g & 1) + r, a2 = g >> 1; f64 i = g + 4 (r & 1), a2 = r >> 1
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
-          qo[(8 * t + (sizeof(T) == 4 ? r : 4 * (r & 1) + (r >> 1) * kStrip)) * ldq] = d[r];
+          for (int r = 0; r < 4; ++r)
+            qo[(8 * t + (sizeof(T) == 4 ? r : 4 * (r & 1) + (r >> 1) * kStrip)) * ldq] = d[r];
+        }
       }
-    }
+      return __any(bad) != 0;
+    };
+    if (__builtin_expect(y_pass(std::false_type{}), 0)) y_pass(std::true_type{});
     if (tid < 2 * kStrip) {
       for (int c = 0; c < qs; ++c) Q[tid * ldq + c] = T(0);
       for (int c = P0 + qs; c < ldq; ++c) Q[tid * ldq + c] = T(0);
@@ -934,40 +1009,48 @@ __global__ __launch_bounds__(back_threads<T>(), 4) void k_back_plane(
     __syncthreads();
     // x down pass: 16 rows (a2, y') per wave, half of the x' tiles
     const int T8 = (O0 + 7) >> 3, half = (T8 + 1) >> 1;
-    for (int job = wave; job < 2 * (2 * kStrip / 16); job += NW) {
-      const int row = (job >> 1) * 16 + n;
-      const T* const in = Q + row * ldq;
-      const int t0 = (job & 1) * half, t1 = min(T8, t0 + half);
-      const int a2 = row >= kStrip ? 1 : 0;
-      T* const o = OUT + 2 * a2 * och + (row - a2 * kStrip) * ldo +
-                   (sizeof(T) == 4 ? (g >> 1) * och + 4 * (g & 1) : g);
-      T B[12];
-      auto fetch = [&](int kb, int slot) {   // points 16 kb - 2 e + 4 r + g
-        const int c = 16 * kb - 2 * e + g + qs;
+    auto x_pass = [&](auto again_) {
+      constexpr bool again = decltype(again_)::value;
+      bool bad = false;
+      for (int job = wave; job < 2 * (2 * kStrip / 16); job += NW) {
+        const int row = (job >> 1) * 16 + n;
+        const T* const in = Q + row * ldq;
+        const int t0 = (job & 1) * half, t1 = min(T8, t0 + half);
+        const int a2 = row >= kStrip ? 1 : 0;
+        T* const o = OUT + 2 * a2 * och + (row - a2 * kStrip) * ldo +
+                     (sizeof(T) == 4 ? (g >> 1) * och + 4 * (g & 1) : g);
+        T B[12];
+        auto fetch = [&](int kb, int slot) {   // points 16 kb - 2 e + 4 r + g
+          const int c = 16 * kb - 2 * e + g + qs;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {   // groups of four in or outside [0, ldq)
-          const bool ok = (uint32_t)(c - g + 4 * r) < (uint32_t)ldq;
-          const T v = in[ok ? c + 4 * r : 0];
-          B[4 * slot + r] = ok ? v : T(0);
-        }
-      };
-      fetch(t0, 1);
-      fetch(t0 + 1, 2);
-      for (int t = t0; t < t1; ++t) {
+          for (int r = 0; r < 4; ++r) {   // groups of four in or outside [0, ldq)
+            const bool ok = (uint32_t)(c - g + 4 * r) < (uint32_t)ldq;
+            const T v = in[ok ? c + 4 * r : 0];
+            B[4 * slot + r] = ok ? v : T(0);
+          }
+        };
+        fetch(t0, 1);
+        fetch(t0 + 1, 2);
+        for (int t = t0; t < t1; ++t) {
 #pragma unroll
-        for (int k = 0; k < 8; ++k) B[k] = B[k + 4];
-        fetch(t + 2, 2);
-        V d = {T(0), T(0), T(0), T(0)};
+          for (int k = 0; k < 8; ++k) B[k] = B[k + 4];
+          fetch(t + 2, 2);
+          V d = {T(0), T(0), T(0), T(0)};
 #pragma unroll
-        for (int k = 0; k < 12; ++k) d = Mma<T>::mma(A[k], B[k], d);
+          for (int k = 0; !again && k < 12; ++k) d = Mma<T>::mma(A[k], B[k], d);
+          if (again) d = taps_only<T>(B, 0, kDown, lane);
+          bad |= not_finite(d[0]);
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int xp = 8 * t + (Mma<T>::row(r, g) & 7);
-          if (8 * t + 7 < O0 || xp < O0)
-            o[8 * t + (sizeof(T) == 4 ? r : 4 * (r & 1) + (r >> 1) * och)] = d[r];
+          for (int r = 0; r < 4; ++r) {
+            const int xp = 8 * t + (Mma<T>::row(r, g) & 7);
+            if (8 * t + 7 < O0 || xp < O0)
+              o[8 * t + (sizeof(T) == 4 ? r : 4 * (r & 1) + (r >> 1) * och)] = d[r];
+          }
         }
       }
-    }
+      return __any(bad) != 0;
+    };
+    if (__builtin_expect(x_pass(std::false_type{}), 0)) x_pass(std::true_type{});
   } else {
     for (int k = tid; k < 4 * och; k += NT) OUT[k] = T(0);
   }
