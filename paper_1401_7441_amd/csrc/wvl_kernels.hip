@@ -427,8 +427,10 @@ __global__ __launch_bounds__(64 * W, 8) void k_sparse_values(const SfDev* __rest
 // in registers: these are the product's operands as they stand, and the
 // product's result has its rows in the same lanes.  The order of every sum is
 // fixed by the tile's cover and K.  Columns outside [0, nsf) never match;
-// positions outside [0, knnz) are skipped.  A function that no entry of a pair
-// names does not enter that pair (its values may be infinite).
+// positions outside [0, knnz) are skipped.  Values that are not finite enter the
+// sums of the entries that name them only: a function that no entry of a pair
+// names is left out of it, and where a sum is not finite all the same it is
+// formed again entry by entry.
 // 16 x 4 x 4 points: the rows of K are scanned once per tile and pair, the
 // products cost m^2 / 2 multiply-adds per point for a cover of m (up to 340
 // functions of radius 5-7 bohr at 0.037 per bohr^3, 37 in the middle of all
@@ -514,6 +516,43 @@ __global__ __launch_bounds__(kDensThreads) void k_dens_tile(
       if (s % 2 == 1) __builtin_amdgcn_sched_barrier(0);   // few addresses at a time
     }
   };
+  // The pair's sum at the lane's point again, over the entries of T alone (a
+  // product with the other elements is zero times an infinity), where the
+  // products gave one that is not finite.  Functions that do not meet the
+  // tile's 16 x 4 x 1 points of this plane are left out, as their zeros are no
+  // values of theirs.
+  auto entries_only = [&](int jh, int ni, int nj) {
+    auto meets = [&](int h) {
+      const int x = ix * kDensTile[0] - geo[h][0], y = iy * kDensTile[1] - geo[h][1];
+      return x > -kDensTile[0] && x < geo[h][3] && y > -kDensTile[1] && y < geo[h][4] &&
+             gz >= geo[h][2] && gz < geo[h][2] + geo[h][5];
+    };
+    auto value = [&](int h) -> double {
+      const int px = gx - geo[h][0], py = gy - geo[h][1], pz = gz - geo[h][2];
+      const int R0 = geo[h][3], R1 = geo[h][4], R2 = geo[h][5];
+      if (!inside || (uint32_t)px >= (uint32_t)R0 || (uint32_t)py >= (uint32_t)R1 ||
+          (uint32_t)pz >= (uint32_t)R2)
+        return 0.0;
+      return (double)fine[fo[h] + ((int64_t)pz * R1 + py) * R0 + px];
+    };
+    double again = 0.0;
+#pragma unroll 1
+    for (int i = g; i < ni; i += 4) {   // the lane's rows
+      if (!meets(i)) continue;
+      double u = 0.0;
+      bool any = false;
+#pragma unroll 1
+      for (int j = 0; j < nj; ++j) {
+        const double t = tk[0][i * LD + j];
+        if (t == 0.0 && __builtin_signbit(t)) continue;   // no entry
+        if (!meets(jh * C + j)) continue;
+        u += t * value(jh * C + j);
+        any = true;
+      }
+      if (any) again += value(i) * u;
+    }
+    return again;
+  };
   for (int ic = 0; ic < m; ic += C) {
     const int ni = min(C, m - ic);
     stage(0, ic, ni);
@@ -557,13 +596,14 @@ __global__ __launch_bounds__(kDensThreads) void k_dens_tile(
         sq += 256;
       };
       fetch(b, kb, pa);
-      // hash of the pair's functions and an empty T
+      // hash of the pair's functions and an empty T: -0 where there is no entry
+      // (entries are added as kb + 0, never -0, so that a sum is never -0 either)
       for (int h = tid; h < kDensSlots; h += NT) hslot[h] = 0xFFFFFFFFu;
       if (tid < 2 * C) used[tid / C][tid % C] = 0;
       const int nr = (ni + 15) & ~15;
       for (int h = tid; h < nr * (LD / 2); h += NT)
         reinterpret_cast<double2*>(tk[0])[h] = reinterpret_cast<double2*>(tk[1])[h] =
-            make_double2(0.0, 0.0);
+            make_double2(-0.0, -0.0);
       __syncthreads();
       if (tid < nrow) {
         const int h = slot(tid);
@@ -587,7 +627,7 @@ __global__ __launch_bounds__(kDensThreads) void k_dens_tile(
           // an entry inside one chunk belongs to its diagonal pair
           if (p < 0 || (!diag && (p >= C) == (pa >= C))) continue;
           const int r = min(pa, p), c = max(pa, p) - (diag ? 0 : C);   // row in I, column in J
-          unsafeAtomicAdd(&tk[pa > p][r * LD + c], kb[u]);
+          unsafeAtomicAdd(&tk[pa > p][r * LD + c], kb[u] + 0.0);
           used[0][r] = 1;
           used[jh][c] = 1;
         }
@@ -611,6 +651,7 @@ __global__ __launch_bounds__(kDensThreads) void k_dens_tile(
 #pragma unroll
       for (int s = 0; s < S; ++s) pj[s] = (uj >> (4 * s)) & 1u ? pj[s] : T(0);
       const double* const ta = tk[0] + n * LD + g;
+      const double before = acc;
 #pragma unroll
       for (int st = 0; st < C / 16; ++st) {
         if (16 * st >= ni) continue;
@@ -628,6 +669,10 @@ __global__ __launch_bounds__(kDensThreads) void k_dens_tile(
 #pragma unroll
         for (int j = 0; j < 4; ++j)
           acc += (ui >> (4 * (4 * st + j))) & 1u ? (double)pi[4 * st + j] * d[j] : 0.0;
+      }
+      if (__builtin_expect(__any(!__builtin_isfinite(acc)), 0)) {
+        const double again = before + entries_only(jh, ni, nj);
+        if (!__builtin_isfinite(acc)) acc = again;
       }
       __syncthreads();   // T, the hash and the flags no longer read
     }
