@@ -276,7 +276,9 @@ __global__ __launch_bounds__(64 * W, 8) void k_sparse_values(const SfDev* __rest
                                                       int64_t nnz, double* __restrict__ val) {
   // coarse runs of a wave's rows: starts (bra, ket), lengths (0: none)
   __shared__ int32_t ea_[W][64], eb_[W][64], el_[W][64];
-  __shared__ double part[W];
+  // A batch of 64 rows adds to one of eight sums per lane, batch b to b mod 8,
+  // whatever the number of waves: a pair has the same bits in every plan.
+  __shared__ double lanes[512];
   // Workgroups are dealt to the 8 XCDs in turn: block b runs on XCD b % 8.
   // Each XCD walks its own contiguous eighth of the processing order, so the
   // pairs resident on one XCD share rows (and, rows being in spatial order,
@@ -285,7 +287,8 @@ __global__ __launch_bounds__(64 * W, 8) void k_sparse_values(const SfDev* __rest
   const int64_t s = (int64_t)(blockIdx.x % 8) * per + blockIdx.x / 8;
   if (s >= nnz) return;
   const int64_t k = order[s];
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   int32_t *const ea = ea_[wv], *const eb = eb_[wv], *const el = el_[wv];
   const int grp = lane >> 4, gl = lane & 15;
   const SfDev& A = sfs[rowi[k]];
@@ -300,8 +303,8 @@ __global__ __launch_bounds__(64 * W, 8) void k_sparse_values(const SfDev* __rest
   const int bnc = (int)(ket_out ? B.on_c : B.n_c);
   const int ny = y1 - y0 + 1;
   const int nrows = (y1 >= y0 && z1 >= z0) ? ny * (z1 - z0 + 1) : 0;
-  double acc = 0.0;
   for (int r0 = 64 * wv; r0 < nrows; r0 += 64 * W) {
+    double acc = 0.0;
     // phase 1
     const int r = r0 + lane;
     const bool in = r < nrows;
@@ -396,15 +399,19 @@ __global__ __launch_bounds__(64 * W, 8) void k_sparse_values(const SfDev* __rest
     fine_runs<T>(pbra, pket, sa0[1], sb0[1], len[1], acc);
     fine_runs<T>(pbra, pket, sa0[2], sb0[2], len[2], acc);
     wave_sync();
+    if (r0 >= 512) acc += lanes[(r0 & 448) + lane];
+    lanes[(r0 & 448) + lane] = acc;
   }
-  for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 64);
-  if (lane == 0) part[wv] = acc;
   __syncthreads();
-  if (threadIdx.x == 0) {
-    acc = 0.0;
-    for (int w = 0; w < W; ++w) acc += part[w];
-    val[k] = acc;
-    if (mirror != nullptr && mirror[s] >= 0) val[mirror[s]] = acc;
+  if (wv == 0) {
+    double sum = 0.0;
+#pragma unroll
+    for (int q = 0; q < 512; q += 64) sum += q < nrows ? lanes[q + lane] : 0.0;
+    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
+    if (lane == 0) {
+      val[k] = sum;
+      if (mirror != nullptr && mirror[s] >= 0) val[mirror[s]] = sum;
+    }
   }
 }
 
@@ -1570,9 +1577,7 @@ int launch_sparse_values(int f64, void* stream, const SfDev* sf, const wvl_seg* 
   // with two, 51 with four, 34 with eight; 120 functions (12,949) 153 / 87 /
   // 69 / 76, H 346 / 296 / 277 / 341.  With many pairs the waves of a pair read
   // the same lines together: FP64 H of 1,000 functions (303,083) 5.53 / 5.28 /
-  // 5.31 / 6.95 ms, but FP32 of 4,000 7.84 / 8.02 / 8.87 / 13.97.  The
-  // line is drawn on the entries of the pattern, not on the pairs summed, so
-  // that S has the same bits however it is called.
+  // 5.31 / 6.95 ms, but FP32 of 4,000 7.84 / 8.02 / 8.87 / 13.97.
   const int w = pairs <= 4096 ? 8 : pairs <= 32768 ? 4 : 2;
   if (f64)
     w == 8   ? go(k_sparse_values<double, 8>, w, 0.0)
