@@ -258,6 +258,7 @@ struct wvl_plan {
   int64_t layout_version = 0;         // bumped when the autotuner changes the layout
   bool in_sub_out = false;            // input patterns inside output patterns (wvl_update)
   int64_t max_in_segs = 0;            // largest input segment count of a function
+  int64_t mean_rows = 0;              // mean rows (y, z) of an input box
   SfDev* d_sf = nullptr;
   wvl_seg* d_seg = nullptr;
   int32_t* d_rt = nullptr;
@@ -1071,6 +1072,8 @@ wvl_status wvl_plan_create(wvl_ctx* ctx, int32_t nsf, const wvl_locreg* lr, cons
   }
   P->max_ws = max_workspace_bytes;
   P->in_sub_out = in_sub_out;
+  for (const SfDev& S : P->h_sf) P->mean_rows += (int64_t)S.n[1] * S.n[2];
+  P->mean_rows /= std::max(1, nsf);
   for (int k = 0; k < nsf; ++k)
     P->max_in_segs = std::max<int64_t>(P->max_in_segs, lr[k].nseg_c + lr[k].nseg_f);
   // the workspace reported covers every layout the autotuner may pick
@@ -1544,7 +1547,7 @@ wvl_status wvl_sparse_overlap(wvl_plan* P, const void* bra_c, int ket_is_output,
                                     P->d_rr, ket_is_output, bra_c, ket_c, pc.d_row, pc.d_col,
                                     half ? pc.d_order_u : pc.d_order,
                                     half ? pc.d_mirror_u : nullptr, half ? pc.nnz_u : pc.nnz,
-                                    pc.nnz, val));
+                                    P->mean_rows, val));
   }
   return WVL_OK;
 }
@@ -2176,7 +2179,7 @@ static wvl_status capture_step(wvl_plan* P, wvl_dtype dt, uint32_t terms, const 
                                          psi_c, ket_out ? hpsi_c : psi_c, pc.d_row, pc.d_col,
                                          half ? pc.d_order_u : pc.d_order,
                                          half ? pc.d_mirror_u : nullptr,
-                                         half ? pc.nnz_u : pc.nnz, pc.nnz, val);
+                                         half ? pc.nnz_u : pc.nnz, P->mean_rows, val);
       if (e != 0) st = hip_fail(ctx, "graph capture", "launch of sparse_values", (hipError_t)e);
     }
   }

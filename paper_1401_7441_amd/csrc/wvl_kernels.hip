@@ -207,9 +207,9 @@ __global__ __launch_bounds__(64) void k_pattern(const SfDev* __restrict__ sfs,
 // Bound by the latency of each wave's chain of loads and by the lines that L1
 // and L2 keep for the others (half of the requests of 1,000 functions miss L2),
 // so that registers stay below those that let eight waves run per SIMD.  H of
-// 1,000 functions of radius 5-7 bohr (303,083 entries) in FP64: 5.62 ms with
-// one wave per pair and 16 lanes per fine run, 5.28 in this form; FP32, 4,000
-// functions: 9.37 and 8.02 ms; S of 56 functions: 187 and 34 us.
+// 1,000 functions of radius 5-7 bohr (301,162 entries) in FP64: 5.63 ms with
+// one wave per pair and 16 lanes per fine run, 5.33 in this form; FP32, 4,000
+// functions: 9.31 and 7.77 ms; S of 56 functions: 112 and 31 us.
 // mirror (may be NULL): for the pair at processing position s, the CSR
 // position that receives the same value as well (the transposed pair of a
 // symmetric matrix), or -1.
@@ -303,8 +303,9 @@ __global__ __launch_bounds__(64 * W, 8) void k_sparse_values(const SfDev* __rest
   const int bnc = (int)(ket_out ? B.on_c : B.n_c);
   const int ny = y1 - y0 + 1;
   const int nrows = (y1 >= y0 && z1 >= z0) ? ny * (z1 - z0 + 1) : 0;
+  double acc = 0.0;
   for (int r0 = 64 * wv; r0 < nrows; r0 += 64 * W) {
-    double acc = 0.0;
+    acc = 0.0;
     // phase 1
     const int r = r0 + lane;
     const bool in = r < nrows;
@@ -400,17 +401,19 @@ __global__ __launch_bounds__(64 * W, 8) void k_sparse_values(const SfDev* __rest
     fine_runs<T>(pbra, pket, sa0[2], sb0[2], len[2], acc);
     wave_sync();
     if (r0 >= 512) acc += lanes[(r0 & 448) + lane];
-    lanes[(r0 & 448) + lane] = acc;
+    if (nrows > 64) lanes[(r0 & 448) + lane] = acc;
   }
-  __syncthreads();
+  if (W > 1 && nrows > 64) __syncthreads();
   if (wv == 0) {
-    double sum = 0.0;
+    if (nrows > 64) {
+      acc = 0.0;
 #pragma unroll
-    for (int q = 0; q < 512; q += 64) sum += q < nrows ? lanes[q + lane] : 0.0;
-    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
+      for (int q = 0; q < 512; q += 64) acc += q < nrows ? lanes[q + lane] : 0.0;
+    }
+    for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 64);
     if (lane == 0) {
-      val[k] = sum;
-      if (mirror != nullptr && mirror[s] >= 0) val[mirror[s]] = sum;
+      val[k] = acc;
+      if (mirror != nullptr && mirror[s] >= 0) val[mirror[s]] = acc;
     }
   }
 }
@@ -1490,7 +1493,8 @@ static inline dim3 grid2(int64_t maxvol, int nsf) {
 
 // Loads the code objects of the kernels a captured step may launch.
 int preload_kernels() {
-  const void* fns[] = {(const void*)k_finalize, (const void*)k_sparse_values<float, 2>,
+  const void* fns[] = {(const void*)k_finalize, (const void*)k_sparse_values<float, 1>,
+                       (const void*)k_sparse_values<double, 1>, (const void*)k_sparse_values<float, 2>,
                        (const void*)k_sparse_values<float, 4>, (const void*)k_sparse_values<float, 8>,
                        (const void*)k_sparse_values<double, 2>,
                        (const void*)k_sparse_values<double, 4>,
@@ -1562,7 +1566,7 @@ int launch_pattern(void* stream, const SfDev* sf, const wvl_seg* seg, const int3
 int launch_sparse_values(int f64, void* stream, const SfDev* sf, const wvl_seg* seg,
                          const int32_t* rt, const RowRun* rr, int ket_out, const void* bra,
                          const void* ket, const int32_t* row, const int32_t* col,
-                         const int32_t* order, const int32_t* mirror, int64_t nnz, int64_t pairs,
+                         const int32_t* order, const int32_t* mirror, int64_t nnz, int64_t rows,
                          double* val) {
   if (nnz == 0) return 0;
   const unsigned nblk = (unsigned)(8 * ((nnz + 7) / 8));
@@ -1572,21 +1576,38 @@ int launch_sparse_values(int f64, void* stream, const SfDev* sf, const wvl_seg* 
                        ket_out, (const T*)bra, (const T*)ket, row, col, order, mirror, nnz, val);
   };
   // Waves per pair: the chip holds 8,192 waves.  With fewer pairs than that
-  // one wave's chain of loads is the time, so a pair's rows are dealt to more:
-  // S of 56 functions (2,516 H entries, FP32) takes 139 us with one wave, 82
-  // with two, 51 with four, 34 with eight; 120 functions (12,949) 153 / 87 /
-  // 69 / 76, H 346 / 296 / 277 / 341.  With many pairs the waves of a pair read
-  // the same lines together: FP64 H of 1,000 functions (303,083) 5.53 / 5.28 /
-  // 5.31 / 6.95 ms, but FP32 of 4,000 7.84 / 8.02 / 8.87 / 13.97.
-  const int w = pairs <= 4096 ? 8 : pairs <= 32768 ? 4 : 2;
+  // one wave's chain of loads is the time, so a pair's batches of 64 rows are
+  // dealt to more: H of 56 functions (3,122 pairs, 724 rows per box, FP64) takes
+  // 194 / 128 / 125 / 120 us with 1 / 2 / 4 / 8 waves, S of 100 (3,900, FP32) 139 /
+  // 83 / 65 / 67.  With many pairs the waves of a pair read the same lines
+  // together: H of 1,000 (301,162) FP64 5.62 / 5.37 / 5.38 / 7.14 ms, FP32 3.93 /
+  // 4.04 / 4.39 / 7.03, S (82,000) 0.50 / 0.47 / 0.53 / 0.93.  A wave without a
+  // batch of its own only costs: 33 rows per box, H of 4,000 (305,559), FP32 0.54 /
+  // 0.94 / 1.69 / 3.61 ms; 95 rows, H of 9,000 (496,106), FP64 2.66 / 2.71 / 4.13 /
+  // 8.59; 155 rows, H of 7,000 (566,476) FP64 4.72 / 4.65 / 6.04 / 12.0, FP32 3.09 /
+  // 3.59.  The number of waves does not change a value.
+  int w;
+  if (rows <= 64) {
+    w = 1;
+  } else if (nnz <= 3584) {
+    w = rows <= 128 ? 2 : rows <= 256 ? 4 : 8;
+  } else if (nnz <= 32768) {
+    w = rows <= 256 ? 2 : 4;
+  } else if (f64) {
+    w = rows <= 128 ? 1 : 2;
+  } else {
+    w = rows <= 256 || (ket_out && nnz > 131072) ? 1 : 2;
+  }
   if (f64)
     w == 8   ? go(k_sparse_values<double, 8>, w, 0.0)
     : w == 4 ? go(k_sparse_values<double, 4>, w, 0.0)
-             : go(k_sparse_values<double, 2>, w, 0.0);
+    : w == 2 ? go(k_sparse_values<double, 2>, w, 0.0)
+             : go(k_sparse_values<double, 1>, w, 0.0);
   else
     w == 8   ? go(k_sparse_values<float, 8>, w, 0.0f)
     : w == 4 ? go(k_sparse_values<float, 4>, w, 0.0f)
-             : go(k_sparse_values<float, 2>, w, 0.0f);
+    : w == 2 ? go(k_sparse_values<float, 2>, w, 0.0f)
+             : go(k_sparse_values<float, 1>, w, 0.0f);
   return (int)hipGetLastError();
 }
 

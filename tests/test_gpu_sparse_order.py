@@ -69,3 +69,36 @@ def test_pair_values_are_those_of_every_plan(dtype):
     for pair in ((0, 1), (2, 5)):
         for a, b in zip(ref, values(pair, 0)):
             assert np.array_equal(a[np.ix_(pair, pair)], b), pair
+
+
+@pytest.mark.parametrize("dtype", ["float64", "float32"])
+@pytest.mark.parametrize("rows,counts", [(17, (59, 60, 84, 100, 255, 256, 363)), (15, (60, 256)),
+                                         (10, (60, 182, 256)), (6, (100,))])
+def test_every_number_of_waves(rows, counts, dtype):
+    """n boxes of 3 x rows x rows points in one place, n^2 H entries and n (n + 1) / 2
+    sums of S, around each line of the rule for the waves per pair: the Gram
+    matrices of the coefficients (FP64 1e-12 of the norms; products of FP32 values
+    are exact in double), and the three first functions' bits as in a plan of
+    their own."""
+    dt = getattr(torch, dtype)
+    box = LR.box_locreg((4, 4, 4), (3, rows, rows), (4, 5, 5), (6, rows + 1, rows + 1))
+    m = box.n_c + 7 * box.n_f
+    rng = np.random.default_rng(rows)
+    data = torch.tensor(rng.standard_normal((2, max(counts), m)), dtype=dt)
+    small = None
+    for n in (3,) + counts:
+        _print(f"case: {n} boxes of {rows * rows} rows, {dtype}")
+        plan = W.Plan(W.Context(0.45, (40, 40, 40)), *to_abi([box] * n))
+        p, h = (data[k, :n].contiguous().cuda() for k in (0, 1))
+        got = []
+        for ket, ket_out in ((p, False), (h, True)):
+            _, cl, val = W.sparse_overlap(plan, p.view(-1), ket.view(-1), ket_out)
+            assert len(cl) == n * n
+            v = val.cpu().numpy().reshape(n, n)
+            a, b = (t.double().cpu().numpy() for t in (p, ket))
+            scale = np.linalg.norm(a, axis=1)[:, None] * np.linalg.norm(b, axis=1)[None, :]
+            assert np.max(np.abs(v - a @ b.T) / scale) <= 1e-12
+            got.append(v[:3, :3].copy())
+        small = small or got
+        for a, b in zip(small, got):
+            assert np.array_equal(a, b), n
