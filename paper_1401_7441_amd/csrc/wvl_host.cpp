@@ -761,6 +761,12 @@ static int plane_bits(const SfDev& S) {
   return (plane_fits(S.n[0], S.n[1], S.n[2], S.ext, 4) ? 1 : 0) |
          (plane_fits(S.n[0], S.n[1], S.n[2], S.ext, 8) ? 2 : 0);
 }
+// and whether its back pass is the wide one in FP32 (bit 2): functions of one
+// launch agree in all three
+static int plane_class(const SfDev& S) {
+  const int bits = plane_bits(S);
+  return bits | (bits && plane_wide(S.n[0], S.n[1], S.ext) ? 4 : 0);
+}
 
 // blocks of k_back_plane per CU, FP32 and FP64
 static int back_blocks(const SfDev& S) {
@@ -801,11 +807,12 @@ static bool make_layout(const wvl_plan* P, int nbins, bool zmfma, Layout* L, std
       int j = k;
       // the matrix-core z part belongs to the column kernels; a chunk's
       // functions take the same kernels
-      const int bits = zmfma ? 0 : plane_bits(P->h_sf[order[k]]);
+      const int cls = zmfma ? 0 : plane_class(P->h_sf[order[k]]), bits = cls & 3;
+      ch.wide = cls & 4;
       ch.plane[0] = bits & 1;
       ch.plane[1] = bits & 2;
       for (; j < b1; ++j) {
-        if (!zmfma && plane_bits(P->h_sf[order[j]]) != bits) break;
+        if (!zmfma && plane_class(P->h_sf[order[j]]) != cls) break;
         // one launch has one LDS size: smaller boxes, of which more blocks fit
         // a CU, get a launch of their own where there are enough of either
         if (j - k >= kLdsSplit && b1 - j >= kLdsSplit && bits &&
@@ -1065,7 +1072,7 @@ wvl_status wvl_plan_create(wvl_ctx* ctx, int32_t nsf, const wvl_locreg* lr, cons
     for (int k = 0; k < nsf; ++k) order[k] = k;
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
       const SfDev &A = P->h_sf[a], &B = P->h_sf[b];
-      const int pa = plane_bits(A), pb = plane_bits(B);
+      const int pa = plane_class(A), pb = plane_class(B);
       if (c == 0 && pa != pb) return pa < pb;
       return (int64_t)A.n[0] * A.n[1] * A.n[2] > (int64_t)B.n[0] * B.n[1] * B.n[2];
     });
@@ -1245,8 +1252,8 @@ static wvl_status apply_chunk(wvl_plan* P, size_t c, int f64, uint32_t terms, co
                                  ch.grid_ks, (size_t)ch.lds_ks[d], workspace, fac, parts));
     WVL_LAUNCH(ctx, KK_BACK_PLANE,
                launch_back_plane(f64, st, P->d_sf, P->d_seg, P->d_rt, P->d_rr, psi_c, wk, ch.nsf,
-                                 ch.grid_bp, (size_t)ch.lds_bp[d], workspace, hpsi_c, pot_on,
-                                 kin_on, accumulate, fac, parts));
+                                 ch.grid_bp, ch.wide, (size_t)ch.lds_bp[d], workspace, hpsi_c,
+                                 pot_on, kin_on, accumulate, fac, parts));
     if ((pot_on && e_pot) || (kin_on && e_kin))
       WVL_LAUNCH(ctx, KK_FINALIZE, launch_plane_energies(f64, st, wk, ch.nsf, parts,
                                                          kin_on ? e_kin : nullptr,

@@ -98,7 +98,7 @@ __host__ __device__ constexpr int plane_ych(int n0, int n1) {                   
   return ((n1 * (pad16(2 * n0 + 29) + 4) + 15) & ~31) + 16;
 }
 constexpr int kPlaneStrip = 24;      // output rows y' per k_back_plane block
-constexpr int kPlaneThreads = 256;   // k_kin_slab, k_back_plane
+constexpr int kPlaneThreads = 256;   // k_kin_slab, k_up_kin
 __host__ __device__ constexpr int plane_strips(int o1) { return (o1 + kPlaneStrip - 1) / kPlaneStrip; }
 // dynamic LDS in elements of the compute type
 constexpr int64_t plane_lds_up(int64_t n0, int64_t n1, bool both, int sz) {
@@ -126,6 +126,13 @@ constexpr bool plane_fits(int64_t n0, int64_t n1, int64_t n2, int64_t e, int sz)
          sz * plane_lds_kin(n0, n2) <= kPlaneLds && sz * plane_lds_back(n0, n1, e) <= kPlaneLds;
 }
 
+// Whether k_back_plane takes a function with more threads in FP32: where a block's LDS
+// leaves room for one block per CU (58 points per axis and more, ext 8).
+constexpr int kWideThreads = 1024;
+constexpr bool plane_wide(int64_t n0, int64_t n1, int64_t e) {
+  return 4 * plane_lds_back(n0, n1, e) > 80 * 1024 - 2048;
+}
+
 // per-chunk launch geometry of the fused kernels, for dtype d (0 f32, 1 f64)
 struct ChunkDev {
   int32_t sf0, nsf;                // positions [sf0, sf0 + nsf) of the processing order
@@ -141,6 +148,7 @@ struct ChunkDev {
   // plane kernels, per type (0 f32, 1 f64): whether the chunk's functions take
   // them, dynamic LDS in bytes, both a2 at once in k_up_plane
   bool plane[2];
+  bool wide;           // k_back_plane in FP32, see plane_wide
   int32_t up_both[2];
   int64_t lds_up[2], lds_ks[2], lds_bp[2];
   int32_t grid_up, grid_ct, grid_ks, grid_bp;
@@ -218,8 +226,8 @@ int launch_kin_slab(int f64, void* stream, const SfDev* sf, const wvl_seg* seg, 
                     size_t lds, void* ws, double fac, double* kpart);
 int launch_back_plane(int f64, void* stream, const SfDev* sf, const wvl_seg* seg,
                       const int32_t* rt, const RowRun* rr, const void* psi, const SfWork* wk,
-                      int nsf, int gridx, size_t lds, const void* ws, void* out, int pot_on,
-                      int kin_on, int accumulate, double fac, double* kpart);
+                      int nsf, int gridx, int wide, size_t lds, const void* ws, void* out,
+                      int pot_on, int kin_on, int accumulate, double fac, double* kpart);
 int launch_plane_energies(int f64, void* stream, const SfWork* wk, int nsf, const double* parts,
                           double* e_kin, double* e_pot);
 int launch_finalize(void* stream, const SfWork* wk, int sf0, int nsf, const double* parts,

@@ -904,18 +904,22 @@ __global__ __launch_bounds__(kPlaneThreads, sizeof(T) == 4 ? 4 : 2) void k_up_ki
 // two (FP64) blocks per CU at the usual box sizes; the phases of one block are
 // covered by the others.
 // FP64 planes fill half a CU's LDS or more: twice the waves per block keep
-// four per SIMD
-template <typename T> constexpr int back_threads() { return sizeof(T) == 4 ? 256 : 512; }
+// four per SIMD.  WIDE, FP32 where one block fills a CU's LDS (plane_wide): 1,024
+// threads for 256, so that its phases are not four waves' on their own (60 boxes
+// of 60^3 points: 4.59 -> 3.08 ms, one of 58^3 85 -> 60 us).
+template <typename T> constexpr int back_threads(bool wide) {
+  return sizeof(T) == 8 ? 512 : wide ? kWideThreads : 256;
+}
 constexpr int kStrip = kPlaneStrip;
 constexpr int kRowWords = 2;   // O0 <= kPlaneMaxN + 32 points per row
-template <typename T>
-__global__ __launch_bounds__(back_threads<T>(), 4) void k_back_plane(
+template <typename T, bool WIDE>
+__global__ __launch_bounds__(back_threads<T>(WIDE), 4) void k_back_plane(
     const SfDev* __restrict__ sfs, const wvl_seg* __restrict__ seg,
     const int32_t* __restrict__ rt, const RowRun* __restrict__ rr, const T* __restrict__ psi,
     const SfWork* __restrict__ wk, const T* __restrict__ ws, T* __restrict__ out, int pot_on,
     int kin_on, int accumulate, double fac, double* __restrict__ kpart) {
   extern __shared__ __align__(32) unsigned char smem_raw[];
-  constexpr int NT = back_threads<T>(), NW = NT / 64;
+  constexpr int NT = back_threads<T>(WIDE), NW = NT / 64;
   constexpr uint32_t SZ = sizeof(T);
   const SfWork& w = wk[blockIdx.y];
   const SfDev& sf = sfs[w.id];
@@ -1211,7 +1215,8 @@ int preload_plane_kernels() {
   const void* lds[] = {(const void*)k_up_plane_valu,     (const void*)k_up_plane,
                        (const void*)k_kin_slab<float>,   (const void*)k_kin_slab<double>,
                        (const void*)k_up_kin<float>,     (const void*)k_up_kin<double>,
-                       (const void*)k_back_plane<float>, (const void*)k_back_plane<double>};
+                       (const void*)k_back_plane<float, false>, (const void*)k_back_plane<float, true>,
+                       (const void*)k_back_plane<double, false>};
   hipError_t e = hipSuccess;
   hipFuncAttributes a;
   for (const void* f : fns)
@@ -1288,18 +1293,22 @@ int launch_kin_slab(int f64, void* stream, const SfDev* sf, const wvl_seg* seg, 
 
 int launch_back_plane(int f64, void* stream, const SfDev* sf, const wvl_seg* seg,
                       const int32_t* rt, const RowRun* rr, const void* psi, const SfWork* wk,
-                      int nsf, int gridx, size_t lds, const void* ws, void* out, int pot_on,
-                      int kin_on, int accumulate, double fac, double* kpart) {
+                      int nsf, int gridx, int wide, size_t lds, const void* ws, void* out,
+                      int pot_on, int kin_on, int accumulate, double fac, double* kpart) {
   if (nsf == 0 || gridx == 0) return 0;
   const dim3 g((unsigned)gridx, (unsigned)nsf);
+  hipStream_t st = (hipStream_t)stream;
+  auto go = [&](auto kernel, int threads, auto t) {
+    using T = decltype(t);
+    hipLaunchKernelGGL(kernel, g, dim3(threads), lds, st, sf, seg, rt, rr, (const T*)psi, wk,
+                       (const T*)ws, (T*)out, pot_on, kin_on, accumulate, fac, kpart);
+  };
   if (f64)
-    hipLaunchKernelGGL(k_back_plane<double>, g, dim3(back_threads<double>()), lds, (hipStream_t)stream, sf,
-                       seg, rt, rr, (const double*)psi, wk, (const double*)ws, (double*)out,
-                       pot_on, kin_on, accumulate, fac, kpart);
+    go(k_back_plane<double, false>, back_threads<double>(false), 0.0);
+  else if (wide)
+    go(k_back_plane<float, true>, back_threads<float>(true), 0.0f);
   else
-    hipLaunchKernelGGL(k_back_plane<float>, g, dim3(back_threads<float>()), lds, (hipStream_t)stream, sf,
-                       seg, rt, rr, (const float*)psi, wk, (const float*)ws, (float*)out, pot_on,
-                       kin_on, accumulate, fac, kpart);
+    go(k_back_plane<float, false>, back_threads<float>(false), 0.0f);
   return (int)hipGetLastError();
 }
 
