@@ -395,11 +395,10 @@ wvl_status wvl_precondition(wvl_plan* plan, wvl_dtype dt, const void* g_c, const
  * its own localization region only).  A plan sorts the functions by box
  * volume and cuts them into bins; every bin runs each stage as one launch
  * over all its functions.  Without a workspace bound the bins use disjoint
- * workspace regions and are independent.
+ * workspace regions.
  *
  * wvl_graph_create captures one step into a HIP graph: the local-H apply of
- * every function (independent bins as parallel branches, on streams the plan
- * owns), then, when s_val / h_val are non-NULL, the overlap values (bra =
+ * every function (the bins one after the other, in one linear graph), then, when s_val / h_val are non-NULL, the overlap values (bra =
  * ket = psi_c) and the Hamiltonian values (bra psi_c, ket hpsi_c) on the
  * plan's patterns, in the CSR order wvl_sparse_overlap reports.  Arguments
  * are those of wvl_apply_local_ham; every buffer must stay valid while the

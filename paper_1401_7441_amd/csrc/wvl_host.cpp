@@ -167,9 +167,8 @@ inline uint32_t morton3(uint32_t x, uint32_t y, uint32_t z) {
 // Workspace layout of a plan: the functions in processing order (sorted by
 // box volume, largest first), cut into `nbins` bins of equal count; a bin is
 // split further into chunks when a workspace bound is given.  Without a
-// bound every chunk has its own workspace region (chunks are independent and
-// may run concurrently); with one, chunks reuse the region one after the
-// other.
+// bound every chunk has its own workspace region; with one, chunks reuse the
+// region one after the other.
 struct Layout {
   std::vector<ChunkDev> chunks;
   std::vector<SfWork> wk;        // per position of the processing order
@@ -186,7 +185,6 @@ struct wvl_graph {
   int64_t layout_version = 0;
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
-  std::vector<hipEvent_t> events;   // fork/join events of the capture, kept with the graph
 };
 
 // Chebyshev coefficients c_0..c_npl on [-1, 1] of
@@ -254,7 +252,7 @@ struct wvl_plan {
   size_t max_ws = 0;                  // the caller's workspace bound (0: none)
   Layout lay;
   int64_t ws_cap[2] = {0, 0};         // workspace bytes reported (F32, F64)
-  std::vector<hipStream_t> streams;   // branch streams of captured graphs
+  hipStream_t capture = nullptr;      // the stream that graphs are captured on
   int64_t layout_version = 0;         // bumped when the autotuner changes the layout
   bool in_sub_out = false;            // input patterns inside output patterns (wvl_update)
   int64_t max_in_segs = 0;            // largest input segment count of a function
@@ -708,7 +706,7 @@ void wvl_plan_destroy(wvl_plan* plan) {
   if (plan->d_wk) (void)hipFree(plan->d_wk);
   free_pattern(plan->pat[0]);
   free_pattern(plan->pat[1]);
-  for (hipStream_t st : plan->streams) (void)hipStreamDestroy(st);
+  if (plan->capture) (void)hipStreamDestroy(plan->capture);
   delete plan;
 }
 
@@ -2114,68 +2112,31 @@ wvl_status wvl_precondition(wvl_plan* P, wvl_dtype dt, const void* g_c, const do
   return WVL_OK;
 }
 
-// Captures the apply (and optional S/H values) into G.  Chunks with
-// disjoint workspace go to parallel branches.
+// Captures the apply (and optional S/H values) into G, one chunk after the
+// other on one stream.  (Bins on parallel branches made hipGraphLaunch crash the
+// process on the host when graphs were captured, launched and destroyed a few
+// dozen times; a linear graph never did.)
 static wvl_status capture_step(wvl_plan* P, wvl_dtype dt, uint32_t terms, const void* psi_c,
                                const void* pot, void* hpsi_c, double* e_kin, double* e_pot,
                                void* workspace, double* s_val, double* h_val, wvl_graph* G) {
   wvl_ctx* ctx = P->ctx;
   const int f64 = dt == WVL_F64;
-  const size_t nch = P->lay.chunks.size();
   // kernels are loaded lazily on first use; a load (which also uploads the
   // constant filter tables) must not happen inside the capture
   if (const int pe = preload_all(); pe != 0)
     return hip_fail(ctx, "graph capture", "kernel preload (hipFuncGetAttributes)",
                     (hipError_t)pe);
-  const size_t nbr = P->lay.disjoint ? std::min<size_t>(nch, 4) : 0;
-  // streams[0] is the capture origin (the context's stream may be the
-  // legacy default stream, which cannot be captured); 1.. are branches
-  while (P->streams.size() < nbr + 1) {
-    hipStream_t st = nullptr;
-    WVL_HIP(ctx, hipStreamCreateWithFlags(&st, hipStreamNonBlocking));
-    P->streams.push_back(st);
-  }
-  std::vector<hipEvent_t>& ev = G->events;
-  auto cleanup = [&]() {
-    for (hipEvent_t e : ev) (void)hipEventDestroy(e);
-    ev.clear();
-  };
-  for (size_t k = 0; k < nbr + 1; ++k) {
-    hipEvent_t e = nullptr;
-    if (hipError_t he = hipEventCreateWithFlags(&e, hipEventDisableTiming); he != hipSuccess) {
-      cleanup();
-      return hip_fail(ctx, "graph capture", "hipEventCreateWithFlags", he);
-    }
-    ev.push_back(e);
-  }
+  // the context's stream may be the legacy default stream, which cannot be captured
+  if (!P->capture) WVL_HIP(ctx, hipStreamCreateWithFlags(&P->capture, hipStreamNonBlocking));
   const bool prof = ctx->prof;
   ctx->prof = false;   // no tracing events inside a graph
-  hipStream_t cs = P->streams[0];
+  hipStream_t cs = P->capture;
   hipError_t he = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
   wvl_status st = he == hipSuccess ? WVL_OK
                                    : hip_fail(ctx, "graph capture", "hipStreamBeginCapture", he);
-  // fork/join steps: the first failing call ends the capture with its name
-  auto step = [&](hipError_t e, const char* call) {
-    if (st == WVL_OK && e != hipSuccess) st = hip_fail(ctx, "graph capture", call, e);
-  };
   if (st == WVL_OK && P->nsf > 0) {
-    if (nbr > 0) {
-      // fork: every branch waits for the capture origin
-      step(hipEventRecord(ev[0], cs), "hipEventRecord (fork)");
-      for (size_t b = 0; st == WVL_OK && b < nbr; ++b)
-        step(hipStreamWaitEvent(P->streams[b + 1], ev[0], 0), "hipStreamWaitEvent (fork)");
-      for (size_t c = 0; st == WVL_OK && c < nch; ++c)
-        st = apply_chunk(P, c, f64, terms, psi_c, pot, hpsi_c, e_kin, e_pot, workspace, 0,
-                         P->streams[1 + c % nbr]);
-      // join
-      for (size_t b = 0; st == WVL_OK && b < nbr; ++b) {
-        step(hipEventRecord(ev[b + 1], P->streams[b + 1]), "hipEventRecord (join)");
-        if (st == WVL_OK) step(hipStreamWaitEvent(cs, ev[b + 1], 0), "hipStreamWaitEvent (join)");
-      }
-    } else {
-      for (size_t c = 0; st == WVL_OK && c < nch; ++c)
-        st = apply_chunk(P, c, f64, terms, psi_c, pot, hpsi_c, e_kin, e_pot, workspace, 0, cs);
-    }
+    for (size_t c = 0; st == WVL_OK && c < P->lay.chunks.size(); ++c)
+      st = apply_chunk(P, c, f64, terms, psi_c, pot, hpsi_c, e_kin, e_pot, workspace, 0, cs);
     for (int ket_out = 0; st == WVL_OK && ket_out < 2; ++ket_out) {
       double* val = ket_out ? h_val : s_val;
       const PatternCache& pc = P->pat[ket_out];
@@ -2199,14 +2160,12 @@ static wvl_status capture_step(wvl_plan* P, wvl_dtype dt, uint32_t terms, const 
   ctx->prof = prof;
   if (st != WVL_OK) {
     if (g) (void)hipGraphDestroy(g);
-    cleanup();
     return st;
   }
   hipGraphExec_t x = nullptr;
   he = hipGraphInstantiate(&x, g, nullptr, nullptr, 0);
   if (he != hipSuccess) {
     (void)hipGraphDestroy(g);
-    cleanup();
     return hip_fail(ctx, "graph capture", "hipGraphInstantiate", he);
   }
   G->plan = P;
@@ -2251,7 +2210,6 @@ void wvl_graph_destroy(wvl_graph* G) {
   if (!G) return;
   if (G->exec) (void)hipGraphExecDestroy(G->exec);
   if (G->graph) (void)hipGraphDestroy(G->graph);
-  for (hipEvent_t e : G->events) (void)hipEventDestroy(e);
   delete G;
 }
 
