@@ -749,7 +749,7 @@ struct PartSlots {
       kz = std::max<int64_t>(kz, kin_blocks(2, S.n[0], S.n[1], S.n[2], zmfma));
     }
     if (bits != 0)
-      kpl = std::max<int64_t>(kpl, 2ll * S.n[2] * plane_strips(S.n[1] + 2 * S.ext) + 2 * S.n[1]);
+      kpl = std::max<int64_t>(kpl, 2ll * S.n[2] * plane_strips(S.n[0], S.n[1], S.ext) + 2 * S.n[1]);
   }
   int64_t kin() const { return std::max(kx + ky + kz, kpl); }
 };
@@ -759,11 +759,13 @@ static int plane_bits(const SfDev& S) {
   return (plane_fits(S.n[0], S.n[1], S.n[2], S.ext, 4) ? 1 : 0) |
          (plane_fits(S.n[0], S.n[1], S.n[2], S.ext, 8) ? 2 : 0);
 }
-// and whether its back pass is the wide one in FP32 (bit 2): functions of one
-// launch agree in all three
+// and the form of its back pass: wide in FP32 (bit 2), 32 rows per block (bit 3);
+// functions of one launch agree in all four
 static int plane_class(const SfDev& S) {
   const int bits = plane_bits(S);
-  return bits | (bits && plane_wide(S.n[0], S.n[1], S.ext) ? 4 : 0);
+  if (bits == 0) return 0;
+  return bits | (plane_wide(S.n[0], S.n[1], S.ext) ? 4 : 0) |
+         (plane_strip(S.n[0], S.n[1], S.ext) == 32 ? 8 : 0);
 }
 
 // blocks of k_back_plane per CU, FP32 and FP64
@@ -807,6 +809,7 @@ static bool make_layout(const wvl_plan* P, int nbins, bool zmfma, Layout* L, std
       // functions take the same kernels
       const int cls = zmfma ? 0 : plane_class(P->h_sf[order[k]]), bits = cls & 3;
       ch.wide = cls & 4;
+      ch.strip = cls & 8 ? 32 : 24;
       ch.plane[0] = bits & 1;
       ch.plane[1] = bits & 2;
       for (; j < b1; ++j) {
@@ -864,7 +867,7 @@ static bool make_layout(const wvl_plan* P, int nbins, bool zmfma, Layout* L, std
         }
         off += sf_elems(S, bits);
         // plane kernels: partials counted on the function's own box
-        const int ns = plane_strips((int)o1);
+        const int ns = plane_strips((int)n0, (int)n1, (int)e);
         W.nepart_pl[0] = (r0 * r1 + 255) / 256;
         W.nepart_pl[1] = (r1 * (p0 / 16) + 3) / 4;
         W.nkpart_pl = 2 * n2 * ns + 2 * n1;
@@ -1250,7 +1253,7 @@ static wvl_status apply_chunk(wvl_plan* P, size_t c, int f64, uint32_t terms, co
                                  ch.grid_ks, (size_t)ch.lds_ks[d], workspace, fac, parts));
     WVL_LAUNCH(ctx, KK_BACK_PLANE,
                launch_back_plane(f64, st, P->d_sf, P->d_seg, P->d_rt, P->d_rr, psi_c, wk, ch.nsf,
-                                 ch.grid_bp, ch.wide, (size_t)ch.lds_bp[d], workspace, hpsi_c,
+                                 ch.grid_bp, ch.wide, ch.strip, (size_t)ch.lds_bp[d], workspace, hpsi_c,
                                  pot_on, kin_on, accumulate, fac, parts));
     if ((pot_on && e_pot) || (kin_on && e_kin))
       WVL_LAUNCH(ctx, KK_FINALIZE, launch_plane_energies(f64, st, wk, ch.nsf, parts,

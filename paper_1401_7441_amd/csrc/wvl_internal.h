@@ -97,9 +97,8 @@ __host__ __device__ constexpr int plane_ldx(int n0) { return ((n0 + 3) & ~7) + 4
 __host__ __device__ constexpr int plane_ych(int n0, int n1) {                          // 16 (mod 32)
   return ((n1 * (pad16(2 * n0 + 29) + 4) + 15) & ~31) + 16;
 }
-constexpr int kPlaneStrip = 24;      // output rows y' per k_back_plane block
 constexpr int kPlaneThreads = 256;   // k_kin_slab, k_up_kin
-__host__ __device__ constexpr int plane_strips(int o1) { return (o1 + kPlaneStrip - 1) / kPlaneStrip; }
+constexpr int64_t kPlaneLds = 160 * 1024 - 4096;   // dynamic LDS of a block at most
 // dynamic LDS in elements of the compute type
 constexpr int64_t plane_lds_up(int64_t n0, int64_t n1, bool both, int sz) {
   return sz == 4 ? 4 + 2 * n1 * (2 * n0 + 1) + n1 * (4 * n0 + 59)
@@ -109,17 +108,36 @@ __host__ __device__ constexpr int plane_kin_elems(int n0, int rows) {   // 4-ali
   return (4 + rows * (4 * n0 + 1) + 3) & ~3;
 }
 constexpr int64_t plane_lds_kin(int64_t n0, int64_t n2) { return plane_kin_elems((int)n0, (int)n2); }
+__host__ __device__ constexpr int64_t plane_lds_back(int64_t n0, int64_t n1, int64_t e, int64_t rows) {
+  const int64_t q = 2 * rows * (pad16((int)(2 * n0 + 29)) + 4), x = plane_kin_elems((int)n0, (int)n1);
+  return (q > x ? q : x) + 4 * rows * ((n0 + 2 * e) | 1);
+}
+// Output rows y' per k_back_plane block: 24; 32 where these are all (a second
+// block for the last few rows costs as much as the first: a block's time is the
+// latency of its phases), unless that takes the box past the LDS of a CU in a
+// type.  300 boxes of 12^3 points: 1.00 -> 0.69 ms in FP32, 1.71 -> 1.20 in FP64;
+// 40 of 96 x 10 x 30 in FP32 1.21 -> 0.59.
+__host__ __device__ constexpr bool plane_strip_lds(int n0, int n1, int e, int rows, int sz) {
+  return sz * plane_lds_back(n0, n1, e, rows) <= kPlaneLds;
+}
+__host__ __device__ constexpr int plane_strip(int n0, int n1, int e) {
+  const int o1 = n1 + 2 * e;
+  return o1 > 24 && o1 <= 32 &&
+                 (plane_strip_lds(n0, n1, e, 32, 4) || !plane_strip_lds(n0, n1, e, 24, 4)) &&
+                 (plane_strip_lds(n0, n1, e, 32, 8) || !plane_strip_lds(n0, n1, e, 24, 8))
+             ? 32 : 24;
+}
+__host__ __device__ constexpr int plane_strips(int n0, int n1, int e) {
+  return (n1 + 2 * e + plane_strip(n0, n1, e) - 1) / plane_strip(n0, n1, e);
+}
 constexpr int64_t plane_lds_back(int64_t n0, int64_t n1, int64_t e) {
-  const int64_t q = 2 * kPlaneStrip * (pad16((int)(2 * n0 + 29)) + 4),
-                x = plane_kin_elems((int)n0, (int)n1);
-  return (q > x ? q : x) + 4 * kPlaneStrip * ((n0 + 2 * e) | 1);
+  return plane_lds_back(n0, n1, e, plane_strip((int)n0, (int)n1, (int)e));
 }
 // Whether a function of this box takes the plane kernels in an element type
 // of sz bytes: its planes fit the LDS of a CU (160 KiB, less the static
 // part).  In FP64 boxes of up to about 50 points per axis do, in FP32 of
 // about 70.  The rule looks at the function's own box only, so that results
 // do not depend on the other functions of a plan.
-constexpr int64_t kPlaneLds = 160 * 1024 - 4096;
 constexpr int kPlaneMaxN = 96;    // bits of k_back_plane's row masks
 constexpr bool plane_fits(int64_t n0, int64_t n1, int64_t n2, int64_t e, int sz) {
   return n0 <= kPlaneMaxN && n1 <= kPlaneMaxN && n2 <= kPlaneMaxN && sz * plane_lds_up(n0, n1, false, sz) <= kPlaneLds &&
@@ -149,6 +167,7 @@ struct ChunkDev {
   // them, dynamic LDS in bytes, both a2 at once in k_up_plane
   bool plane[2];
   bool wide;           // k_back_plane in FP32, see plane_wide
+  int32_t strip;       // its rows per block, see plane_strip
   int32_t up_both[2];
   int64_t lds_up[2], lds_ks[2], lds_bp[2];
   int32_t grid_up, grid_ct, grid_ks, grid_bp;
@@ -226,7 +245,7 @@ int launch_kin_slab(int f64, void* stream, const SfDev* sf, const wvl_seg* seg, 
                     size_t lds, void* ws, double fac, double* kpart);
 int launch_back_plane(int f64, void* stream, const SfDev* sf, const wvl_seg* seg,
                       const int32_t* rt, const RowRun* rr, const void* psi, const SfWork* wk,
-                      int nsf, int gridx, int wide, size_t lds, const void* ws, void* out,
+                      int nsf, int gridx, int wide, int strip, size_t lds, const void* ws, void* out,
                       int pot_on, int kin_on, int accumulate, double fac, double* kpart);
 int launch_plane_energies(int f64, void* stream, const SfWork* wk, int nsf, const double* parts,
                           double* e_kin, double* e_pot);

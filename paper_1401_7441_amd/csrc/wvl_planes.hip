@@ -850,7 +850,7 @@ __device__ __forceinline__ void kin_slab(int bx, const SfDev* __restrict__ sfs,
     }
   }
   const double b = plane_block_sum(eacc);
-  if (threadIdx.x == 0) kpart[w.kpart + 2 * N2 * plane_strips(N1 + 2 * e) + bx] = b;
+  if (threadIdx.x == 0) kpart[w.kpart + 2 * N2 * plane_strips(N0, N1, e) + bx] = b;
 }
 
 __global__ __launch_bounds__(256) void k_up_plane(
@@ -891,7 +891,7 @@ __global__ __launch_bounds__(kPlaneThreads, sizeof(T) == 4 ? 4 : 2) void k_up_ki
 }
 
 // ---------------------------------------------------------------------------
-// k_back_plane: block = (function, z', a3, strip of 24 rows y')
+// k_back_plane: block = (function, z', a3, strip of 24 or 32 rows y')
 // ---------------------------------------------------------------------------
 // G2 -> y down pass -> Q[a2][row][px] in LDS -> x down pass ->
 // OUT[a1 + 2 a2][row][x'] in LDS; then the plane z = z' - ext is uncompressed
@@ -910,9 +910,8 @@ __global__ __launch_bounds__(kPlaneThreads, sizeof(T) == 4 ? 4 : 2) void k_up_ki
 template <typename T> constexpr int back_threads(bool wide) {
   return sizeof(T) == 8 ? 512 : wide ? kWideThreads : 256;
 }
-constexpr int kStrip = kPlaneStrip;
 constexpr int kRowWords = 2;   // O0 <= kPlaneMaxN + 32 points per row
-template <typename T, bool WIDE>
+template <typename T, bool WIDE, int kStrip>
 __global__ __launch_bounds__(back_threads<T>(WIDE), 4) void k_back_plane(
     const SfDev* __restrict__ sfs, const wvl_seg* __restrict__ seg,
     const int32_t* __restrict__ rt, const RowRun* __restrict__ rr, const T* __restrict__ psi,
@@ -927,7 +926,7 @@ __global__ __launch_bounds__(back_threads<T>(WIDE), 4) void k_back_plane(
   const int R1 = 2 * N1 + 29, P0 = pad16(2 * N0 + 29);
   const int O0 = N0 + 2 * e, O1 = N1 + 2 * e, O2 = N2 + 2 * e;
   // blocks are dealt to the 8 XCDs in turn (gridDim.x is a multiple of 8)
-  const int NS = plane_strips(O1), per = 2 * NS, bj = blockIdx.x >> 3;
+  const int NS = (O1 + kStrip - 1) / kStrip, per = 2 * NS, bj = blockIdx.x >> 3;
   const int zp = 8 * (bj / per) + (blockIdx.x & 7);
   if (zp >= O2) return;   // uniform over the block
   const int a3 = (bj % per) & 1, strip = (bj % per) >> 1;
@@ -1215,8 +1214,12 @@ int preload_plane_kernels() {
   const void* lds[] = {(const void*)k_up_plane_valu,     (const void*)k_up_plane,
                        (const void*)k_kin_slab<float>,   (const void*)k_kin_slab<double>,
                        (const void*)k_up_kin<float>,     (const void*)k_up_kin<double>,
-                       (const void*)k_back_plane<float, false>, (const void*)k_back_plane<float, true>,
-                       (const void*)k_back_plane<double, false>};
+                       (const void*)k_back_plane<float, false, 24>,
+                       (const void*)k_back_plane<float, false, 32>,
+                       (const void*)k_back_plane<float, true, 24>,
+                       (const void*)k_back_plane<float, true, 32>,
+                       (const void*)k_back_plane<double, false, 24>,
+                       (const void*)k_back_plane<double, false, 32>};
   hipError_t e = hipSuccess;
   hipFuncAttributes a;
   for (const void* f : fns)
@@ -1293,7 +1296,7 @@ int launch_kin_slab(int f64, void* stream, const SfDev* sf, const wvl_seg* seg, 
 
 int launch_back_plane(int f64, void* stream, const SfDev* sf, const wvl_seg* seg,
                       const int32_t* rt, const RowRun* rr, const void* psi, const SfWork* wk,
-                      int nsf, int gridx, int wide, size_t lds, const void* ws, void* out,
+                      int nsf, int gridx, int wide, int strip, size_t lds, const void* ws, void* out,
                       int pot_on, int kin_on, int accumulate, double fac, double* kpart) {
   if (nsf == 0 || gridx == 0) return 0;
   const dim3 g((unsigned)gridx, (unsigned)nsf);
@@ -1304,11 +1307,14 @@ int launch_back_plane(int f64, void* stream, const SfDev* sf, const wvl_seg* seg
                        (const T*)ws, (T*)out, pot_on, kin_on, accumulate, fac, kpart);
   };
   if (f64)
-    go(k_back_plane<double, false>, back_threads<double>(false), 0.0);
+    strip == 24 ? go(k_back_plane<double, false, 24>, back_threads<double>(false), 0.0)
+                : go(k_back_plane<double, false, 32>, back_threads<double>(false), 0.0);
   else if (wide)
-    go(k_back_plane<float, true>, back_threads<float>(true), 0.0f);
+    strip == 24 ? go(k_back_plane<float, true, 24>, back_threads<float>(true), 0.0f)
+                : go(k_back_plane<float, true, 32>, back_threads<float>(true), 0.0f);
   else
-    go(k_back_plane<float, false>, back_threads<float>(false), 0.0f);
+    strip == 24 ? go(k_back_plane<float, false, 24>, back_threads<float>(false), 0.0f)
+                : go(k_back_plane<float, false, 32>, back_threads<float>(false), 0.0f);
   return (int)hipGetLastError();
 }
 

@@ -1,8 +1,10 @@
 """The forms of the back pass on either side of their lines, alone and mixed in
 one plan: in FP32 boxes whose blocks leave room for one per CU take more threads
-(57 and 58 points per axis at ext 8, 64 x 64 x 4).  Against the oracle with the
-bounds of the other parity tests (FP64 1e-12, FP32 1e-5 per function), and each
-function of the mixed plan bit for bit as alone, also cut into bins."""
+(57 and 58 points per axis at ext 8, 64 x 64 x 4); boxes of 25 to 32 output rows
+take them in one block (not 64 x 16 x 3, which FP64 could no longer take).  Against
+the oracle with the bounds of the other parity tests (FP64 1e-12, FP32 1e-5 per
+function), and each function of the mixed plan bit for bit as alone, also cut into
+bins."""
 import numpy as np
 import pytest
 
@@ -19,7 +21,9 @@ if torch.cuda.is_available():
 
 # dims, ext
 BOXES = [((57, 57, 3), 8), ((58, 58, 3), 8), ((64, 64, 4), 8), ((96, 30, 2), 8), ((20, 21, 5), 8),
-         ((60, 59, 2), 0), ((30, 33, 4), 3)]
+         ((60, 59, 2), 0), ((30, 33, 4), 3),
+         ((20, 8, 5), 8), ((20, 9, 5), 8), ((9, 16, 5), 8), ((20, 17, 4), 8), ((96, 10, 3), 8),
+         ((64, 16, 3), 8), ((30, 32, 4), 0), ((31, 25, 4), 0), ((17, 26, 5), 3), ((1, 27, 1), 2)]
 
 
 @pytest.fixture(scope="module")
