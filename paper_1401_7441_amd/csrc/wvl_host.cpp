@@ -264,8 +264,9 @@ struct wvl_plan {
   SfWork* d_wk = nullptr;
   int64_t* d_foff = nullptr;          // fine-box offsets (wvl_synthesize), function order
   int64_t max_fine = 0;               // largest fine box (elements)
-  int64_t* d_cptr = nullptr;          // density: functions meeting each k_dens_tile tile
-  int32_t* d_csf = nullptr;
+  DensTile* d_tiles = nullptr;        // density: k_dens_tile's tiles in launch order
+  int32_t* d_csf = nullptr;           // and the functions that meet them
+  int64_t dens_heavy = 0;             // how many of these
   wvl_plan_info info{};
   PatternCache pat[2];
   std::unique_ptr<FoeCoef> foe_coef;  // Chebyshev node table of the last wvl_foe degree
@@ -699,7 +700,7 @@ void wvl_plan_destroy(wvl_plan* plan) {
   if (plan->d_sf) (void)hipFree(plan->d_sf);
   if (plan->d_seg) (void)hipFree(plan->d_seg);
   if (plan->d_foff) (void)hipFree(plan->d_foff);
-  if (plan->d_cptr) (void)hipFree(plan->d_cptr);
+  if (plan->d_tiles) (void)hipFree(plan->d_tiles);
   if (plan->d_csf) (void)hipFree(plan->d_csf);
   if (plan->d_rt) (void)hipFree(plan->d_rt);
   if (plan->d_rr) (void)hipFree(plan->d_rr);
@@ -1597,7 +1598,7 @@ wvl_status wvl_synthesize(wvl_plan* P, wvl_dtype dt, const void* psi_c, void* fi
 
 // functions whose fine box meets each k_dens_tile tile, increasing index
 static wvl_status ensure_cover(wvl_plan* P) {
-  if (P->d_cptr) return WVL_OK;
+  if (P->d_tiles) return WVL_OK;
   wvl_ctx* ctx = P->ctx;
   int gf[3], nt[3];
   for (int a = 0; a < 3; ++a) {
@@ -1653,17 +1654,31 @@ static wvl_status ensure_cover(wvl_plan* P) {
                 (long long)maxc, kDensMaxCover);
   if (P->nsf >= (1 << 24))   // the tile kernel's lookup keys hold 24-bit indices
     return fail(ctx, WVL_EUNSUPPORTED, "density: more than 2^24 - 1 functions");
+  // tiles of the most chunks first, so that no long one is left for the end,
+  // those of at most kDensLight functions last; otherwise in grid order
+  constexpr int kClasses = (4 * kDensMaxCover + 63) / 64 + 1;   // by chunks of 64
+  auto klass = [&](int64_t t) {
+    const int64_t m = cptr[t + 1] - cptr[t];
+    return m <= kDensLight ? kClasses : kClasses - 1 - (int)std::min<int64_t>(kClasses - 1, (m + 63) / 64);
+  };
+  std::vector<int64_t> at(kClasses + 2, 0);
+  for (int64_t t = 0; t < ntile; ++t) ++at[klass(t) + 1];
+  for (int k = 0; k <= kClasses; ++k) at[k + 1] += at[k];
+  P->dens_heavy = at[kClasses];
+  std::vector<DensTile> tiles(ntile);
+  for (int64_t t = 0; t < ntile; ++t)
+    tiles[at[klass(t)]++] = DensTile{(int32_t)t, (int32_t)(cptr[t + 1] - cptr[t]), cptr[t]};
   auto drop = [&]() {
-    for (void** p : {(void**)&P->d_cptr, (void**)&P->d_csf})
+    for (void** p : {(void**)&P->d_tiles, (void**)&P->d_csf})
       if (*p) {
         (void)hipFree(*p);
         *p = nullptr;
       }
   };
   wvl_status st;
-  // d_cptr last: it marks the lists as ready
+  // d_tiles last: it marks the lists as ready
   if ((st = upload(ctx, &P->d_csf, csf.data(), sizeof(int32_t) * csf.size())) != WVL_OK ||
-      (st = upload(ctx, &P->d_cptr, cptr.data(), sizeof(int64_t) * cptr.size())) != WVL_OK) {
+      (st = upload(ctx, &P->d_tiles, tiles.data(), sizeof(DensTile) * ntile)) != WVL_OK) {
     drop();
     return st;
   }
@@ -1692,7 +1707,8 @@ wvl_status wvl_density(wvl_plan* P, wvl_dtype dt, const void* fine, const int64_
   for (int a = 0; a < 3; ++a) gf[a] = 2 * ctx->grid.n[a] + 29;
   WVL_LAUNCH(ctx, KK_DENS_TILE,
              launch_dens_tile(f64, ctx->stream, P->d_sf, P->d_foff, fine, k_rowptr, k_col, k_val,
-                              k_nnz, P->d_cptr, P->d_csf, P->nsf, gf, rho));
+                              k_nnz, P->d_tiles, P->d_csf, P->dens_heavy,
+                              P->nsf, gf, rho));
   return WVL_OK;
 }
 

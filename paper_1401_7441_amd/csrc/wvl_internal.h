@@ -209,10 +209,17 @@ int launch_up_z(int f64, void* stream, const SfWork* wk, const SfDev* sf, int ns
 // meet one plane (16 x 4 x 1 points) of a tile
 constexpr int kDensTile[3] = {16, 4, 4};
 constexpr int kDensMaxCover = 1024;
+// a tile and the m functions that meet it, csf[c0 .. c0 + m); in launch order,
+// first the nheavy tiles that more than kDensLight functions meet
+struct DensTile {
+  int32_t tile, m;
+  int64_t c0;
+};
+constexpr int kDensLight = 32;
 int launch_dens_tile(int f64, void* stream, const SfDev* sf, const int64_t* foff,
                      const void* fine, const int64_t* krow, const int32_t* kcol,
-                     const double* kval, int64_t knnz, const int64_t* cptr, const int32_t* csf,
-                     int nsf, const int* gf, void* rho);
+                     const double* kval, int64_t knnz, const DensTile* tiles, const int32_t* csf,
+                     int64_t nheavy, int nsf, const int* gf, void* rho);
 int launch_pot_column(int f64, void* stream, const SfDev* sf, const SfWork* wk, int sf0, int nsf,
                       int gridx, void* ws, const void* pot, int nf1, int nf2, double* epart,
                       const double* conf, double hh, int padded);

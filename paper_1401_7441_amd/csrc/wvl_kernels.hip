@@ -445,28 +445,36 @@ __global__ __launch_bounds__(64 * W, 8) void k_sparse_values(const SfDev* __rest
 // products cost m^2 / 2 multiply-adds per point for a cover of m (up to 340
 // functions of radius 5-7 bohr at 0.037 per bohr^3, 37 in the middle of all
 // tiles).  1,000 such functions in FP32: 16.8 ms with 16 x 4 x 1 points and the
-// sums on the vector units; 7.8 ms in this form, of which the products take
-// 2.7 (1.6 at the full FP64 matrix rate), the scans 2.5 and the values 1.0.
+// sums on the vector units; 8.0 ms in this form, of which the products take
+// 2.7 (1.6 at the full FP64 matrix rate), the scans 2.5 and the values 1.0; 7.5
+// with the tiles of the most chunks first, as long ones are not left for the end
+// (400 functions of 6-7 bohr at 0.5 per bohr^3: 8.6 and 6.2 ms).
 // Tiles of 16 x 4 x 2 points (two blocks per CU) took 9.6 ms, chunks of 128
 // functions 9.4 (spilled registers).
-// hash of a pair's functions: at most 128 in 2048 slots (function << 8 |
-// position), open addressing, so that one read settles most lookups
-constexpr int kDensLogSlots = 11, kDensSlots = 1 << kDensLogSlots;
-__device__ __forceinline__ int dens_slot(int b) {
-  return (int)(((uint32_t)b * 2654435761u) >> (32 - kDensLogSlots));
-}
-
-// functions per chunk: both chunks' values at a wave's points fit its registers
-constexpr int kDensChunk = 64, kDensLd = kDensChunk + 4;   // T's rows 4 (mod 16) apart: banks
+// C: functions per chunk.  64: both chunks' values at a wave's points fit its
+// registers.  kDensLight, for the tiles that at most so many functions meet: a
+// third of the LDS and half of the registers, so that two blocks share a CU and
+// the steps of one, of which there are as many for a few functions as for 64, are
+// covered by the other's (same sums, same bits).  FP32, with blocks of K without an
+// entry left out: 30 functions 0.28 -> 0.17 ms, one 0.117 -> 0.081 (an empty grid
+// for the most part), a diagonal K of 1,000 6.8 -> 4.5.
+constexpr int kDensChunk = 64;
 constexpr int kDensThreads = 64 * 4 * kDensTile[2];
-template <typename T>
-__global__ __launch_bounds__(kDensThreads) void k_dens_tile(
+template <typename T, int C>
+__global__ __launch_bounds__(kDensThreads, C == kDensLight ? 8 : 4) void k_dens_tile(
     const SfDev* __restrict__ sfs, const int64_t* __restrict__ foff, const T* __restrict__ fine,
     const int64_t* __restrict__ krow, const int32_t* __restrict__ kcol,
-    const double* __restrict__ kval, int64_t knnz, const int64_t* __restrict__ cptr,
+    const double* __restrict__ kval, int64_t knnz, const DensTile* __restrict__ tiles,
     const int32_t* __restrict__ csf, int nsf, int tx, int ty, int g0, int g1, int g2,
     T* __restrict__ rho) {
-  constexpr int C = kDensChunk, S = C / 4, LD = kDensLd, NT = kDensThreads, NW = NT / 64;
+  constexpr int U = C == kDensLight ? 1 : 4;   // runs of 64 entries of K under way
+  // blocks of 16 x 16 without an entry are left out (FP64 has no registers for it)
+  constexpr bool kSkip = sizeof(T) == 4;
+  constexpr int S = C / 4, LD = C + 4, NT = kDensThreads, NW = NT / 64;   // T's rows 4 (mod 16) apart: banks
+  // hash of a pair's functions: at most 2 C in 32 C slots (function << 8 |
+  // position), open addressing, so that one read settles most lookups
+  constexpr int kDensSlots = 32 * C;
+  auto dens_slot = [](int b) { return (int)(((uint64_t)((uint32_t)b * 2654435761u) * kDensSlots) >> 32); };
   typedef double V __attribute__((ext_vector_type(4)));
   // T: entries of the rows i, and of the rows j (each element then has one
   // wave that adds to it, so duplicated entries add up in their order)
@@ -479,8 +487,11 @@ __global__ __launch_bounds__(kDensThreads) void k_dens_tile(
   __shared__ int64_t fo[2 * C], kq[2 * C];
   __shared__ int32_t kl[2 * C];
   __shared__ uint8_t used[2][C];      // the function has an entry in the pair's block
-  static_assert(C == 64, "a lane per function of a chunk");
-  const int tile = blockIdx.x;
+  __shared__ uint8_t blk[64];         // 16 x 16 blocks of T that hold entries
+  static_assert(C <= 64, "a lane per function of a chunk");
+  const DensTile dt = tiles[blockIdx.x];
+  const int tile = dt.tile, m = dt.m;
+  const int64_t c0 = dt.c0;
   const int ix = tile % tx, iy = (tile / tx) % ty, iz = tile / (tx * ty);
   const int tid = threadIdx.x, lane = tid & 63, n = lane & 15, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -488,8 +499,10 @@ __global__ __launch_bounds__(kDensThreads) void k_dens_tile(
   const int gy = iy * kDensTile[1] + (wave & 3);
   const int gz = iz * kDensTile[2] + (wave >> 2);
   const bool inside = gx < g0 && gy < g1 && gz < g2;
-  const int64_t c0 = cptr[tile];
-  const int m = (int)(cptr[tile + 1] - c0);
+  if (m == 0) {   // uniform over the block
+    if (inside && g == 0) rho[((int64_t)gz * g1 + gy) * g0 + gx] = T(0);
+    return;
+  }
   double acc = 0.0;
   T pi[S], pj[S];
   // stages a chunk's functions at half C (a barrier before and after)
@@ -578,17 +591,17 @@ __global__ __launch_bounds__(kDensThreads) void k_dens_tile(
 #pragma unroll
         for (int s = 0; s < S; ++s) pj[s] = pi[s];
       }
-      // the wave's rows to scan (I's, then J's), i = wave, wave + NW, ..: 256
+      // the wave's rows to scan (I's, then J's), i = wave, wave + NW, ..: 64 U
       // entries at a time, the next ones loaded while these are looked up
       const int nrow = ni + (diag ? 0 : nj);
       int si = wave, sq = 0;   // the next row and its first entry
       auto slot = [&](int i) { return i < ni ? i : C + i - ni; };
-      int b[4], bn[4], pa = 0, pan = 0;
-      double kb[4], kn[4];
-      auto fetch = [&](int (&bb)[4], double (&kk)[4], int& row) {
+      int b[U], bn[U], pa = 0, pan = 0;
+      double kb[U], kn[U];
+      auto fetch = [&](int (&bb)[U], double (&kk)[U], int& row) {
         row = -1;
 #pragma unroll
-        for (int u = 0; u < 4; ++u) bb[u] = -1;
+        for (int u = 0; u < U; ++u) bb[u] = -1;
         while (si < nrow && sq >= kl[slot(si)]) {
           si += NW;
           sq = 0;
@@ -598,18 +611,19 @@ __global__ __launch_bounds__(kDensThreads) void k_dens_tile(
         const int64_t q = kq[row] + sq;
         const int left = kl[row] - sq;
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
+        for (int u = 0; u < U; ++u)
           if (64 * u + lane < left) {
             bb[u] = kcol[q + 64 * u + lane];
             kk[u] = kval[q + 64 * u + lane];
           }
-        sq += 256;
+        sq += 64 * U;
       };
       fetch(b, kb, pa);
       // hash of the pair's functions and an empty T: -0 where there is no entry
       // (entries are added as kb + 0, never -0, so that a sum is never -0 either)
       for (int h = tid; h < kDensSlots; h += NT) hslot[h] = 0xFFFFFFFFu;
       if (tid < 2 * C) used[tid / C][tid % C] = 0;
+      if (kSkip && tid < 64) blk[tid] = 0;
       const int nr = (ni + 15) & ~15;
       for (int h = tid; h < nr * (LD / 2); h += NT)
         reinterpret_cast<double2*>(tk[0])[h] = reinterpret_cast<double2*>(tk[1])[h] =
@@ -625,7 +639,7 @@ __global__ __launch_bounds__(kDensThreads) void k_dens_tile(
       while (pa >= 0) {   // uniform over the wave
         fetch(bn, kn, pan);
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
+        for (int u = 0; u < U; ++u) {
           if (b[u] < 0 || b[u] >= nsf) continue;
           int at = dens_slot(b[u]);
           uint32_t v = hslot[at];
@@ -643,7 +657,7 @@ __global__ __launch_bounds__(kDensThreads) void k_dens_tile(
         }
         pa = pan;
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
+        for (int u = 0; u < U; ++u) {
           b[u] = bn[u];
           kb[u] = kn[u];
         }
@@ -654,21 +668,25 @@ __global__ __launch_bounds__(kDensThreads) void k_dens_tile(
         const double2 v = reinterpret_cast<double2*>(tk[1])[h];
         t.x += v.x;
         t.y += v.y;
+        if (kSkip && (!(__builtin_signbit(t.x) && t.x == 0.0) || !(__builtin_signbit(t.y) && t.y == 0.0)))
+          blk[(h / (LD / 2) >> 4) * 4 + (2 * (h % (LD / 2)) >> 4)] = 1;
       }
       __syncthreads();
       // bit 4 s: function 4 s + g has an entry
-      const uint64_t ui = __ballot(used[0][lane]) >> g, uj = __ballot(used[jh][lane]) >> g;
+      const uint64_t ui = __ballot(lane < C && used[0][lane % C]) >> g,
+                     uj = __ballot(lane < C && used[jh][lane % C]) >> g;
+      const uint64_t ub = kSkip ? __ballot(blk[lane]) : ~0ull;
 #pragma unroll
       for (int s = 0; s < S; ++s) pj[s] = (uj >> (4 * s)) & 1u ? pj[s] : T(0);
       const double* const ta = tk[0] + n * LD + g;
       const double before = acc;
 #pragma unroll
       for (int st = 0; st < C / 16; ++st) {
-        if (16 * st >= ni) continue;
+        if (16 * st >= ni || !((ub >> (4 * st)) & 15u)) continue;
         V d = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
         for (int cb = 0; cb < C / 16; ++cb) {
-          if (16 * cb >= nj || (diag && cb < st)) continue;
+          if (16 * cb >= nj || (diag && cb < st) || !((ub >> (4 * st + cb)) & 1u)) continue;
           __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
           for (int s = 4 * cb; s < 4 * cb + 4; ++s) {
@@ -1500,8 +1518,9 @@ int preload_kernels() {
                        (const void*)k_sparse_values<double, 4>,
                        (const void*)k_sparse_values<double, 8>, (const void*)k_update<float>,
                        (const void*)k_update<double>, (const void*)k_sf_dot<float>,
-                       (const void*)k_sf_dot<double>, (const void*)k_dens_tile<float>,
-                       (const void*)k_dens_tile<double>, (const void*)k_grad_rows<float>,
+                       (const void*)k_sf_dot<double>, (const void*)k_dens_tile<float, kDensChunk>,
+                       (const void*)k_dens_tile<float, kDensLight>,
+                       (const void*)k_dens_tile<double, kDensChunk>, (const void*)k_grad_rows<float>,
                        (const void*)k_grad_rows<double>};
   for (const void* f : fns) {
     hipFuncAttributes a;
@@ -1613,21 +1632,25 @@ int launch_sparse_values(int f64, void* stream, const SfDev* sf, const wvl_seg* 
 
 int launch_dens_tile(int f64, void* stream, const SfDev* sf, const int64_t* foff,
                      const void* fine, const int64_t* krow, const int32_t* kcol,
-                     const double* kval, int64_t knnz, const int64_t* cptr, const int32_t* csf,
-                     int nsf, const int* gf, void* rho) {
+                     const double* kval, int64_t knnz, const DensTile* tiles, const int32_t* csf,
+                     int64_t nheavy, int nsf, const int* gf, void* rho) {
   const int tx = (gf[0] + kDensTile[0] - 1) / kDensTile[0];
   const int ty = (gf[1] + kDensTile[1] - 1) / kDensTile[1];
   const int tz = (gf[2] + kDensTile[2] - 1) / kDensTile[2];
-  const dim3 g((unsigned)((int64_t)tx * ty * tz));
-  hipStream_t st = (hipStream_t)stream;
-  if (f64)
-    hipLaunchKernelGGL(k_dens_tile<double>, g, dim3(kDensThreads), 0, st, sf, foff,
-                       (const double*)fine, krow, kcol, kval, knnz, cptr, csf, nsf, tx, ty, gf[0],
-                       gf[1], gf[2], (double*)rho);
-  else
-    hipLaunchKernelGGL(k_dens_tile<float>, g, dim3(kDensThreads), 0, st, sf, foff,
-                       (const float*)fine, krow, kcol, kval, knnz, cptr, csf, nsf, tx, ty, gf[0],
-                       gf[1], gf[2], (float*)rho);
+  const int64_t ntile = (int64_t)tx * ty * tz;
+  auto go = [&](auto kernel, const DensTile* list, int64_t n, auto t) {
+    using T = decltype(t);
+    if (n > 0)
+      hipLaunchKernelGGL(kernel, dim3((unsigned)n), dim3(kDensThreads), 0, (hipStream_t)stream, sf,
+                         foff, (const T*)fine, krow, kcol, kval, knnz, list, csf, nsf, tx, ty, gf[0],
+                         gf[1], gf[2], (T*)rho);
+  };
+  if (f64) {   // all tiles (the light form would spill)
+    go(k_dens_tile<double, kDensChunk>, tiles, ntile, 0.0);
+  } else {
+    go(k_dens_tile<float, kDensChunk>, tiles, nheavy, 0.0f);
+    go(k_dens_tile<float, kDensLight>, tiles + nheavy, ntile - nheavy, 0.0f);
+  }
   return (int)hipGetLastError();
 }
 
