@@ -1863,15 +1863,15 @@ wvl_status wvl_foe(wvl_plan* P, const double* s_val, const double* h_val, int32_
   // 79, 8,000 106 / 110 (two blocks left per CU): the line lies where the
   // gain ends and the row still fits 64 KiB.
   const bool spread = (int64_t)n + pc.maxdeg <= kFoeSpread;
-  auto rmul = [&](double al, const double* R, const double* A, double be, const double* D, double* C) {
-    return launch_foe_rmul(s, n, pc.d_foe_rows, rp, cl, al, R, A, be, D, C, pc.maxdeg);
+  auto rmul = [&](double al, const double* R, const double* A, double be, const double* D, double* C,
+                  const int64_t* transposed = nullptr) {
+    return launch_foe_rmul(s, n, pc.d_foe_rows, rp, cl, al, R, A, be, D, transposed, C, pc.maxdeg);
   };
   // o = ((Sh M)|_P Sh)|_P for the symmetric Sh, from M or (spread) M^T; o is
   // neither M nor X, which is overwritten
   auto two_sided = [&](const double* M, double* o) -> wvl_status {
     if (spread) {
-      WVL_LAUNCH(ctx, KK_FOE, rmul(1.0, M, Sh, 0.0, nullptr, o));
-      WVL_LAUNCH(ctx, KK_FOE, launch_foe_gather(s, nnz, tp, o, X));
+      WVL_LAUNCH(ctx, KK_FOE, rmul(1.0, M, Sh, 0.0, nullptr, X, tp));
       WVL_LAUNCH(ctx, KK_FOE, rmul(1.0, X, Sh, 0.0, nullptr, o));
     } else {
       WVL_LAUNCH(ctx, KK_FOE, mm(1.0, Sh, M, 0.0, nullptr, X));

@@ -273,13 +273,13 @@ constexpr int kFoeMaxCol = 1 << 21;
 int launch_foe_mm(void* stream, int nrow, const int32_t* rows, const int64_t* rowptr,
                   const int32_t* col, double alpha, const double* A, const double* B, double beta,
                   const double* D, double* C, int lognb, int maxdeg);
-// C = alpha (R A)|_P + beta D, A symmetric, from rows spread out in LDS: where
-// the functions plus the longest row's entries number at most kFoeSpread (64
-// KiB of LDS; beyond it the launch is refused)
+// C = alpha (R A)|_P + beta D (with tpos: stored transposed), A symmetric, from
+// rows spread out in LDS: where the functions plus the longest row's entries
+// number at most kFoeSpread (64 KiB of LDS; beyond it the launch is refused)
 constexpr int kFoeSpread = 8192;
 int launch_foe_rmul(void* stream, int nrow, const int32_t* rows, const int64_t* rowptr,
                     const int32_t* col, double alpha, const double* R, const double* A, double beta,
-                    const double* D, double* C, int maxdeg);
+                    const double* D, const int64_t* tpos, double* C, int maxdeg);
 int launch_foe_axpby(void* stream, int64_t nnz, double a, const double* X, double b,
                      const double* Y, const int32_t* row, const int32_t* col, double d,
                      double* out);

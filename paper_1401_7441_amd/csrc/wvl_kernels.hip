@@ -4,6 +4,8 @@
 // itself runs in the fused kernels of wvl_fused.hip.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "wvl_internal.h"
 
 namespace wvl {
@@ -890,59 +892,77 @@ __global__ __launch_bounds__(64 * W) void k_foe_mm(
   }
 }
 
-// C = alpha (R A)|_P + beta D for a symmetric A on P: one workgroup per row r
-// of P (longest work first), row r of R spread out in LDS (n doubles, zeros
-// elsewhere); a group of 16 lanes takes an entry c of the row and adds up
-// R_rk A_ck over row c of A, so that an entry costs one LDS read and no
-// lookup.  Twelve loads of a row under way per lane cover the usual rows with
-// one latency; the lanes' sums are added in a fixed tree.  Bound by the reads
-// of A through L2 (12 bytes per product).  1,000 functions with 163 entries a
-// row (27M products): 70 us with k_foe_mm, 43 here (256 threads and four loads:
-// 54); 4,000 with 72 entries: 54 and 34 us.
+// C = alpha (R A)|_P + beta D for a symmetric A on P (tpos: stored transposed,
+// without D): a workgroup takes row r of P (longest work first), row r of R
+// spread out in LDS (n doubles, zeros elsewhere); a group of 16 lanes takes an
+// entry c of the row and adds up R_rk A_ck over row c of A, so that an entry costs
+// one LDS read and no lookup.  Twelve loads of a row under way per lane cover the
+// usual rows with one latency; the lanes' sums are added in a fixed tree.  Bound
+// by the reads of A through L2 (12 bytes per product).  1,000 functions with 163
+// entries a row (27M products): 70 us with k_foe_mm, 43 here (256 threads and four
+// loads: 54); 4,000 with 72 entries: 54 and 34 us.
+// LOOP: a block takes several rows (see the launch): the n zeros are written once,
+// and only a row's own entries cleared after it.  A row's run starts are read
+// before the first barrier with one row per block, after it with several: the other
+// way round costs 2 and 10 %.
 constexpr int kRmulThreads = 512;
+template <bool LOOP>
 __global__ __launch_bounds__(kRmulThreads) void k_foe_rmul(
     const int32_t* __restrict__ rows, const int64_t* __restrict__ rowptr,
     const int32_t* __restrict__ col, int n, double alpha, const double* __restrict__ R,
     const double* __restrict__ A, double beta, const double* __restrict__ D,
-    double* __restrict__ C, int maxdeg) {
+    const int64_t* __restrict__ tpos, double* __restrict__ C, int maxdeg) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   double* const x = reinterpret_cast<double*>(smem_raw);   // [n]
   int* const kst = reinterpret_cast<int*>(x + n);           // start and length of the rows c
   int* const kdg = kst + maxdeg;
   const int tid = threadIdx.x, l = tid & 15;
-  const int i = rows[blockIdx.x];
-  const int64_t r0 = rowptr[i];
-  const int deg = (int)(rowptr[i + 1] - r0);
   for (int k = tid; k < n; k += kRmulThreads) x[k] = 0.0;
-  for (int p = tid; p < deg; p += kRmulThreads) {
-    const int64_t k0 = rowptr[col[r0 + p]];
-    kst[p] = (int)k0;
-    kdg[p] = (int)(rowptr[col[r0 + p] + 1] - k0);
-  }
-  __syncthreads();
-  for (int p = tid; p < deg; p += kRmulThreads) x[col[r0 + p]] = R[r0 + p];
-  __syncthreads();
-  for (int p = tid >> 4; p < deg; p += kRmulThreads / 16) {
-    const int* const cc = col + kst[p];
-    const double* const av = A + kst[p];
-    const int kd = kdg[p];
-    double s = 0.0;
-    constexpr int U = 12;
-    for (int q = l; q < kd; q += 16 * U) {
-      int k[U];
-      double a[U];
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-        if (q + 16 * u < kd) {
-          k[u] = cc[q + 16 * u];
-          a[u] = av[q + 16 * u];
-        }
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-        if (q + 16 * u < kd) s += a[u] * x[k[u]];
+  for (int rq = blockIdx.x; rq < n; rq += gridDim.x) {
+    const int i = rows[rq];
+    const int64_t r0 = rowptr[i];
+    const int deg = (int)(rowptr[i + 1] - r0);
+    auto runs = [&](int p, int c) {
+      const int64_t k0 = rowptr[c];
+      kst[p] = (int)k0;
+      kdg[p] = (int)(rowptr[c + 1] - k0);
+    };
+    if (!LOOP)   // meanwhile
+      for (int p = tid; p < deg; p += kRmulThreads) runs(p, col[r0 + p]);
+    __syncthreads();   // x is zero
+    for (int p = tid; p < deg; p += kRmulThreads) {
+      const int c = col[r0 + p];
+      if (LOOP) runs(p, c);
+      x[c] = R[r0 + p];
     }
-    for (int o = 8; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-    if (l == 0) C[r0 + p] = D ? alpha * s + beta * D[r0 + p] : alpha * s;
+    __syncthreads();
+    for (int p = tid >> 4; p < deg; p += kRmulThreads / 16) {
+      const int* const cc = col + kst[p];
+      const double* const av = A + kst[p];
+      const int kd = kdg[p];
+      double s = 0.0;
+      constexpr int U = 12;
+      for (int q = l; q < kd; q += 16 * U) {
+        int k[U];
+        double a[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+          if (q + 16 * u < kd) {
+            k[u] = cc[q + 16 * u];
+            a[u] = av[q + 16 * u];
+          }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+          if (q + 16 * u < kd) s += a[u] * x[k[u]];
+      }
+      for (int o = 8; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+      if (l == 0) C[tpos ? tpos[r0 + p] : r0 + p] = D ? alpha * s + beta * D[r0 + p] : alpha * s;
+    }
+    if (!LOOP) return;
+    if (rq + (int)gridDim.x < n) {
+      __syncthreads();
+      for (int p = tid; p < deg; p += kRmulThreads) x[col[r0 + p]] = 0.0;
+    }
   }
 }
 
@@ -1680,12 +1700,21 @@ int launch_foe_mm(void* stream, int nrow, const int32_t* rows, const int64_t* ro
 
 int launch_foe_rmul(void* stream, int nrow, const int32_t* rows, const int64_t* rowptr,
                     const int32_t* col, double alpha, const double* R, const double* A, double beta,
-                    const double* D, double* C, int maxdeg) {
+                    const double* D, const int64_t* tpos, double* C, int maxdeg) {
   if (nrow == 0) return 0;
   if ((int64_t)nrow + maxdeg > kFoeSpread) return (int)hipErrorInvalidValue;
   const size_t lds = (size_t)nrow * 8 + (size_t)maxdeg * 8;
-  hipLaunchKernelGGL(k_foe_rmul, dim3((unsigned)nrow), dim3(kRmulThreads), lds,
-                     (hipStream_t)stream, rows, rowptr, col, nrow, alpha, R, A, beta, D, C, maxdeg);
+  // one row per block while a CU's LDS holds four blocks (its 2,048 threads),
+  // beyond that as many blocks as the 256 CUs hold, each with several rows: an
+  // expansion of degree 50 of 7,900 functions with 6 entries a row 3.03 -> 2.38 ms, of
+  // 6,000 with 50 3.03 -> 2.91, but of 4,000 with 72 2.70 -> 2.97
+  const int fit = (int)(160 * 1024 / (lds + 256));
+  const bool loop = fit < 2048 / kRmulThreads && 256 * fit < nrow;
+  auto go = [&](auto kernel, int grid) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(kRmulThreads), lds, (hipStream_t)stream,
+                       rows, rowptr, col, nrow, alpha, R, A, beta, D, tpos, C, maxdeg);
+  };
+  loop ? go(k_foe_rmul<true>, 256 * fit) : go(k_foe_rmul<false>, nrow);
   return (int)hipGetLastError();
 }
 
