@@ -191,7 +191,11 @@ wvl_status wvl_compress(wvl_plan* plan, wvl_dtype dt, const void* box, void* hps
  *   <phi|T|phi> and the potential energy sum_r V f(r)^2 on the fine grid.
  *   workspace: device, at least the plan's workspace size for dt.
  * T is the exact Galerkin kinetic operator of the two-level basis; V is the
- * magic-filter quadrature of the local potential on the fine grid. */
+ * magic-filter quadrature of the local potential on the fine grid.
+ * hpsi_c may lie over psi_c if a function's output then overwrites the input of
+ * no other (the same patterns, hpsi_c == psi_c), or if one chunk holds all
+ * functions (no max_workspace_bytes, or a large one): the column kernels run,
+ * which take longer. */
 wvl_status wvl_apply_local_ham(wvl_plan* plan, wvl_dtype dt, uint32_t terms, const void* psi_c,
                                const void* pot, void* hpsi_c, double* e_kin, double* e_pot,
                                void* workspace);

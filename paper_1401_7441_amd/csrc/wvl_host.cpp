@@ -251,6 +251,7 @@ struct wvl_plan {
   std::vector<int32_t> order[2];
   size_t max_ws = 0;                  // the caller's workspace bound (0: none)
   Layout lay;
+  Layout in_place;                    // column kernels for all (apply with hpsi over psi)
   int64_t ws_cap[2] = {0, 0};         // workspace bytes reported (F32, F64)
   hipStream_t capture = nullptr;      // the stream that graphs are captured on
   int64_t layout_version = 0;         // bumped when the autotuner changes the layout
@@ -262,6 +263,7 @@ struct wvl_plan {
   int32_t* d_rt = nullptr;
   RowRun* d_rr = nullptr;
   SfWork* d_wk = nullptr;
+  SfWork* d_wk_in_place = nullptr;
   int64_t* d_foff = nullptr;          // fine-box offsets (wvl_synthesize), function order
   int64_t max_fine = 0;               // largest fine box (elements)
   DensTile* d_tiles = nullptr;        // density: k_dens_tile's tiles in launch order
@@ -705,6 +707,7 @@ void wvl_plan_destroy(wvl_plan* plan) {
   if (plan->d_rt) (void)hipFree(plan->d_rt);
   if (plan->d_rr) (void)hipFree(plan->d_rr);
   if (plan->d_wk) (void)hipFree(plan->d_wk);
+  if (plan->d_wk_in_place) (void)hipFree(plan->d_wk_in_place);
   free_pattern(plan->pat[0]);
   free_pattern(plan->pat[1]);
   if (plan->capture) (void)hipStreamDestroy(plan->capture);
@@ -784,10 +787,14 @@ constexpr int kLdsSplit = 64;
 // does not fit the kernels' LDS stages.  With a workspace bound, the chunks of
 // the plane kernels keep within the column kernels' workspace as well
 // (P->ws_cap, from the layouts with zmfma, which are made first): what a plan
-// reports is then what the column kernels need, for every layout.
-static bool make_layout(const wvl_plan* P, int nbins, bool zmfma, Layout* L, std::string* err) {
+// reports is then what the column kernels need, for every layout.  zmfma (the
+// matrix-core z part belongs to the column kernels) or column: column kernels for
+// all functions.
+static bool make_layout(const wvl_plan* P, int nbins, bool zmfma, Layout* L, std::string* err,
+                        bool column = false) {
   const int nsf = P->nsf;
-  const std::vector<int32_t>& order = P->order[zmfma ? 1 : 0];
+  column = column || zmfma;
+  const std::vector<int32_t>& order = P->order[column ? 1 : 0];
   L->chunks.clear();
   L->wk.assign(nsf, SfWork{});
   L->nbins = nbins;
@@ -806,15 +813,14 @@ static bool make_layout(const wvl_plan* P, int nbins, bool zmfma, Layout* L, std
       int64_t elems = 0;
       PartSlots most;
       int j = k;
-      // the matrix-core z part belongs to the column kernels; a chunk's
-      // functions take the same kernels
-      const int cls = zmfma ? 0 : plane_class(P->h_sf[order[k]]), bits = cls & 3;
+      // a chunk's functions take the same kernels
+      const int cls = column ? 0 : plane_class(P->h_sf[order[k]]), bits = cls & 3;
       ch.wide = cls & 4;
       ch.strip = cls & 8 ? 32 : 24;
       ch.plane[0] = bits & 1;
       ch.plane[1] = bits & 2;
       for (; j < b1; ++j) {
-        if (!zmfma && plane_class(P->h_sf[order[j]]) != cls) break;
+        if (!column && plane_class(P->h_sf[order[j]]) != cls) break;
         // one launch has one LDS size: smaller boxes, of which more blocks fit
         // a CU, get a launch of their own where there are enough of either
         if (j - k >= kLdsSplit && b1 - j >= kLdsSplit && bits &&
@@ -826,7 +832,7 @@ static bool make_layout(const wvl_plan* P, int nbins, bool zmfma, Layout* L, std
         // partial slots are at most a few per 256 output points
         const int64_t bytes = align_bytes((elems + need) * 8) + (int64_t)(j - k + 1) * 4096 * 8;
         if (j > k && P->max_ws > 0 && (size_t)bytes > P->max_ws) break;
-        if (j > k && P->max_ws > 0 && !zmfma) {
+        if (j > k && P->max_ws > 0 && !column) {
           const int64_t pb = (j - k + 1) * (top.pot + top.kin()) * 8;
           if (align_bytes((elems + need) * 4) + pb > P->ws_cap[0] ||
               align_bytes((elems + need) * 8) + pb > P->ws_cap[1])
@@ -1098,6 +1104,11 @@ wvl_status wvl_plan_create(wvl_ctx* ctx, int32_t nsf, const wvl_locreg* lr, cons
       P->ws_cap[1] = std::max(P->ws_cap[1], L.bytes(8));
       if (nb == 1 && zm == 0) P->lay = std::move(L);
     }
+  // at most the z part's partials smaller than the layout with zmfma
+  if (std::string err; !make_layout(P, 1, false, &P->in_place, &err, true)) {
+    wvl_plan_destroy(P);
+    return fail(ctx, WVL_EUNSUPPORTED, "%s", err.c_str());
+  }
   const int64_t best_f32 = P->ws_cap[0], best_f64 = P->ws_cap[1];
   P->info.nsf = nsf;
   P->info.in_coefs = in_coefs;
@@ -1120,6 +1131,7 @@ wvl_status wvl_plan_create(wvl_ctx* ctx, int32_t nsf, const wvl_locreg* lr, cons
       (st = upload(ctx, &P->d_rt, rt.data(), sizeof(int32_t) * rt.size())) != WVL_OK ||
       (st = upload(ctx, &P->d_rr, rr.data(), sizeof(RowRun) * rr.size())) != WVL_OK ||
       (st = upload(ctx, &P->d_wk, P->lay.wk.data(), sizeof(SfWork) * nsf)) != WVL_OK ||
+      (st = upload(ctx, &P->d_wk_in_place, P->in_place.wk.data(), sizeof(SfWork) * nsf)) != WVL_OK ||
       (st = upload(ctx, &P->d_foff, foff.data(), sizeof(int64_t) * (nsf + 1))) != WVL_OK) {
     wvl_plan_destroy(P);
     return st;
@@ -1203,7 +1215,6 @@ static wvl_status apply_args(wvl_plan* P, wvl_dtype dt, uint32_t terms, const vo
   return WVL_OK;
 }
 
-// Enqueues the stages of chunk c on stream st.
 // Blocks of the up pass and the z part of the kinetic term that go in one
 // launch: as many as the chip holds at four per CU.  Both only read psi, so a
 // small call saves a launch and its latency: apply of 1 / 4 / 16 functions in
@@ -1213,19 +1224,29 @@ static wvl_status apply_args(wvl_plan* P, wvl_dtype dt, uint32_t terms, const vo
 // -> 852 us, FP32, 60 of 16-48 points per axis 1.08 -> 1.21 ms.
 constexpr int64_t kUpKinBlocks = 1024;
 
-static wvl_status apply_chunk(wvl_plan* P, size_t c, int f64, uint32_t terms, const void* psi_c,
-                              const void* pot, void* hpsi_c, double* e_kin, double* e_pot,
-                              void* workspace, int accumulate, hipStream_t st,
-                              const double* conf = nullptr) {
+// Whether hpsi_c is written over psi_c.  The plane kernels' back pass reads psi
+// while other blocks write hpsi; the column kernels read all of a chunk's psi
+// before they write, so an apply in place takes them.
+static bool in_place(const wvl_plan* P, int f64, const void* psi_c, const void* hpsi_c) {
+  const int64_t sz = f64 ? 8 : 4;
+  const char *a = (const char*)psi_c, *b = (const char*)hpsi_c;
+  return a < b + P->info.out_coefs * sz && b < a + P->info.in_coefs * sz;
+}
+
+// Enqueues the stages of chunk c of the layout on stream st.
+static wvl_status apply_chunk(wvl_plan* P, const Layout& lay, const SfWork* d_wk, size_t c, int f64,
+                              uint32_t terms, const void* psi_c, const void* pot, void* hpsi_c,
+                              double* e_kin, double* e_pot, void* workspace, int accumulate,
+                              hipStream_t st, const double* conf) {
   wvl_ctx* ctx = P->ctx;
   const int sz = f64 ? 8 : 4;
   const int d = f64 ? 1 : 0;
   const int nf1 = 2 * ctx->grid.n[0] + 29, nf2 = 2 * ctx->grid.n[1] + 29;
   const double fac = -2.0 / (ctx->grid.h * ctx->grid.h);   // -1/2 (2/h)^2
   const int pot_on = (terms & WVL_POT) ? 1 : 0, kin_on = (terms & WVL_KIN) ? 1 : 0;
-  const ChunkDev& ch = P->lay.chunks[c];
-  const SfWork* wk = P->d_wk + ch.sf0;
-  double* parts = (double*)((char*)workspace + align_bytes(P->lay.elems_span * sz));
+  const ChunkDev& ch = lay.chunks[c];
+  const SfWork* wk = d_wk + ch.sf0;
+  double* parts = (double*)((char*)workspace + align_bytes(lay.elems_span * sz));
   if (ch.plane[d]) {
     // the up pass and the z part of the kinetic term side by side in one launch
     const bool side = pot_on && kin_on && (int64_t)ch.nsf * (ch.grid_up + ch.grid_ks) <= kUpKinBlocks;
@@ -1280,7 +1301,7 @@ static wvl_status apply_chunk(wvl_plan* P, size_t c, int f64, uint32_t terms, co
                                                 ch.grid_kx, workspace, fac, parts));
     WVL_LAUNCH(ctx, KK_KIN_YCOL, launch_kin_col(f64, st, 1, P->d_sf, wk, ch.sf0, ch.nsf,
                                                 ch.grid_ky, workspace, fac, parts));
-    if (P->lay.zmfma)
+    if (lay.zmfma)
       WVL_LAUNCH(ctx, KK_KIN_ZCOL, launch_kin_zmfma(f64, st, P->d_sf, wk, ch.sf0, ch.nsf,
                                                     ch.grid_kz, workspace, fac, parts));
     else
@@ -1301,17 +1322,29 @@ static wvl_status apply_chunk(wvl_plan* P, size_t c, int f64, uint32_t terms, co
   return WVL_OK;
 }
 
+// Enqueues all chunks of an apply on stream st.
+static wvl_status apply_chunks(wvl_plan* P, int f64, uint32_t terms, const void* psi_c,
+                               const void* pot, void* hpsi_c, double* e_kin, double* e_pot,
+                               void* workspace, int accumulate, hipStream_t st,
+                               const double* conf = nullptr) {
+  const bool over = in_place(P, f64, psi_c, hpsi_c);
+  const Layout& lay = over ? P->in_place : P->lay;
+  const SfWork* d_wk = over ? P->d_wk_in_place : P->d_wk;
+  wvl_status rc = WVL_OK;
+  for (size_t c = 0; rc == WVL_OK && c < lay.chunks.size(); ++c)
+    rc = apply_chunk(P, lay, d_wk, c, f64, terms, psi_c, pot, hpsi_c, e_kin, e_pot, workspace,
+                     accumulate, st, conf);
+  return rc;
+}
+
 static wvl_status apply_impl(wvl_plan* P, wvl_dtype dt, uint32_t terms, const void* psi_c,
                              const void* pot, void* hpsi_c, double* e_kin, double* e_pot,
                              void* workspace, int accumulate, const char* who,
                              const double* conf = nullptr) {
   wvl_status st = apply_args(P, dt, terms, psi_c, pot, hpsi_c, workspace, who, conf != nullptr);
   if (st != WVL_OK || P->nsf == 0) return st;
-  for (size_t c = 0; c < P->lay.chunks.size(); ++c)
-    if ((st = apply_chunk(P, c, dt == WVL_F64, terms, psi_c, pot, hpsi_c, e_kin, e_pot, workspace,
-                          accumulate, P->ctx->stream, conf)) != WVL_OK)
-      return st;
-  return WVL_OK;
+  return apply_chunks(P, dt == WVL_F64, terms, psi_c, pot, hpsi_c, e_kin, e_pot, workspace,
+                      accumulate, P->ctx->stream, conf);
 }
 
 wvl_status wvl_apply_local_ham(wvl_plan* plan, wvl_dtype dt, uint32_t terms, const void* psi_c,
@@ -2154,8 +2187,7 @@ static wvl_status capture_step(wvl_plan* P, wvl_dtype dt, uint32_t terms, const 
   wvl_status st = he == hipSuccess ? WVL_OK
                                    : hip_fail(ctx, "graph capture", "hipStreamBeginCapture", he);
   if (st == WVL_OK && P->nsf > 0) {
-    for (size_t c = 0; st == WVL_OK && c < P->lay.chunks.size(); ++c)
-      st = apply_chunk(P, c, f64, terms, psi_c, pot, hpsi_c, e_kin, e_pot, workspace, 0, cs);
+    st = apply_chunks(P, f64, terms, psi_c, pot, hpsi_c, e_kin, e_pot, workspace, 0, cs);
     for (int ket_out = 0; st == WVL_OK && ket_out < 2; ++ket_out) {
       double* val = ket_out ? h_val : s_val;
       const PatternCache& pc = P->pat[ket_out];
