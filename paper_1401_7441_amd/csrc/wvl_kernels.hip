@@ -1302,7 +1302,7 @@ __global__ __launch_bounds__(TPB) void k_cg_init(const SfDev* __restrict__ sfs,
 // Bound by the latency of phase 2's loads and by its vector instructions.
 // 500 functions of radius 5-7 bohr at 0.037 per bohr^3, FP32: 69.0 ms with one
 // lookup and one value at a time, each waited for; 6.1 ms with the lists and 8
-// or 4 runs under way; 4.6 ms with neighbour records of 80 instead of 136 bytes
+// or 4 runs under way; 4.6 ms with neighbour records of 72 instead of 144 bytes
 // (five blocks per CU by LDS), 16 runs and multiply-adds under the lane mask.
 constexpr int kGradNb = 256;
 constexpr int kGradCap = 128;     // list entries per wave: 64 neighbours, two runs each
@@ -1317,6 +1317,7 @@ struct GradNb {
   int64_t rr, cin, cout;
   double a, m;
 };
+static_assert(sizeof(GradNb) == 72);
 // a run of |phi_d> or H|phi_d> in the row: points x0 .. x1, the value of
 // component comp at p[per x + comp], its coefficient
 template <typename T> struct GradRun {
@@ -1342,7 +1343,7 @@ __device__ __forceinline__ void grad_add(const GradRun<T>* list, int n, const in
       c[u] = e.c;
 #pragma unroll
       for (int k = 0; k < NS; ++k) {
-        in[u][k] = (uint32_t)(gx[k] - e.x0) <= (uint32_t)x1 && x1 >= 0;
+        in[u][k] = (uint32_t)gx[k] - (uint32_t)e.x0 <= (uint32_t)x1 && x1 >= 0;
         v[u][k] = T(0);
         if (in[u][k]) v[u][k] = e.p[lc[k]];
       }
@@ -1417,7 +1418,7 @@ __global__ __launch_bounds__(256, 4) void k_grad_rows(const SfDev* __restrict__ 
             for (int k = 0; k < 4; ++k) {
               const int j = j0 + 64 * k + lane;
               const int pt = j / per, comp = j - per * pt;
-              gx[k] = j < len ? as + pt : INT32_MIN;   // meets no run
+              gx[k] = j < len ? as + pt : INT32_MIN;   // meets no run (unsigned differences)
               lc[k] = per * (as + pt) + comp;
               acc[k] = 0.0;
             }
