@@ -246,7 +246,8 @@ wvl_status wvl_kinetic(wvl_plan* plan, wvl_dtype dt, const void* psi_c, void* hp
  * the device, cached in the plan, *nnz set (the call synchronizes the
  * stream).  Otherwise rowptr (device int64[nsf+1]), col (device int32[nnz])
  * and val (device double[nnz]) are filled, each optional; values are dot
- * products accumulated in double in an order fixed per pair.  For S with
+ * products accumulated in double in an order fixed per pair, the same in every
+ * plan and for every number of waves a pair gets.  For S with
  * bra_c == ket_c the pairs a <= b are summed and each value written to
  * (a, b) and (b, a); a pair's sum does not depend on which side is the bra,
  * so the values are those of the full computation, bit for bit. */
@@ -322,7 +323,9 @@ wvl_status wvl_density(wvl_plan* plan, wvl_dtype dt, const void* fine, const int
  *            8 ((npl + 7) nnz + 2 npl + 6) bytes keeps every T^i (one
  *            recursion); at least 8 (9 nnz + npl + 5) bytes runs the
  *            recursion twice.  Both give the same values, bit for bit.
- * All arithmetic is in double, sums in fixed orders (bitwise reproducible).
+ * All arithmetic is in double, sums in fixed orders (bitwise reproducible; the
+ * order within a product's entry is that of one of two kernels, chosen by the
+ * number of functions plus the longest row: up to 8,192 or more).
  * Synchronizes (the traces and bounds come back to the host).  Errors:
  * WVL_EINVAL for bad parameters, null buffers, a scratch below the smaller
  * size, or S and H that make H~' not finite; WVL_EUNSUPPORTED when P is
@@ -402,9 +405,10 @@ wvl_status wvl_precondition(wvl_plan* plan, wvl_dtype dt, const void* g_c, const
  * workspace regions.
  *
  * wvl_graph_create captures one step into a HIP graph: the local-H apply of
- * every function (the bins one after the other, in one linear graph), then, when s_val / h_val are non-NULL, the overlap values (bra =
- * ket = psi_c) and the Hamiltonian values (bra psi_c, ket hpsi_c) on the
- * plan's patterns, in the CSR order wvl_sparse_overlap reports.  Arguments
+ * every function (the bins one after the other, in one linear graph), then,
+ * when s_val / h_val are non-NULL, the overlap values (bra = ket = psi_c) and
+ * the Hamiltonian values (bra psi_c, ket hpsi_c) on the plan's patterns, in the
+ * CSR order wvl_sparse_overlap reports.  Arguments
  * are those of wvl_apply_local_ham; every buffer must stay valid while the
  * graph lives.  Patterns are built before the capture (this synchronizes).
  * wvl_graph_launch enqueues the graph on the context's stream; results are

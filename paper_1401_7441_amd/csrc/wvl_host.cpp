@@ -779,8 +779,11 @@ static int back_blocks(const SfDev& S) {
   const int64_t b = cu / (8 * plane_lds_back(S.n[0], S.n[1], S.ext) + fix);
   return (int)(64 * std::min<int64_t>(4, a) + std::min<int64_t>(4, b));
 }
-// fewest functions of a launch split off for its LDS size (their blocks fill
-// the chip several times: 100 or more per function)
+// fewest functions of a launch split off for its LDS size.  n boxes of 24^3 and n
+// of 36^3 points, one launch and two: n = 16 0.443 / 0.490 ms in FP32, 0.97 / 0.93
+// in FP64; 32 0.838 / 0.874, 1.91 / 1.76; 64 1.619 / 1.616, 3.78 / 3.46; 128 3.19 /
+// 3.14, 7.54 / 6.87.  34^3 and 46^3 at 64: 3.49 / 3.30, 6.55 / 6.46; 16: 0.907 /
+// 0.914, 1.67 / 1.69.  From 64 on no pair of sizes loses in either type.
 constexpr int kLdsSplit = 64;
 
 // Builds the layout for `nbins` bins; false (with a message) when a box

@@ -135,8 +135,8 @@ constexpr int64_t plane_lds_back(int64_t n0, int64_t n1, int64_t e) {
 }
 // Whether a function of this box takes the plane kernels in an element type
 // of sz bytes: its planes fit the LDS of a CU (160 KiB, less the static
-// part).  In FP64 boxes of up to about 50 points per axis do, in FP32 of
-// about 70.  The rule looks at the function's own box only, so that results
+// part).  With ext 8, cubes of up to 49 points per axis do in FP64, of 66 in FP32;
+// flatter boxes up to kPlaneMaxN points along any axis.  The rule looks at the function's own box only, so that results
 // do not depend on the other functions of a plan.
 constexpr int kPlaneMaxN = 96;    // bits of k_back_plane's row masks
 constexpr bool plane_fits(int64_t n0, int64_t n1, int64_t n2, int64_t e, int sz) {

@@ -10,7 +10,7 @@
 //                 k_pot_column and k_up_z of wvl_fused.hip here
 //   k_kin_slab    (y, a2): uncompress one x-z slab, z part of the kinetic
 //                 term -> OZ
-//   k_back_plane  (z', a3, 24 rows y'): y and x down passes, x and y parts of
+//   k_back_plane  (z', a3, 24 or 32 rows y'): y and x down passes, x and y parts of
 //                 the kinetic term from the uncompressed plane, OZ, and the
 //                 compression onto the output pattern, in LDS
 //
@@ -902,7 +902,7 @@ __global__ __launch_bounds__(kPlaneThreads, sizeof(T) == 4 ? 4 : 2) void k_up_ki
 // strips) run on one XCD, whose L2 joins their stores and serves their shared
 // reads.  24 rows: three row tiles of the x pass, and LDS for four (FP32) or
 // two (FP64) blocks per CU at the usual box sizes; the phases of one block are
-// covered by the others.
+// covered by the others.  32 where that is all of the box's rows (plane_strip).
 // FP64 planes fill half a CU's LDS or more: twice the waves per block keep
 // four per SIMD.  WIDE, FP32 where one block fills a CU's LDS (plane_wide): 1,024
 // threads for 256, so that its phases are not four waves' on their own (60 boxes
