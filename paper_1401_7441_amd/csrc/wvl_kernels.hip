@@ -206,12 +206,14 @@ __global__ __launch_bounds__(64) void k_pattern(const SfDev* __restrict__ sfs,
 // each under way; then the whole wave takes the fine runs (seven wavelets per
 // point: 70 values on average) and the further ones, four under way.  Every
 // lane's partial sum and the final tree have an order fixed by the pair.
-// Bound by the latency of each wave's chain of loads and by the lines that L1
-// and L2 keep for the others (half of the requests of 1,000 functions miss L2),
-// so that registers stay below those that let eight waves run per SIMD.  H of
-// 1,000 functions of radius 5-7 bohr (301,162 entries) in FP64: 5.63 ms with
-// one wave per pair and 16 lanes per fine run, 5.33 in this form; FP32, 4,000
-// functions: 9.31 and 7.77 ms; S of 56 functions: 112 and 31 us.
+// Bound by the lines read from beyond L2: H of 1,000 functions of radius 5-7 bohr
+// (301,162 entries) reads 18.9 GB in FP32 and 31.5 GB in FP64 there (42 and 46 % of
+// the requests miss), 4.8 and 5.8 TB/s (a large copy: 4.8); seven waves per SIMD
+// are resident and wait three quarters (FP64: two thirds) of their time, the
+// vector units are 53 and 36 % busy.  Registers stay below those that let eight
+// waves run.  That H in FP64: 5.63 ms with one wave per pair and 16 lanes per fine
+// run, 5.4 in this form; FP32, 4,000 functions: 9.46 and 7.92 ms; S
+// of 56 functions: 112 and 31 us.
 // mirror (may be NULL): for the pair at processing position s, the CSR
 // position that receives the same value as well (the transposed pair of a
 // symmetric matrix), or -1.

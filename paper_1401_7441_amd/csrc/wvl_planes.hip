@@ -15,10 +15,10 @@
 //                 compression onto the output pattern, in LDS
 //
 // Against the column kernels a step writes and reads three arrays (G1, G2, OZ)
-// instead of nine: 17 instead of 38 GB of traffic for 1,000 functions of radius
-// 5-7 bohr in FP32 (13.0 -> 8.1 ms; FP64 25.2 -> 14.7 ms), and one launch of a
+// instead of nine: 16 instead of 38 GB of traffic for 1,000 functions of radius
+// 5-7 bohr in FP32 (13.0 -> 8.1 ms; FP64 25.3 -> 15.0 ms), and one launch of a
 // single function waits for four short kernels instead of nine serial chains
-// (FP64 442 -> 52 us).
+// (FP64 442 -> 53 us).
 //
 // The down passes, and in FP64 the up passes, are products with banded Toeplitz
 // matrices and run on the matrix cores (16x16x4): an output tile is 16 fine
