@@ -206,14 +206,15 @@ __global__ __launch_bounds__(64) void k_pattern(const SfDev* __restrict__ sfs,
 // each under way; then the whole wave takes the fine runs (seven wavelets per
 // point: 70 values on average) and the further ones, four under way.  Every
 // lane's partial sum and the final tree have an order fixed by the pair.
-// Bound by the lines read from beyond L2: H of 1,000 functions of radius 5-7 bohr
-// (301,162 entries) reads 18.9 GB in FP32 and 31.5 GB in FP64 there (42 and 46 % of
-// the requests miss), 4.8 and 5.8 TB/s (a large copy: 4.8); seven waves per SIMD
-// are resident and wait three quarters (FP64: two thirds) of their time, the
-// vector units are 53 and 36 % busy.  Registers stay below those that let eight
-// waves run.  That H in FP64: 5.63 ms with one wave per pair and 16 lanes per fine
-// run, 5.4 in this form; FP32, 4,000 functions: 9.46 and 7.92 ms; S
-// of 56 functions: 112 and 31 us.
+// Bound by the lines read from beyond L2, in FP64 by their bytes: H of 1,000
+// functions of radius 5-7 bohr (301,162 entries) reads 31.4 GB there, 5.8 TB/s (a
+// large copy: 4.8); in FP32 18.9 GB, 4.8 TB/s, but 14.7 GB with two waves per pair
+// take no less time, so there the wait for a line counts as well.  Seven waves per
+// SIMD are resident and wait for two thirds (FP64) and three quarters of their
+// time, the vector units are 36 and 53 % busy.  Registers stay below those that
+// let eight waves run.  That H in FP64: 5.63 ms with one wave per pair and 16 lanes
+// per fine run, 5.4 in this form; FP32, 4,000 functions: 9.46 and 7.92 ms; S of 56
+// functions: 112 and 31 us.
 // mirror (may be NULL): for the pair at processing position s, the CSR
 // position that receives the same value as well (the transposed pair of a
 // symmetric matrix), or -1.
