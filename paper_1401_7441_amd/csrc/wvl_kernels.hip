@@ -211,8 +211,8 @@ __global__ __launch_bounds__(64) void k_pattern(const SfDev* __restrict__ sfs,
 // large copy: 4.8); in FP32 18.9 GB, 4.8 TB/s, but 14.7 GB with two waves per pair
 // take no less time, so there the wait for a line counts as well.  Seven waves per
 // SIMD are resident and wait for two thirds (FP64) and three quarters of their
-// time, the vector units are 36 and 53 % busy.  Registers stay below those that
-// let eight waves run.  That H in FP64: 5.63 ms with one wave per pair and 16 lanes
+// time; a SIMD issues 0.36 and 0.53 vector instructions in four cycles (the FP32
+// up pass 1.3).  Registers stay below those that let eight waves run.  That H in FP64: 5.63 ms with one wave per pair and 16 lanes
 // per fine run, 5.4 in this form; FP32, 4,000 functions: 9.46 and 7.92 ms; S of 56
 // functions: 112 and 31 us.
 // mirror (may be NULL): for the pair at processing position s, the CSR
