@@ -251,7 +251,7 @@ struct wvl_plan {
   std::vector<int32_t> order[2];
   size_t max_ws = 0;                  // the caller's workspace bound (0: none)
   Layout lay;
-  Layout in_place;                    // column kernels for all (apply with hpsi over psi)
+  Layout in_place;                    // column kernels for all (an output over psi)
   int64_t ws_cap[2] = {0, 0};         // workspace bytes reported (F32, F64)
   hipStream_t capture = nullptr;      // the stream that graphs are captured on
   int64_t layout_version = 0;         // bumped when the autotuner changes the layout
@@ -1227,13 +1227,14 @@ static wvl_status apply_args(wvl_plan* P, wvl_dtype dt, uint32_t terms, const vo
 // -> 852 us, FP32, 60 of 16-48 points per axis 1.08 -> 1.21 ms.
 constexpr int64_t kUpKinBlocks = 1024;
 
-// Whether hpsi_c is written over psi_c.  The plane kernels' back pass reads psi
-// while other blocks write hpsi; the column kernels read all of a chunk's psi
-// before they write, so an apply in place takes them.
-static bool in_place(const wvl_plan* P, int f64, const void* psi_c, const void* hpsi_c) {
+// Whether an output of n elements is written over psi_c.  The plane kernels' back
+// pass reads psi while other blocks write hpsi, and their classes cut a bin into
+// chunks; the column kernels read all of a chunk's psi before they write, so a call
+// in place takes them.
+static bool in_place(const wvl_plan* P, int f64, const void* psi_c, const void* out, int64_t n) {
   const int64_t sz = f64 ? 8 : 4;
-  const char *a = (const char*)psi_c, *b = (const char*)hpsi_c;
-  return a < b + P->info.out_coefs * sz && b < a + P->info.in_coefs * sz;
+  const char *a = (const char*)psi_c, *b = (const char*)out;
+  return a < b + n * sz && b < a + P->info.in_coefs * sz;
 }
 
 // Enqueues the stages of chunk c of the layout on stream st.
@@ -1330,7 +1331,7 @@ static wvl_status apply_chunks(wvl_plan* P, int f64, uint32_t terms, const void*
                                const void* pot, void* hpsi_c, double* e_kin, double* e_pot,
                                void* workspace, int accumulate, hipStream_t st,
                                const double* conf = nullptr) {
-  const bool over = in_place(P, f64, psi_c, hpsi_c);
+  const bool over = in_place(P, f64, psi_c, hpsi_c, P->info.out_coefs);
   const Layout& lay = over ? P->in_place : P->lay;
   const SfWork* d_wk = over ? P->d_wk_in_place : P->d_wk;
   wvl_status rc = WVL_OK;
@@ -1605,9 +1606,10 @@ wvl_status wvl_synthesize(wvl_plan* P, wvl_dtype dt, const void* psi_c, void* fi
   if (P->nsf == 0) return WVL_OK;
   if (!psi_c || !fine || !workspace) return fail(ctx, WVL_EINVAL, "wvl_synthesize: null buffer");
   const int f64 = dt == WVL_F64 ? 1 : 0;
-  for (size_t c = 0; c < P->lay.chunks.size(); ++c) {
-    const ChunkDev& ch = P->lay.chunks[c];
-    const SfWork* wk = P->d_wk + ch.sf0;
+  const bool over = in_place(P, f64, psi_c, fine, P->info.fine_box);
+  const Layout& lay = over ? P->in_place : P->lay;
+  for (const ChunkDev& ch : lay.chunks) {
+    const SfWork* wk = (over ? P->d_wk_in_place : P->d_wk) + ch.sf0;
     hipStream_t st = ctx->stream;
     if (ch.plane[f64]) {
       WVL_LAUNCH(ctx, KK_UP_PLANE,

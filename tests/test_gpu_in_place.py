@@ -121,3 +121,25 @@ def test_apply_in_place(cases, dtype, tol, ext, bound, shift):
     o = own.cpu().numpy()
     for k in range(n):
         assert rel_err(o[case.out_slice(k)], case.oracle(k)[0]) < tol, k
+
+
+@pytest.mark.parametrize("ext,bound", [(0, 0), (4, 0)])
+@pytest.mark.parametrize("dtype,tol", [("f64", 1e-12), ("f32", 1e-5)])
+def test_synthesize_in_place(cases, dtype, tol, ext, bound):
+    """The values on the fine boxes written over the coefficients, against those in a
+    buffer of their own."""
+    case = cases[ext]
+    dt = torch.float32 if dtype == "f32" else torch.float64
+    plan = W.Plan(W.Context(case.g.h, case.g.grid_n), case.rec, case.segs, max_workspace=bound)
+    nin, nf = plan.info["in_coefs"], plan.info["fine_box"]
+    assert plan.info["chunks"] > 1 and nf > nin
+    ws = plan.new_workspace(dt)
+    want = torch.zeros(nf, dtype=dt, device="cuda")
+    W.synthesize(plan, torch.tensor(case.psi, dtype=dt, device="cuda"), want, workspace=ws)
+    _print(f"case: synthesis in place, {dtype}, ext {ext}")
+    for at in (0, nf // 2, nf - nin):
+        buf = torch.zeros(nf, dtype=dt, device="cuda")
+        buf[at:at + nin] = torch.tensor(case.psi, dtype=dt, device="cuda")
+        W.synthesize(plan, buf[at:at + nin], buf, workspace=ws)
+        torch.cuda.synchronize()
+        assert rel_err(buf.cpu().numpy(), want.cpu().numpy()) < tol, at
